@@ -2,8 +2,11 @@
 // sectors Eq. sreverse_sum) and the fused energy of Eq. vqe_energy: the
 // full-space kernel, launch planning of the sector kernels (whose device code
 // lives in sector.h), and the C ABI entry points, single and batched.
+#include <iterator>
 #include <mutex>
+#include <string>
 
+#include "panel.h"
 #include "sector.h"
 
 namespace pbs {
@@ -51,18 +54,21 @@ __global__ __launch_bounds__(kBlock) void k_apply_full(uint64_t dim, uint32_t n_
 
 
 // Per-job sums of workgroup partials (one workgroup per job, fixed order).
-__global__ __launch_bounds__(kBlock) void k_batch_finish(const BatchJob* jobs, uint32_t n_jobs, uint32_t total_blocks,
-                                                         const double* partial, double* result) {
-  const uint32_t j = blockIdx.x;
-  const uint32_t b0 = jobs[j].block_base;
-  const uint32_t b1 = j + 1 < n_jobs ? jobs[j + 1].block_base : total_blocks;
+struct FinishJob {
+  uint32_t first, count;  // the job's partials
+  uint32_t slot, pad;     // its place in the caller's list
+};
+__global__ __launch_bounds__(kBlock) void k_batch_finish(const FinishJob* jobs, const double* partial,
+                                                         double* result) {
+  const FinishJob J = jobs[blockIdx.x];
   double a = 0, b = 0, c = 0;
-  for (uint32_t i = b0 + threadIdx.x; i < b1; i += kBlock) {
-    a += partial[3ull * i];
-    b += partial[3ull * i + 1];
-    c += partial[3ull * i + 2];
+  for (uint32_t i = threadIdx.x; i < J.count; i += kBlock) {
+    const uint64_t at = 3ull * (static_cast<uint64_t>(J.first) + i);
+    a += partial[at];
+    b += partial[at + 1];
+    c += partial[at + 2];
   }
-  block_reduce3_store<kBlock>(a, b, c, result + 3ull * jobs[j].slot);
+  block_reduce3_store<kBlock>(a, b, c, result + 3ull * J.slot);
 }
 
 // Sums per-workgroup partials in a fixed order (deterministic).
@@ -93,6 +99,16 @@ int device_lds_limit() {
     return 64 * 1024;
   }
   return v;
+}
+
+uint32_t device_cus() {
+  int dev = 0, v = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  return static_cast<uint32_t>(v);
 }
 
 // Fills the sector kernel's arguments and LDS layout for this operator/space.
@@ -314,6 +330,51 @@ bool plan_rows(const pbs_grouped& h, const SectorArgs& a, bool r16, bool expval,
   return true;
 }
 
+struct PanelShape {
+  int variant = 0;  // of kPanelVariants
+  size_t lds = 0;
+};
+
+// Arguments and shape of the panel kernel when the operator's factor tables
+// allow it for this sector and every factored part is switched on.
+bool plan_panel(const pbs_grouped& h, const pbs_space& sp, PanelArgs* out, PanelShape* shape) {
+  const FactorPlan* F = h.fplan.get();
+  if (!h.real_coef || F == nullptr || !F->panel || h.fact_on != (kFactZero | kFactMoves | kFactAlpha)) return false;
+  if (F->n_orb != sp.n_orb || F->n_alpha != sp.n_alpha || F->n_beta != sp.n_beta) return false;
+  PanelArgs a{};
+  a.dim_alpha = static_cast<uint32_t>(sp.dim_alpha);
+  a.dim_beta = static_cast<uint32_t>(sp.dim_beta);
+  shape->variant = F->panel_variant;
+  const PanelVariant& v = kPanelVariants[F->panel_variant];
+  a.n_blk = panel_blocks(a.dim_alpha, v.rows, device_cus());
+  a.n_tiles = F->n_tiles;
+  a.n_img = F->n_img;
+  a.n_pairs = h.n_pairs;
+  a.n_bb = F->n_bb;
+  a.diag_rank = F->diag_rank;
+  a.diag_off = F->diag_off;
+  a.alist_off = F->alist_off.get();
+  a.alist_src = F->alist_src.get();
+  a.alist_c = F->alist_c.get();
+  a.plist_off = F->plist_off.get();
+  a.plist_src = F->plist_src.get();
+  a.plist_cls = F->plist_cls.get();
+  a.pimg = F->pimg.get();
+  a.c0img = F->c0img.get();
+  a.diag_a = F->diag_a.get();
+  a.cls_f = F->cls_f.get();
+  a.fz = F->fz.get();
+  a.bb_src = F->bb_src.get();
+  a.bb_c = F->bb_c.get();
+  a.pull = F->pull.get();
+  a.pull_cnt = F->pull_cnt.get();
+  *out = a;
+  const size_t stage = sp.dim_beta * 32u;
+  const size_t lists = sp.dim_alpha * (8u * v.rows + 4u) + 4u * kPW;
+  shape->lds = align16(static_cast<uint32_t>(std::max({stage, lists, static_cast<size_t>(kPanelMixBytes + kPanelPullBytes)})));
+  return true;
+}
+
 // Launches the apply (EXPVAL: with the energy partials) for target alpha
 // rows [row_begin, row_end) of a sector space (the whole space by default);
 // out holds those rows only, from row_begin's first column.  Returns the
@@ -340,6 +401,21 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     // the kernels store target t = row * dim_beta + column at out[t]: shift
     // the base so that row_begin's first column lands at out[0]
     if (o) o = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(o) - row_begin * sp.dim_beta * sizeof(T));
+    PanelArgs pa;
+    PanelShape ps;
+    if (plan_panel(h, sp, &pa, &ps)) {
+      pa.row_begin = static_cast<uint32_t>(row_begin);
+      pa.row_end = static_cast<uint32_t>(row_end);
+      // the blocks that hold rows row_begin and row_end - 1
+      auto block_of = [&](uint64_t row) { return static_cast<uint32_t>(((row + 1) * pa.n_blk - 1) / pa.dim_alpha); };
+      pa.blk0 = block_of(row_begin);
+      const uint32_t blocks = block_of(row_end - 1) - pa.blk0 + 1u;
+      void* kern = panel_kernel(dt, EXPVAL, false, ps.variant);
+      void* args[] = {&pa, &p, &o, &partial};
+      PBS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(ps.lds)));
+      PBS_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(kPanelLanes), args, ps.lds, s));
+      return rows;
+    }
     RowsLayout Lr;
     size_t lds_rows = 0;
     if (h.real_coef && plan_rows(h, a, r16, EXPVAL, &Lr, &lds_rows)) {
@@ -509,7 +585,16 @@ pbs_status pbs_expval_noalloc(const pbs_grouped* h, const pbs_space* sp, pbs_dty
 struct pbs_batch {
   uint32_t n_jobs = 0;
   uint32_t total_blocks = 0;  // work items (alpha row, column chunk) over all jobs
-  uint32_t grid = 0;          // workgroups launched (fewer than the items when persistent)
+  // jobs of the sector kernel: one launch
+  uint32_t n_sector = 0, sector_items = 0;
+  uint32_t grid = 0;  // workgroups launched (fewer than the items when persistent)
+  // jobs of the panel kernel: one launch per variant
+  struct PanelLaunch {
+    int variant = 0;
+    uint32_t first = 0, n = 0, items = 0, grid = 0;  // jobs first .. first + n - 1 of pjobs
+    size_t lds = 0;
+  };
+  std::vector<PanelLaunch> panels;
   pbs_dtype dt = PBS_C64;
   bool r16 = false, row_lds = false, realc = false;
   size_t lds = 0;
@@ -520,6 +605,9 @@ struct pbs_batch {
   std::vector<const void*> psi;
   std::vector<void*> out;
   pbs::DevBuf<pbs::BatchJob> jobs;
+  pbs::DevBuf<pbs::PanelJob> pjobs;
+  pbs::DevBuf<pbs::FinishJob> finish;
+  std::string table;  // the job tables of the schedule in use, byte for byte (the tuner compares them)
   pbs::DevBuf<double> partial;
 };
 
@@ -544,35 +632,53 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   const bool given = config & PBS_BATCH_GIVEN_ORDER, allow_row = !(config & PBS_BATCH_NO_ROW_STAGING);
   const bool qenum = !(config & PBS_BATCH_NO_DOUBLE_MOVES), penum = !(config & PBS_BATCH_NO_SINGLE_MOVES);
   const bool factd = !(config & PBS_BATCH_NO_FACTORED);
-  std::vector<BatchJob> jobs(n);
-  std::vector<double> cost(n);
-  std::vector<uint64_t> items(n);
+  // jobs that a single launch gives to the panel kernel run on it here too,
+  // unless a flag asks for another evaluation
+  std::vector<PanelJob> pj(n);
+  std::vector<PanelShape> shape(n);
+  std::vector<uint32_t> sector;
+  std::vector<std::vector<uint32_t>> by_variant(std::size(kPanelVariants));
+  for (uint32_t i = 0; i < n; ++i) {
+    if (allow_row && qenum && penum && factd && plan_panel(*B.h[i], *B.sp[i], &pj[i].args, &shape[i]))
+      by_variant[shape[i].variant].push_back(i);
+    else
+      sector.push_back(i);
+  }
+  const uint32_t ns = static_cast<uint32_t>(sector.size());
+  std::vector<BatchJob> jobs(ns);
+  std::vector<double> cost(ns);
+  std::vector<uint64_t> items(ns);
+  auto cost_of = [&](uint32_t i) {
+    return static_cast<double>(B.sp[i]->dim) * static_cast<double>(B.h[i]->n_pterm + 1);
+  };
   // one launch shares one kernel variant: rows staged only if every job's
   // row fits, LDS rank tables only if every job has n_orb <= 16
   bool r16 = true, rowlds = allow_row, realc = true;
-  for (uint32_t i = 0; i < n; ++i) realc = realc && B.h[i]->real_coef;
-  for (uint32_t i = 0; i < n; ++i) {
+  for (uint32_t i : sector) realc = realc && B.h[i]->real_coef;
+  for (uint32_t k = 0; k < ns; ++k) {
     bool job_r16 = false;
-    plan_sector(*B.h[i], *B.sp[i], esz, allow_row, realc, &jobs[i].args, &job_r16, penum, qenum, factd);
+    plan_sector(*B.h[sector[k]], *B.sp[sector[k]], esz, allow_row, realc, &jobs[k].args, &job_r16, penum, qenum,
+                factd);
     r16 = r16 && job_r16;
-    rowlds = rowlds && jobs[i].args.row_lds;
+    rowlds = rowlds && jobs[k].args.row_lds;
   }
   size_t lds = 0;
-  for (uint32_t i = 0; i < n; ++i) {
+  for (uint32_t k = 0; k < ns; ++k) {
+    const uint32_t i = sector[k];
     bool job_r16 = false;
     const Launch L =
-        plan_sector(*B.h[i], *B.sp[i], esz, rowlds, realc, &jobs[i].args, &job_r16, penum, qenum, factd);
-    if (!r16) jobs[i].args.rank16 = nullptr;
-    jobs[i].psi = B.psi[i];
-    jobs[i].out = B.out[i];
-    jobs[i].chunks = L.chunks;
-    jobs[i].block_base = 0;
-    jobs[i].slot = i;  // original position (energies are written there)
-    jobs[i].rows = static_cast<uint32_t>(B.sp[i]->dim_alpha);
-    jobs[i].pad = 0;
+        plan_sector(*B.h[i], *B.sp[i], esz, rowlds, realc, &jobs[k].args, &job_r16, penum, qenum, factd);
+    if (!r16) jobs[k].args.rank16 = nullptr;
+    jobs[k].psi = B.psi[i];
+    jobs[k].out = B.out[i];
+    jobs[k].chunks = L.chunks;
+    jobs[k].block_base = 0;
+    jobs[k].slot = i;  // original position (energies are written there)
+    jobs[k].rows = static_cast<uint32_t>(B.sp[i]->dim_alpha);
+    jobs[k].pad = 0;
     lds = std::max(lds, L.lds);
-    cost[i] = static_cast<double>(B.sp[i]->dim) * static_cast<double>(B.h[i]->n_pterm + 1);
-    items[i] = static_cast<uint64_t>(B.sp[i]->dim_alpha) * L.chunks;
+    cost[k] = cost_of(i);
+    items[k] = static_cast<uint64_t>(B.sp[i]->dim_alpha) * L.chunks;
   }
   // largest jobs first, so the launch does not end on a long straggler
   const BatchPlan plan = batch_plan(cost, items, given);
@@ -581,52 +687,115 @@ void fill_batch(pbs_batch& B, uint32_t config) {
                               : order_field == PBS_BATCH_ORDER_ROW_FAST ? kOrderRowFast
                               : order_field == PBS_BATCH_ORDER_XCD_ROWS ? kOrderXcdRows
                               : (rowlds ? kOrderRowFast : kOrderXcdRows);
-  for (uint32_t i = 0; i < n; ++i) jobs[i].order = grid_order;
-  PBS_REQUIRE(plan.total < (1ull << 31), PBS_ERR_RANGE, "batch needs more than 2^31 workgroups");
-  std::vector<BatchJob> sorted(n);
-  for (uint32_t k = 0; k < n; ++k) {
+  for (uint32_t k = 0; k < ns; ++k) jobs[k].order = grid_order;
+  uint64_t all = 0, rows = 0;
+  for (uint32_t i = 0; i < n; ++i) all += B.sp[i]->dim_alpha * ((B.sp[i]->dim_beta + kSB - 1) / kSB);
+  PBS_REQUIRE(all < (1ull << 31), PBS_ERR_RANGE, "batch needs more than 2^31 workgroups");
+  std::vector<BatchJob> sorted(ns);
+  std::vector<FinishJob> finish;
+  for (uint32_t k = 0; k < ns; ++k) {
     sorted[k] = jobs[plan.order[k]];
     sorted[k].block_base = static_cast<uint32_t>(plan.base[k]);
+    finish.push_back({sorted[k].block_base, static_cast<uint32_t>(items[plan.order[k]]), sorted[k].slot, 0u});
   }
-  const uint64_t base = plan.total;
   if (lds > 64 * 1024) {
     for (bool ev : {false, true})
       PBS_HIP(hipFuncSetAttribute(sector_kernel(B.dt, ev, true, r16, rowlds, realc),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
   }
-  if (B.partial.n < 3ull * base) B.partial.alloc(3ull * base);
-  if (B.jobs.n < n) B.jobs.alloc(n);
-  PBS_HIP(hipMemcpy(B.jobs.get(), sorted.data(), n * sizeof(BatchJob), hipMemcpyHostToDevice));
-  B.total_blocks = static_cast<uint32_t>(base);
+  const uint32_t cus = device_cus();
+  // panel launches, the costliest variant first; a launch of several jobs
+  // takes full row blocks once they fill the device for some rounds
+  std::vector<PanelJob> psorted;
+  std::vector<pbs_batch::PanelLaunch> panels;
+  for (int v = static_cast<int>(std::size(kPanelVariants)) - 1; v >= 0; --v) {
+    const std::vector<uint32_t>& list = by_variant[v];
+    if (list.empty()) continue;
+    const uint32_t r = kPanelVariants[v].rows;
+    uint64_t least = 0;
+    for (uint32_t i : list) least += (B.sp[i]->dim_alpha + r - 1) / r;
+    std::vector<double> pcost;
+    std::vector<uint64_t> pitems;
+    pbs_batch::PanelLaunch P;
+    P.variant = v;
+    P.first = static_cast<uint32_t>(psorted.size());
+    P.n = static_cast<uint32_t>(list.size());
+    for (uint32_t i : list) {
+      if (least >= 4ull * cus) pj[i].args.n_blk = (pj[i].args.dim_alpha + r - 1) / r;
+      pj[i].args.row_end = pj[i].args.dim_alpha;
+      pj[i].psi = B.psi[i];
+      pj[i].out = B.out[i];
+      pcost.push_back(cost_of(i));
+      pitems.push_back(pj[i].args.n_blk);
+      P.lds = std::max(P.lds, shape[i].lds);
+    }
+    const BatchPlan pp = batch_plan(pcost, pitems, given);
+    for (uint32_t k = 0; k < P.n; ++k) {
+      const uint32_t i = list[pp.order[k]];
+      pj[i].block_base = static_cast<uint32_t>(pp.base[k]);
+      pj[i].first = static_cast<uint32_t>(plan.total + rows);
+      finish.push_back({pj[i].first, pj[i].args.dim_alpha, i, 0u});
+      rows += pj[i].args.dim_alpha;
+      psorted.push_back(pj[i]);
+    }
+    P.items = static_cast<uint32_t>(pp.total);
+    P.grid = config & PBS_BATCH_PERSISTENT ? std::min(P.items, cus) : P.items;  // one workgroup per compute unit
+    for (bool ev : {false, true})
+      PBS_HIP(hipFuncSetAttribute(panel_kernel(B.dt, ev, true, v), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  static_cast<int>(P.lds)));
+    panels.push_back(P);
+  }
+  const uint64_t parts = plan.total + rows;
+  if (B.partial.n < 3ull * parts) B.partial.alloc(3ull * parts);
+  if (B.jobs.n < ns) B.jobs.alloc(ns);
+  if (B.pjobs.n < psorted.size()) B.pjobs.alloc(psorted.size());
+  if (B.finish.n < n) B.finish.alloc(n);
+  if (ns) PBS_HIP(hipMemcpy(B.jobs.get(), sorted.data(), ns * sizeof(BatchJob), hipMemcpyHostToDevice));
+  if (!psorted.empty())
+    PBS_HIP(hipMemcpy(B.pjobs.get(), psorted.data(), psorted.size() * sizeof(PanelJob), hipMemcpyHostToDevice));
+  PBS_HIP(hipMemcpy(B.finish.get(), finish.data(), n * sizeof(FinishJob), hipMemcpyHostToDevice));
+  B.n_sector = ns;
+  B.sector_items = static_cast<uint32_t>(plan.total);
+  B.total_blocks = static_cast<uint32_t>(all);
+  B.panels = std::move(panels);
   B.r16 = r16;
   B.row_lds = rowlds;
   B.realc = realc;
   B.lds = lds;
-  B.grid = B.total_blocks;
-  if (config & PBS_BATCH_PERSISTENT) {
+  B.grid = B.sector_items;
+  if (ns && (config & PBS_BATCH_PERSISTENT)) {
     // as many workgroups as are resident at once (both kernel forms share
     // their resources); each walks the item list with a fixed stride
-    int dev = 0, cus = 0, per_cu = 0;
-    PBS_HIP(hipGetDevice(&dev));
-    PBS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    int per_cu = 0;
     PBS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sector_kernel(B.dt, false, true, r16, rowlds, realc),
                                                          kSB, lds));
-    const uint64_t resident = static_cast<uint64_t>(std::max(cus, 1)) * static_cast<uint64_t>(std::max(per_cu, 1));
-    B.grid = static_cast<uint32_t>(std::min<uint64_t>(B.total_blocks, resident));
+    const uint64_t resident = static_cast<uint64_t>(cus) * static_cast<uint64_t>(std::max(per_cu, 1));
+    B.grid = static_cast<uint32_t>(std::min<uint64_t>(B.sector_items, resident));
   }
+  B.table.assign(1, static_cast<char>(rowlds));
+  B.table.append(reinterpret_cast<const char*>(sorted.data()), ns * sizeof(BatchJob));
+  B.table.append(reinterpret_cast<const char*>(psorted.data()), psorted.size() * sizeof(PanelJob));
   B.config = config;
 }
 
 void launch_batch(const pbs_batch& b, double* energies, hipStream_t s) {
   const bool ev = energies != nullptr;
-  void* kern = sector_kernel(b.dt, ev, true, b.r16, b.row_lds, b.realc);
-  const BatchJob* jobs = b.jobs.get();
-  uint32_t n = b.n_jobs, items = b.total_blocks;
   double* partial = b.partial.get();
-  void* args[] = {&jobs, &n, &items, &partial};
-  PBS_HIP(hipLaunchKernel(kern, dim3(b.grid), dim3(kSB), args, b.lds, s));
+  if (b.n_sector) {
+    void* kern = sector_kernel(b.dt, ev, true, b.r16, b.row_lds, b.realc);
+    const BatchJob* jobs = b.jobs.get();
+    uint32_t n = b.n_sector, items = b.sector_items;
+    void* args[] = {&jobs, &n, &items, &partial};
+    PBS_HIP(hipLaunchKernel(kern, dim3(b.grid), dim3(kSB), args, b.lds, s));
+  }
+  for (const auto& P : b.panels) {
+    const PanelJob* jobs = b.pjobs.get() + P.first;
+    uint32_t n = P.n, items = P.items;
+    void* args[] = {&jobs, &n, &items, &partial};
+    PBS_HIP(hipLaunchKernel(panel_kernel(b.dt, ev, true, P.variant), dim3(P.grid), dim3(kPanelLanes), args, P.lds, s));
+  }
   if (ev) {
-    hipLaunchKernelGGL(k_batch_finish, dim3(n), dim3(kBlock), 0, s, jobs, n, b.total_blocks, partial, energies);
+    hipLaunchKernelGGL(k_batch_finish, dim3(b.n_jobs), dim3(kBlock), 0, s, b.finish.get(), partial, energies);
     PBS_HIP(hipGetLastError());
   }
 }
@@ -697,10 +866,7 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
     // time of schedule c (schedules with the same table and variant share one measurement)
     auto time_config = [&](uint32_t c) {
       fill_batch(*b, c);
-      std::string key(1, static_cast<char>(b->row_lds));
-      std::vector<BatchJob> table(b->n_jobs);
-      PBS_HIP(hipMemcpy(table.data(), b->jobs.get(), b->n_jobs * sizeof(BatchJob), hipMemcpyDeviceToHost));
-      key.append(reinterpret_cast<const char*>(table.data()), table.size() * sizeof(BatchJob));
+      const std::string& key = b->table;
       for (const auto& e : seen)
         if (e.first == key) return e.second;
       launch_batch(*b, nullptr, s);  // warm-up
@@ -711,7 +877,7 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
       float t = 0.f;
       PBS_HIP(hipEventElapsedTime(&t, e0, e1));
       const double per = static_cast<double>(t) / reps;
-      seen.emplace_back(std::move(key), per);
+      seen.emplace_back(key, per);
       return per;
     };
     uint32_t best = 0;

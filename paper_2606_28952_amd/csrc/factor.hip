@@ -247,6 +247,145 @@ __global__ __launch_bounds__(kImgBlock) void k_pair_images(uint32_t n_img, uint3
   }
 }
 
+// ---- tables of the panel kernel (panel.h)
+
+// Beta-only part of the X_alpha = 0 class per move and column: source column
+// (two moves share a word) and coefficient; moves in the order of
+// k_fact_moves, then of k_fact_quads.
+__global__ void k_panel_moves(uint64_t db, uint32_t n_orb, uint32_t n_beta, uint32_t n_moves, uint32_t n_bb,
+                              const uint32_t* str_b, const int32_t* pk, const int32_t* qk, const uint32_t* p_lo,
+                              const uint32_t* q_lo, const uint32_t* zb, const double* c, uint16_t* src, double* coef) {
+  const uint32_t ne = n_orb - n_beta, n_ep = ne * (ne - 1) / 2;
+  const uint32_t full = (n_orb == 32) ? 0xffffffffu : ((1u << n_orb) - 1u);
+  const uint64_t n = static_cast<uint64_t>(n_bb) * db;
+  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < n;
+       i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
+    const uint32_t m = static_cast<uint32_t>(i / db);
+    const uint64_t j = i % db;
+    const uint32_t tb = str_b[j], emp = ~tb & full;
+    uint32_t X;
+    int32_t k;
+    const uint32_t* lo;
+    if (m < n_moves) {
+      const uint32_t p = kth_bit(tb, m / ne), q = kth_bit(emp, m % ne);
+      const uint32_t a = p < q ? p : q, b = p < q ? q : p;
+      X = (1u << p) | (1u << q);
+      k = pk[b * (b - 1) / 2 + a];
+      lo = p_lo;
+    } else {
+      uint32_t a, b, d, e;
+      pair_at((m - n_moves) / n_ep, n_beta, a, b);
+      pair_at((m - n_moves) % n_ep, ne, d, e);
+      X = (1u << kth_bit(tb, a)) | (1u << kth_bit(tb, b)) | (1u << kth_bit(emp, d)) | (1u << kth_bit(emp, e));
+      k = qk[colex_rank(X)];
+      lo = q_lo;
+    }
+    src[((m / 2) * db + j) * 2 + (m & 1u)] = static_cast<uint16_t>(colex_rank(tb ^ X));
+    coef[m * db + j] = k >= 0 ? eval_rows(zb, c, lo[k], lo[k + 1], tb) : 0.0;
+  }
+}
+
+// Per alpha row: the alpha-dependent part of the X_alpha = 0 pair groups
+// (one value per orbital pair), then the diagonal group's folded factors.
+__global__ __launch_bounds__(128) void k_panel_rows(uint64_t da, uint32_t n_pairs, uint32_t rank, uint32_t fu0,
+                                                    const uint32_t* str_a, const uint32_t* al_lo,
+                                                    const uint32_t* al_za, const double* al_c, const uint32_t* fu_t0,
+                                                    const uint32_t* ft_za, const double* ft_c, double* img,
+                                                    double* diag) {
+  for (uint64_t i = blockIdx.x; i < da; i += gridDim.x) {
+    const uint32_t ta = str_a[i];
+    for (uint32_t j = threadIdx.x; j < n_pairs + rank; j += blockDim.x) {
+      if (j < n_pairs)
+        img[i * n_pairs + j] = eval_rows(al_za, al_c, al_lo[j], al_lo[j + 1], ta);
+      else
+        diag[i * rank + (j - n_pairs)] =
+            eval_rows(ft_za, ft_c, fu_t0[fu0 + j - n_pairs], fu_t0[fu0 + j - n_pairs + 1], ta);
+    }
+  }
+}
+
+// The V entries that each target reads.  Targets are taken in groups of 64
+// (group 8 j + w belongs to wave w of the panel workgroup); one wave per
+// group.  Pass 0 writes, per tile of source columns, the most entries any
+// lane of the group has; pass 1 places the entries of lane l at
+// pull[(off + i) * 64 + l], i in the order of the lane's moves.
+constexpr uint32_t kPullWaves = kPanelLanes / 64;
+__global__ __launch_bounds__(64) void k_pull(uint32_t pass, uint32_t db, uint32_t n_orb, uint32_t n_beta,
+                                             uint32_t n_tiles, const uint32_t* str_b, const uint32_t* zpair,
+                                             uint8_t* cnt, const uint32_t* off, uint16_t* pull) {
+  __shared__ uint8_t s_n[kPanelCols / kPanelTile][64];
+  const uint32_t g = blockIdx.x, w = g % kPullWaves, jg = g / kPullWaves, lane = threadIdx.x;
+  const uint32_t t = g * 64u + lane;
+  for (uint32_t k = 0; k < n_tiles; ++k) s_n[k][lane] = 0;
+  if (t < db) {
+    const uint32_t full = (n_orb == 32) ? 0xffffffffu : ((1u << n_orb) - 1u);
+    const uint32_t tb = str_b[t];
+    for (uint32_t occ = tb; occ; occ &= occ - 1) {
+      const uint32_t p = __ffs(occ) - 1;
+      for (uint32_t emp = ~tb & full; emp; emp &= emp - 1) {
+        const uint32_t q = __ffs(emp) - 1;
+        const uint32_t a = p < q ? p : q, b = p < q ? q : p, pair = b * (b - 1) / 2 + a;
+        const uint32_t src = colex_rank(tb ^ (1u << p) ^ (1u << q)), tile = src / kPanelTile;
+        const uint32_t i = s_n[tile][lane]++;
+        if (pass)
+          pull[(static_cast<uint64_t>(off[(tile * kPullWaves + w) * 8u + jg]) + i) * 64u + lane] =
+              static_cast<uint16_t>(pair * kPanelTile + src % kPanelTile + ((__popc(zpair[pair] & tb) & 1u) << 15));
+      }
+    }
+  }
+  if (pass) return;
+  for (uint32_t k = 0; k < n_tiles; ++k) {
+    uint32_t m = s_n[k][lane];
+    for (int d = 32; d > 0; d >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(m, d, 64)));
+    if (lane == 0) cnt[(k * kPullWaves + w) * 8u + jg] = static_cast<uint8_t>(m);
+  }
+}
+
+// First slot of every (tile, wave, group), in that order, and the records of
+// FactorPlan::pull_cnt; total[0] = all slots, total[1] = the most of one tile.
+// One workgroup of one wave (at most 64 tiles).
+static_assert(kPanelCols / kPanelTile <= 64, "one lane per tile");
+__global__ __launch_bounds__(64) void k_pull_offsets(uint32_t n_tiles, const uint8_t* cnt, uint32_t* off, uint4* rec,
+                                                     uint32_t* total) {
+  const uint32_t tile = threadIdx.x;
+  const uint8_t* c = cnt + tile * kPullWaves * 8u;
+  uint32_t sum = 0;
+  if (tile < n_tiles)
+    for (uint32_t i = 0; i < kPullWaves * 8u; ++i) sum += c[i];
+  uint32_t incl = sum, most = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t v = __shfl_up(incl, d, 64);
+    if (tile >= static_cast<uint32_t>(d)) incl += v;
+    most = max(most, static_cast<uint32_t>(__shfl_xor(most, d, 64)));
+  }
+  if (tile == 63) {
+    total[0] = incl;
+    total[1] = most;
+  }
+  if (tile >= n_tiles) return;
+  uint32_t at = 0;
+  for (uint32_t w = 0; w < kPullWaves; ++w) {
+    uint32_t lo = 0, hi = 0;
+    const uint32_t first = at;
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint32_t n = c[w * 8u + j];
+      off[(tile * kPullWaves + w) * 8u + j] = incl - sum + at;
+      if (j < 4)
+        lo |= n << (8 * j);
+      else
+        hi |= n << (8 * (j - 4));
+      at += n;
+    }
+    rec[tile * kPullWaves + w] = make_uint4(lo, hi, first, incl - sum);
+  }
+}
+
+__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
+  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < n;
+       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
+    p[i] = v;
+}
+
 // ---------------------------------------------------------------- host side
 
 // Pinned host staging for the build's small host<->device copies, one buffer
@@ -283,17 +422,25 @@ class Staging {
   Staging(const Staging&) = delete;
   Staging& operator=(const Staging&) = delete;
 
-  // handle-owned buffer (hipMalloc), filled from h
-  template <class T>
-  void upload(DevBuf<T>& d, const std::vector<T>& h) {
-    d.alloc(h.size());
-    put(d.get(), h);
-  }
-  // temporary of the build, from the call's scratch arena
-  template <class T>
-  void upload_temp(DevBuf<T>& d, const std::vector<T>& h) {
-    d = DevBuf<T>(h.size(), s_);
-    put(d.get(), h);
+  // memory for a slab (the handle's own, or the call's scratch arena) and its
+  // uploaded parts in one copy
+  void commit(Slab& b, DevBuf<char>& mem, bool temp) {
+    const size_t n = b.bytes(), up = b.upload_bytes();
+    if (temp)
+      mem = DevBuf<char>(n, s_);
+    else
+      mem.alloc(n);
+    b.place(mem.get());
+    if (up == 0) return;
+    if (void* p = take(up)) {
+      b.fill_host(static_cast<char*>(p));
+      PBS_HIP(hipMemcpyAsync(mem.get(), p, up, hipMemcpyHostToDevice, s_));
+    } else {
+      std::vector<char> image(up);
+      b.fill_host(image.data());
+      PBS_HIP(hipMemcpyAsync(mem.get(), image.data(), up, hipMemcpyHostToDevice, s_));
+      PBS_HIP(hipStreamSynchronize(s_));  // the image ends here
+    }
   }
   // n values of d into out, complete after wait()
   template <class T>
@@ -340,24 +487,68 @@ class Staging {
     if (!pool_->base || top_ > pool_->cap) return nullptr;
     return static_cast<char*>(pool_->base) + at;
   }
-  template <class T>
-  void put(T* dst, const std::vector<T>& h) {
-    if (h.empty()) return;
-    const size_t bytes = h.size() * sizeof(T);
-    if (void* p = take(bytes)) {
-      std::memcpy(p, h.data(), bytes);
-      PBS_HIP(hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, s_));
-    } else {
-      PBS_HIP(hipMemcpyAsync(dst, h.data(), bytes, hipMemcpyHostToDevice, s_));
-      PBS_HIP(hipStreamSynchronize(s_));  // h may change once we return
-    }
-  }
-
   hipStream_t s_;
   Pool* pool_ = nullptr;
   size_t top_ = 0, wanted_ = 0;
   std::vector<Pending> pending_;
 };
+
+// The beta-only lists of the X_alpha = 0 class (one per pair group, then one
+// per quad group) and, per orbital pair, the alpha list of what is left of
+// its pair groups; false when the operator or the sector is not one that the
+// panel kernel evaluates (see FactorPlan::panel).
+struct PanelLists {
+  std::vector<uint32_t> p_lo{0}, q_lo{0}, zb, al_lo{0}, al_za;
+  std::vector<double> c, al_c;
+};
+bool panel_lists(const FactorPlan& F, const pbs_grouped& h, const pbs_space& sp, const HostTables& T,
+                 const std::vector<ClassMeta>& meta, const std::vector<uint4>& cls_f,
+                 const std::vector<uint32_t>& zpair, const std::vector<uint32_t>& icls, PanelLists* L) {
+  if (F.c0 == 0xffffffffu || F.ns_sizes[2] != 0 || !h.pair_sign) return false;
+  for (uint32_t c : icls)
+    if (__builtin_popcount(meta[c].xa) != 2) return false;  // then a row has N_alpha (n_orb - N_alpha) at most
+  const ClassMeta& m = meta[F.c0];
+  if (m.q1 != m.g1 || (m.zg >= 0 && cls_f[F.c0].y == 0)) return false;
+  const uint32_t gz_end = m.zg >= 0 ? m.g0 + 1 : m.g0;
+  std::vector<std::vector<std::pair<uint32_t, double>>> al(h.n_pairs);
+  for (uint32_t g = gz_end; g < m.q1; ++g) {
+    const bool quad = g >= m.p1;
+    uint32_t pair = 0;
+    if (!quad) {
+      const uint32_t x = T.pg_xb[g];
+      const uint32_t lo = static_cast<uint32_t>(__builtin_ctz(x)), hi = 31u - static_cast<uint32_t>(__builtin_clz(x));
+      pair = hi * (hi - 1) / 2 + lo;
+    }
+    if (g == m.p1) L->q_lo[0] = static_cast<uint32_t>(L->zb.size());
+    for (uint32_t u = T.pg_u0[g]; u < T.pg_u0[g + 1]; ++u) {
+      double b = 0.0;
+      bool any = false;
+      for (uint32_t t = T.u_t0[u]; t < T.u_t0[u + 1]; ++t) {
+        if (T.pt_za[t] == 0u) {
+          b += T.pt_c[t];
+          any = true;
+        } else if (quad || T.u_zb[u] != zpair[pair]) {
+          return false;  // an alpha-dependent term without the pair's beta parity
+        } else {
+          al[pair].emplace_back(T.pt_za[t], T.pt_c[t]);
+        }
+      }
+      if (any) {
+        L->zb.push_back(T.u_zb[u]);
+        L->c.push_back(b);
+      }
+    }
+    (quad ? L->q_lo : L->p_lo).push_back(static_cast<uint32_t>(L->zb.size()));
+  }
+  for (const auto& l : al) {
+    for (const auto& t : l) {
+      L->al_za.push_back(t.first);
+      L->al_c.push_back(t.second);
+    }
+    L->al_lo.push_back(static_cast<uint32_t>(L->al_za.size()));
+  }
+  return true;
+}
 
 void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   auto plan = std::make_unique<FactorPlan>();
@@ -370,7 +561,8 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   HostTables T;
   std::vector<double> pt_c2;
   std::vector<ClassMeta> meta;
-  std::vector<uint32_t> ns;
+  std::vector<uint32_t> ns, zpair;
+  st.fetch(zpair, h.zpair, h.n_pairs + 1);
   st.fetch(T.pg_u0, h.pg_u0, h.n_pgroup + 1);
   st.fetch(T.u_zb, h.u_zb, h.n_unique);
   st.fetch(T.u_t0, h.u_t0, h.n_unique + 1);
@@ -506,31 +698,143 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   F.t_quad = most_terms(F.c0_fq, F.c0_fu1);
   F.t_zero = most_terms(F.c0_fu1, F.n_fu);
   F.n_ft = static_cast<uint32_t>(ft_za.size());
-  st.upload(F.fu_t0, fu_t0);
-  st.upload(F.ft_za, ft_za);
-  st.upload(F.ft_c, ft_c);
-  st.upload(F.cls_f, cls_f);
-  DevBuf<uint32_t> d_qlo, d_qzb;
-  DevBuf<double> d_qc;
-  st.upload_temp(d_qlo, q_lo);
-  st.upload_temp(d_qzb, q_zb);
-  st.upload_temp(d_qc, q_c);
 
+  // the class lists: simple classes (when every unique of every one of them
+  // has beta Z-mask 0), image classes, and what is left without them
+  const uint64_t da = sp.dim_alpha;
+  std::vector<uint32_t> simple, icls, flag(h.n_class, 0u);
+  bool plain = true;
+  for (uint32_t c = 0; c < h.n_class && plain; ++c) {
+    if (!(meta[c].flags & kClassSimple)) continue;
+    simple.push_back(c);
+    for (uint32_t u = meta[c].ua; u < meta[c].u_end; ++u) plain = plain && T.u_zb[u] == 0u;
+  }
+  F.alist = plain && !simple.empty();
+  if (F.alist) F.n_alpha = sp.n_alpha;
+  if (F.alist && h.pair_sign) {
+    for (uint32_t c : ns) {
+      const ClassMeta& m = meta[c];
+      if (c == F.c0 || m.pm < 0 || !(m.flags & kClassPairsSingle) || m.p1 != m.g1) continue;
+      if (m.zg >= 0 && (cls_f[c].y == 0 || cls_f[c].y > 2)) continue;
+      icls.push_back(c);
+      flag[c] = 1u;
+    }
+  }
+  F.plist = !icls.empty();
+  std::vector<uint32_t> rest[3];
+  F.ns_sizes.assign(3, 0u);
+  for (uint32_t c : ns) {
+    F.ns_uniques += meta[c].u_end - meta[c].ua;
+    F.ns_groups += meta[c].g1 - meta[c].g0;
+    for (int k = 0; k < 3; ++k)
+      if (!((k != 1 && c == F.c0) || (k != 0 && flag[c]))) rest[k].push_back(c);
+  }
+  for (int k = 0; k < 3; ++k) F.ns_sizes[k] = static_cast<uint32_t>(rest[k].size());
+  PanelLists L;
+  F.panel_variant = panel_variant_for(sp.dim_alpha, sp.dim_beta, h.n_pairs, sp.n_alpha * (sp.n_orb - sp.n_alpha) + 1u);
+  bool panel = F.plist && F.panel_variant >= 0 && panel_lists(F, h, sp, T, meta, cls_f, zpair, icls, &L);
+
+  // tables whose sizes are known, and the temporaries of this call
+  const bool moves = F.c0 != 0xffffffffu;
+  Slab own, tmp;
+  own.upload(F.fu_t0, fu_t0);
+  own.upload(F.ft_za, ft_za);
+  own.upload(F.ft_c, ft_c);
+  own.upload(F.cls_f, cls_f);
+  for (int k = 0; k < 3; ++k) own.upload(F.ns_rest[k], rest[k]);
+  if (F.plist) own.upload(F.pimg_flag, flag);
+  own.add(F.fz, static_cast<uint64_t>(n_zrows) * db);
+  DevBuf<uint32_t> d_qlo, d_qzb, d_simple, d_icls, cnt_a, cnt_p, ent_row;
+  DevBuf<double> d_qc;
+  DevBuf<int32_t> d_pk, d_qk;
+  tmp.upload(d_qlo, q_lo);
+  tmp.upload(d_qzb, q_zb);
+  tmp.upload(d_qc, q_c);
+  if (moves) {
+    tmp.upload(d_pk, pk);
+    tmp.upload(d_qk, qk);
+    own.add(F.em, static_cast<uint64_t>(n_moves) * db);
+    own.add(F.fp, static_cast<uint64_t>(n_moves) * F.r2 * db);
+    own.add(F.eq, n_qmoves * db);
+    own.add(F.fq, n_qmoves * F.r3 * db);
+  }
+  if (F.alist) {
+    tmp.upload(d_simple, simple);
+    tmp.add(cnt_a, da);
+    own.add(F.alist_off, da + 1);
+  }
+  if (F.plist) {
+    tmp.upload(d_icls, icls);
+    tmp.add(cnt_p, da);
+    own.add(F.plist_off, da + 1);
+    F.n_img = h.n_pairs + 3;
+  }
+  DevBuf<uint32_t> d_plo, d_ql2, d_zb, d_allo, d_alza, pull_off, pull_total;
+  DevBuf<double> d_c, d_alc;
+  DevBuf<uint8_t> pull_n;
+  uint32_t n_rec = 0;
+  const uint32_t pull_groups = static_cast<uint32_t>((db + 63) / 64);
+  if (panel) {
+    F.n_bb = F.n_moves + F.n_qmoves;
+    F.n_tiles = static_cast<uint32_t>((db + kPanelTile - 1) / kPanelTile);
+    const ClassMeta& m = meta[F.c0];
+    F.diag_rank = m.zg >= 0 ? cls_f[F.c0].y : 0u;
+    F.diag_off = cls_f[F.c0].z | (static_cast<uint64_t>(cls_f[F.c0].w) << 32);
+    n_rec = F.n_tiles * kPullWaves;
+    tmp.upload(d_plo, L.p_lo);
+    tmp.upload(d_ql2, L.q_lo);
+    tmp.upload(d_zb, L.zb);
+    tmp.upload(d_c, L.c);
+    tmp.upload(d_allo, L.al_lo);
+    tmp.upload(d_alza, L.al_za);
+    tmp.upload(d_alc, L.al_c);
+    tmp.add(pull_n, 8ull * n_rec);
+    tmp.add(pull_off, 8ull * n_rec);
+    tmp.add(pull_total, 2);
+    own.add(F.bb_src, (F.n_bb + 1ull) / 2ull * db);
+    own.add(F.bb_c, F.n_bb * db);
+    own.add(F.c0img, da * h.n_pairs);
+    own.add(F.diag_a, da * F.diag_rank);
+    own.add(F.pull_cnt, n_rec);
+  }
+  DevBuf<char> tmp_mem;
+  st.commit(own, F.mem[0], false);
+  st.commit(tmp, tmp_mem, true);
+
+  // counts first: they come back while the other tables are built
+  const unsigned row_grid = static_cast<unsigned>(std::min<uint64_t>(da, 65536));
+  std::vector<uint32_t> ca, cp, slots;
+  if (F.alist) {
+    hipLaunchKernelGGL(k_alpha_list, dim3(row_grid), dim3(256), 0, s, 0u, da, sp.n_alpha, sp.str_alpha.get(),
+                       d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
+                       h.pt_za.get(), h.pt_c.get(), nullptr, cnt_a.get(), nullptr, nullptr);
+    st.fetch(ca, cnt_a, da);
+    exclusive_scan_u32(cnt_a.get(), F.alist_off.get(), da, F.alist_off.get() + da, s);
+  }
+  if (F.plist) {
+    hipLaunchKernelGGL(k_pair_list, dim3(row_grid), dim3(256), 0, s, 0u, da, sp.n_alpha, sp.str_alpha.get(),
+                       d_icls.get(), static_cast<uint32_t>(icls.size()), h.cls_meta.get(), nullptr, cnt_p.get(),
+                       nullptr, nullptr, nullptr);
+    st.fetch(cp, cnt_p, da);
+    exclusive_scan_u32(cnt_p.get(), F.plist_off.get(), da, F.plist_off.get() + da, s);
+  }
+  if (panel) {
+    // (every slot count is below 256, so a fill of 32-bit zeros clears four)
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(2ull * n_rec, 256, 4096)), dim3(256), 0, s,
+                       reinterpret_cast<uint32_t*>(pull_n.get()), 2ull * n_rec, 0u);
+    hipLaunchKernelGGL(k_pull, dim3(pull_groups), dim3(64), 0, s, 0u, static_cast<uint32_t>(db), sp.n_orb, sp.n_beta,
+                       F.n_tiles, sp.str_beta.get(), h.zpair.get(), pull_n.get(), nullptr, nullptr);
+    hipLaunchKernelGGL(k_pull_offsets, dim3(1), dim3(64), 0, s, F.n_tiles, pull_n.get(), pull_off.get(),
+                       F.pull_cnt.get(), pull_total.get());
+    st.fetch(slots, pull_total, 2);
+  }
+  PBS_HIP(hipGetLastError());
   if (n_zrows) {
-    F.fz.alloc(static_cast<uint64_t>(n_zrows) * db);
     const uint64_t n = static_cast<uint64_t>(n_zrows) * db;
     hipLaunchKernelGGL(k_fact_rows, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n_zrows, db, sp.str_beta.get(),
                        d_qlo.get() + rows_z, d_qzb.get(), d_qc.get(), F.fz.get());
-    PBS_HIP(hipGetLastError());
   }
-  if (F.c0 != 0xffffffffu) {
-    DevBuf<int32_t> d_pk, d_qk;
-    st.upload_temp(d_pk, pk);
-    st.upload_temp(d_qk, qk);
-    F.em.alloc(static_cast<uint64_t>(n_moves) * db);
-    F.fp.alloc(static_cast<uint64_t>(n_moves) * F.r2 * db);
-    F.eq.alloc(n_qmoves * db);
-    F.fq.alloc(n_qmoves * F.r3 * db);
+  if (moves) {
     const uint64_t nm = static_cast<uint64_t>(n_moves) * db, nq = n_qmoves * db;
     hipLaunchKernelGGL(k_fact_moves, dim3(grid_for(nm, 256, 65536)), dim3(256), 0, s, db, sp.n_orb, sp.n_beta, F.r2,
                        sp.str_beta.get(), d_pk.get(), d_qlo.get() + rows_p, d_qzb.get(), d_qc.get(), F.em.get(),
@@ -539,111 +843,60 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
     hipLaunchKernelGGL(k_fact_quads, dim3(grid_for(nq, 256, 65536)), dim3(256), 0, s, db, sp.n_orb, sp.n_beta,
                        F.r3, slot0, sp.str_beta.get(), d_qk.get(), d_qlo.get() + rows_q, d_qzb.get(), d_qc.get(),
                        F.eq.get(), F.fq.get());
-    PBS_HIP(hipGetLastError());
   }
-  // alpha lists of the simple classes, when every unique of every simple
-  // class has beta Z-mask 0
-  {
-    std::vector<uint32_t> simple;
-    bool plain = true;
-    for (uint32_t c = 0; c < h.n_class && plain; ++c) {
-      if (!(meta[c].flags & kClassSimple)) continue;
-      simple.push_back(c);
-      for (uint32_t u = meta[c].ua; u < meta[c].u_end; ++u) plain = plain && T.u_zb[u] == 0u;
-    }
-    const uint64_t da = sp.dim_alpha;
-    if (plain && !simple.empty() && sp.n_orb <= 32) {
-      DevBuf<uint32_t> d_simple, cnt(da, s);
-      st.upload_temp(d_simple, simple);
-      const unsigned grid = static_cast<unsigned>(std::min<uint64_t>(da, 65536));
-      hipLaunchKernelGGL(k_alpha_list, dim3(grid), dim3(256), 0, s, 0u, da, sp.n_alpha, sp.str_alpha.get(),
-                         d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
-                         h.pt_za.get(), h.pt_c.get(), nullptr, cnt.get(), nullptr, nullptr);
-      PBS_HIP(hipGetLastError());
-      std::vector<uint32_t> c, off(da + 1, 0u);
-      st.fetch(c, cnt, da);
-      st.wait();
-      for (uint64_t i = 0; i < da; ++i) {
-        off[i + 1] = off[i] + c[i];
-        F.alist_max = std::max(F.alist_max, c[i]);
-      }
-      st.upload(F.alist_off, off);
-      F.alist_src.alloc(off[da]);
-      F.alist_c.alloc(off[da]);
-      if (off[da]) {
-        hipLaunchKernelGGL(k_alpha_list, dim3(grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),
-                           d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
-                           h.pt_za.get(), h.pt_c.get(), F.alist_off.get(), nullptr, F.alist_src.get(),
-                           F.alist_c.get());
-        PBS_HIP(hipGetLastError());
-      }
-      F.alist = true;
-      F.n_alpha = sp.n_alpha;
-    }
+  if (panel) {
+    hipLaunchKernelGGL(k_panel_moves, dim3(grid_for(F.n_bb * db, 256, 65536)), dim3(256), 0, s, db, sp.n_orb,
+                       sp.n_beta, F.n_moves, F.n_bb, sp.str_beta.get(), d_pk.get(), d_qk.get(), d_plo.get(),
+                       d_ql2.get(), d_zb.get(), d_c.get(), reinterpret_cast<uint16_t*>(F.bb_src.get()), F.bb_c.get());
+    hipLaunchKernelGGL(k_panel_rows, dim3(row_grid), dim3(128), 0, s, da, h.n_pairs, F.diag_rank, cls_f[F.c0].x,
+                       sp.str_alpha.get(), d_allo.get(), d_alza.get(), d_alc.get(), F.fu_t0.get(), F.ft_za.get(),
+                       F.ft_c.get(), F.c0img.get(), F.diag_a.get());
   }
-  // image classes and their per-row images
-  std::vector<uint32_t> flag(h.n_class, 0u);
-  if (F.alist && h.pair_sign && F.n_alpha == sp.n_alpha) {
-    std::vector<uint32_t> icls;
-    const std::vector<uint4>& cf = cls_f;  // as uploaded to F.cls_f
-    for (uint32_t c : ns) {
-      const ClassMeta& m = meta[c];
-      if (c == F.c0 || m.pm < 0 || !(m.flags & kClassPairsSingle) || m.p1 != m.g1) continue;
-      if (m.zg >= 0 && (cf[c].y == 0 || cf[c].y > 2)) continue;
-      icls.push_back(c);
-      flag[c] = 1u;
-    }
-    const uint64_t da = sp.dim_alpha;
-    if (!icls.empty()) {
-      DevBuf<uint32_t> d_cls, cnt(da, s);
-      st.upload_temp(d_cls, icls);
-      const unsigned grid = static_cast<unsigned>(std::min<uint64_t>(da, 65536));
-      hipLaunchKernelGGL(k_pair_list, dim3(grid), dim3(256), 0, s, 0u, da, sp.n_alpha, sp.str_alpha.get(), d_cls.get(),
-                         static_cast<uint32_t>(icls.size()), h.cls_meta.get(), nullptr, cnt.get(), nullptr, nullptr,
-                         nullptr);
-      PBS_HIP(hipGetLastError());
-      std::vector<uint32_t> c, off(da + 1, 0u);
-      st.fetch(c, cnt, da);
-      st.wait();
-      for (uint64_t i = 0; i < da; ++i) off[i + 1] = off[i] + c[i];
-      const uint64_t n_ent = off[da];
-      st.upload(F.plist_off, off);
-      F.plist_src.alloc(n_ent);
-      F.plist_cls.alloc(n_ent);
-      DevBuf<uint32_t> ent_row(n_ent, s);
-      F.n_img = h.n_pairs + 3;
-      F.pimg.alloc(n_ent * F.n_img);
-      if (n_ent) {
-        hipLaunchKernelGGL(k_pair_list, dim3(grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),
-                           d_cls.get(), static_cast<uint32_t>(icls.size()), h.cls_meta.get(), F.plist_off.get(),
-                           nullptr, F.plist_src.get(), F.plist_cls.get(), ent_row.get());
-        PBS_REQUIRE(n_ent < (1ull << 31), PBS_ERR_RANGE, "more than 2^31 alpha-image entries");
-        hipLaunchKernelGGL(k_pair_images, dim3(static_cast<unsigned>(n_ent)), dim3(kImgBlock), 0, s, F.n_img,
-                           h.n_pairs, sp.str_alpha.get(), F.plist_cls.get(), ent_row.get(), h.cls_meta.get(),
-                           h.pmap.get(), h.pg_u0.get(), h.u_t0.get(), h.pt_za.get(), h.pt_c.get(), F.cls_f.get(),
-                           F.fu_t0.get(), F.ft_za.get(), F.ft_c.get(), F.pimg.get());
-        PBS_HIP(hipGetLastError());
-      }
-      st.upload(F.pimg_flag, flag);
-      F.plist = true;
-    }
+  PBS_HIP(hipGetLastError());
+  st.wait();
+
+  // the lists and images, whose sizes the counts give
+  uint64_t n_list = 0, n_ent = 0;
+  for (uint32_t v : ca) {
+    n_list += v;
+    F.alist_max = std::max(F.alist_max, v);
   }
-  {
-    // the image flags as uploaded to F.pimg_flag, none without images
-    if (!F.plist) flag.assign(h.n_class, 0u);
-    for (uint32_t c : ns) {
-      F.ns_uniques += meta[c].u_end - meta[c].ua;
-      F.ns_groups += meta[c].g1 - meta[c].g0;
-    }
-    F.ns_sizes.assign(3, 0u);
-    for (int k = 0; k < 3; ++k) {
-      std::vector<uint32_t> l;
-      for (uint32_t c : ns)
-        if (!((k != 1 && c == F.c0) || (k != 0 && flag[c]))) l.push_back(c);
-      F.ns_sizes[k] = static_cast<uint32_t>(l.size());
-      st.upload(F.ns_rest[k], l);
-    }
+  for (uint32_t v : cp) n_ent += v;
+  PBS_REQUIRE(n_ent < (1ull << 31), PBS_ERR_RANGE, "more than 2^31 alpha-image entries");
+  panel = panel && slots[1] <= kPanelPullSlots;
+  // absent entries read V's zero; a tile's copy may run past the last slot
+  const uint64_t pull_words = panel ? 32ull * (slots[0] + kPanelPullSlots) : 0u;
+  Slab lists;
+  lists.add(F.alist_src, n_list);
+  lists.add(F.alist_c, n_list);
+  lists.add(F.plist_src, n_ent);
+  lists.add(F.plist_cls, n_ent);
+  lists.add(F.pimg, n_ent * F.n_img);
+  lists.add(F.pull, pull_words / 4);
+  st.commit(lists, F.mem[1], false);
+  if (n_list)
+    hipLaunchKernelGGL(k_alpha_list, dim3(row_grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),
+                       d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
+                       h.pt_za.get(), h.pt_c.get(), F.alist_off.get(), nullptr, F.alist_src.get(), F.alist_c.get());
+  if (n_ent) {
+    ent_row = DevBuf<uint32_t>(n_ent, s);
+    hipLaunchKernelGGL(k_pair_list, dim3(row_grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),
+                       d_icls.get(), static_cast<uint32_t>(icls.size()), h.cls_meta.get(), F.plist_off.get(), nullptr,
+                       F.plist_src.get(), F.plist_cls.get(), ent_row.get());
+    hipLaunchKernelGGL(k_pair_images, dim3(static_cast<unsigned>(n_ent)), dim3(kImgBlock), 0, s, F.n_img, h.n_pairs,
+                       sp.str_alpha.get(), F.plist_cls.get(), ent_row.get(), h.cls_meta.get(), h.pmap.get(),
+                       h.pg_u0.get(), h.u_t0.get(), h.pt_za.get(), h.pt_c.get(), F.cls_f.get(), F.fu_t0.get(),
+                       F.ft_za.get(), F.ft_c.get(), F.pimg.get());
   }
+  if (panel) {
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(pull_words, 256, 4096)), dim3(256), 0, s,
+                       reinterpret_cast<uint32_t*>(F.pull.get()), pull_words, kPanelZero | (kPanelZero << 16));
+    hipLaunchKernelGGL(k_pull, dim3(pull_groups), dim3(64), 0, s, 1u, static_cast<uint32_t>(db), sp.n_orb, sp.n_beta,
+                       F.n_tiles, sp.str_beta.get(), h.zpair.get(), pull_n.get(), pull_off.get(),
+                       reinterpret_cast<uint16_t*>(F.pull.get()));
+    F.panel = true;
+  }
+  PBS_HIP(hipGetLastError());
   PBS_HIP(hipStreamSynchronize(s));
   h.fplan = std::move(plan);
 }

@@ -82,6 +82,7 @@ constexpr uint32_t kMaxQuads = 2048;        // largest C(h, 4) given a quad map 
 // em/fp for its single moves, eq/fq for its double moves).  Real
 // coefficients only.
 struct FactorPlan {
+  DevBuf<char> mem[2];  // every table below: sizes known up front, and those known after counting
   uint32_t n_orb = 0, n_beta = 0;  // the beta sector the tables are for
   uint64_t dim_beta = 0;
   uint32_t n_fu = 0, n_ft = 0;     // factor uniques and their terms
@@ -133,6 +134,23 @@ struct FactorPlan {
   // its tables exist), without the image classes, and without both
   std::vector<uint32_t> ns_sizes;  // [3]
   DevBuf<uint32_t> ns_rest[3];
+  // Tables of the panel kernel (panel.h), when every class of the operator
+  // is a simple class, an image class or the X_alpha = 0 class, whose pair
+  // groups split into a beta-only part and a part with the pair's parity
+  // zpair, and whose quad groups are beta-only.
+  bool panel = false;
+  int panel_variant = -1;    // of kPanelVariants
+  uint32_t n_bb = 0, n_tiles = 0, diag_rank = 0;
+  uint64_t diag_off = 0;
+  DevBuf<uint32_t> bb_src;   // [ceil(n_bb / 2)][dim_beta]: source columns of moves 2i | 2i + 1 << 16
+  DevBuf<double> bb_c;       // [n_bb][dim_beta]: beta-only coefficient of each move
+  DevBuf<double> c0img;      // [dim_alpha][n_pairs]: X_alpha = 0 pair groups, alpha-dependent part
+  DevBuf<double> diag_a;     // [dim_alpha][diag_rank]: folded factors of the diagonal group
+  // the V entries each target reads: per tile of source columns, wave and
+  // target group, slots of 64 two-byte entries; and per (tile, wave) the
+  // slots of its target groups (a byte each, x and y), the wave's first slot
+  // in the tile (z) and the tile's first slot (w)
+  DevBuf<uint4> pull, pull_cnt;
   // sizes for the rows kernel: longest alpha list, and the uniques and
   // groups of all non-simple classes
   uint32_t alist_max = 0, ns_uniques = 0, ns_groups = 0;

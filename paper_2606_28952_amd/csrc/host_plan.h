@@ -34,6 +34,62 @@ constexpr uint32_t kFCapMax = 4096;    // and the largest (offsets are packed in
 constexpr uint32_t kMaxR1 = 32;        // largest factored rank of an X_beta = 0 group
 constexpr uint32_t kFactZeroSlots = 4;  // zero factors at the start of the class-0 fold
 
+// Panel kernel (panel.h): lanes per workgroup, most beta columns (seven
+// target columns per lane), columns per V tile, most classes per row (13 K
+// steps of four, the X_alpha = 0 class among them) and orbital pairs (six
+// 16-row tiles), and the V tile's zero entry.
+constexpr uint32_t kPanelLanes = 512;
+constexpr uint32_t kPanelCols = 7 * kPanelLanes;
+constexpr uint32_t kPanelTile = 64;
+constexpr uint32_t kPanelClasses = 52;
+constexpr uint32_t kPanelPairs = 96;
+constexpr uint32_t kPanelZero = kPanelPairs * kPanelTile;
+constexpr uint32_t kPanelPullSlots = 128;  // gather entries of a V tile: slots of 64 lanes
+constexpr uint32_t kPanelVBytes = (kPanelZero + 1u) * 16u;
+// LDS: the V tile, the image matrix and the classes' records; before them the
+// staged rows, then the list coefficients and sources, in the same place
+constexpr uint32_t kPanelMixBytes = kPanelVBytes + kPanelPairs * kPanelClasses * 8u + kPanelClasses * 32u;
+constexpr uint32_t kPanelPullBytes = kPanelPullSlots * 128u;  // after the classes' records
+
+// The panel kernel's variants: beta columns (512 per target column of a
+// lane), orbital pairs (32 per 16-pair tile of a wave), classes per row (four
+// per K step, the X_alpha = 0 class included) and target rows per workgroup
+// that each one is built for.  Fixed counts keep the products free of
+// branches, so a row's loads stay in flight across them; the narrow ones
+// save the padding (at 11 orbitals 8 K steps instead of 13).  Two rows with
+// seven columns per lane: four need 112 registers for the sums alone and
+// spill (28 qubits, complex64: 14.9 ms against 11.6).
+struct PanelVariant {
+  uint32_t cols, pairs, classes, rows;
+};
+constexpr PanelVariant kPanelVariants[] = {{512, 64, 32, 4},   {512, 96, 52, 4},  {1024, 96, 40, 4}, {1024, 96, 52, 4},
+                                           {2048, 96, 44, 4}, {2048, 96, 52, 4}, {3584, 96, 52, 2}};
+constexpr int kPanelWide = 4;  // first variant for more than 1,024 columns
+
+// The first variant that holds the sector, or -1.  Sectors of at most 512
+// beta and more than 512 alpha strings are left to the sector kernel: a row
+// is then too short to fill a workgroup's lanes and matrix tiles, while its
+// image matrix loads in full (7 of 14 alpha and 3 beta orbitals, complex64:
+// 1.98 ms against 1.64; 462 strings each: 0.148 ms against 0.152).
+inline int panel_variant_for(uint64_t rows, uint64_t cols, uint32_t pairs, uint32_t classes) {
+  if (rows > kPanelCols || (cols <= kPanelLanes && rows > kPanelLanes)) return -1;
+  int v = 0;
+  for (const PanelVariant& p : kPanelVariants) {
+    if (cols <= p.cols && pairs <= p.pairs && classes <= p.classes) return v;
+    ++v;
+  }
+  return -1;
+}
+
+// Row blocks that split dim_alpha rows evenly into at most `rows` each:
+// as few as that allows, rounded up to whole rounds of one workgroup per
+// compute unit (one row each when there are fewer rows than units).
+inline uint32_t panel_blocks(uint32_t dim_alpha, uint32_t rows, uint32_t cus) {
+  if (dim_alpha <= cus) return dim_alpha;
+  const uint32_t least = (dim_alpha + rows - 1u) / rows;
+  return std::min(dim_alpha, (least + cus - 1u) / cus * cus);
+}
+
 inline uint32_t align16(uint32_t v) { return (v + 15u) & ~15u; }
 
 // What the layout depends on: the device's LDS per workgroup (less the

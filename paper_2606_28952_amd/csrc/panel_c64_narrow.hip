@@ -1,0 +1,16 @@
+// complex64 panel kernels for at most 1,024 beta columns (panel.h; the
+// variants are those of kPanelVariants in host_plan.h).
+#include "panel.h"
+
+namespace pbs {
+
+void* panel_kernel_c64_narrow(bool expval, bool batch, int variant) {
+  switch (variant) {
+    case 0: return panel_variant<float2, 1, 2, 8, 4>(expval, batch);
+    case 1: return panel_variant<float2, 1, 3, 13, 4>(expval, batch);
+    case 2: return panel_variant<float2, 2, 3, 10, 4>(expval, batch);
+    default: return panel_variant<float2, 2, 3, 13, 4>(expval, batch);
+  }
+}
+
+}  // namespace pbs

@@ -149,6 +149,60 @@ struct DevBuf {
   }
 };
 
+// Several buffers in one allocation: parts are listed first, then laid out
+// (uploaded ones together, so that one copy fills them) and placed at a base
+// address.  The buffers borrow their memory from whoever owns the base; they
+// must not move between listing and placing.
+class Slab {
+ public:
+  template <class T>
+  void add(DevBuf<T>& b, size_t n) {
+    list(b, n, nullptr);
+  }
+  // filled from h, which must live until the copy is staged
+  template <class T>
+  void upload(DevBuf<T>& b, const std::vector<T>& h) {
+    list(b, h.size(), h.data());
+  }
+  size_t bytes() {
+    size_t at = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+      for (Part& p : parts_)
+        if ((p.src == nullptr) == (pass == 1)) {
+          p.off = at;
+          at += (p.bytes + 255) & ~static_cast<size_t>(255);
+        }
+      if (pass == 0) upload_bytes_ = at;
+    }
+    return at;
+  }
+  size_t upload_bytes() const { return upload_bytes_; }  // after bytes()
+  void fill_host(char* image) const {
+    for (const Part& p : parts_)
+      if (p.src) std::memcpy(image + p.off, p.src, p.bytes);
+  }
+  void place(char* base) {
+    for (const Part& p : parts_)
+      if (p.bytes) *p.ptr = base + p.off;
+  }
+
+ private:
+  struct Part {
+    void** ptr;
+    const void* src;
+    size_t bytes, off;
+  };
+  template <class T>
+  void list(DevBuf<T>& b, size_t n, const void* src) {
+    b.release();
+    b.n = n;
+    b.borrowed = true;
+    parts_.push_back({reinterpret_cast<void**>(&b.ptr), n ? src : nullptr, n * sizeof(T), 0});
+  }
+  std::vector<Part> parts_;
+  size_t upload_bytes_ = 0;
+};
+
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline unsigned grid_for(uint64_t n, unsigned block, unsigned cap = 1u << 20) {

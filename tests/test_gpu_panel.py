@@ -1,0 +1,109 @@
+"""Panel kernel (matrix-core evaluation of factored two-body sectors) against
+the oracle where it is quick enough and against the unfactored evaluation of
+the sector kernel everywhere, at the edges of its tiles: beta columns around
+its 64-column tiles and its 512-column widths, class counts that do and do not
+fill a step of four, one to four target rows per workgroup.
+
+Both evaluations sum the same float64 products in another order, so the bars
+are those of every factored path: 1e-12 relative 2-norm in float64, 1e-6 for
+complex64 storage on the same FP32-rounded input."""
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import apply as oapply
+from oracle import jw as ojw
+from oracle import space as ospace
+from tests.conftest import rel_err
+
+pytestmark = pytest.mark.gpu
+
+# (n_orb, N_alpha, N_beta): 5 classes per row = one step and one more; 6 and
+# 10 columns; 56 and 70; 210; rows and columns on both sides of 256 and 512;
+# 715 (ten steps), 924, 1,001, 1,287 and 1,716 columns; 3,432 columns
+CASES = [(4, 2, 2), (5, 1, 2), (5, 4, 3), (8, 3, 5), (8, 4, 4), (10, 3, 6), (10, 5, 4), (11, 4, 6), (11, 6, 5),
+         (12, 2, 6), (12, 3, 5), (13, 2, 9), (13, 3, 8), (13, 2, 7), (14, 2, 4), (14, 2, 7)]
+
+
+@pytest.mark.parametrize("n_o,na,nb", CASES)
+def test_panel_matches_oracle_and_plain(dev, n_o, na, nb):
+    from paper_2606_28952_amd import api
+
+    seed = 900 + 17 * n_o + 5 * na + nb
+    h1, h2 = synth.molecular_spin_integrals(n_o, seed)
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(n_o, na, nb)
+    psi_np = synth.random_state(sp.dim, seed + 1)
+    psi = torch.from_numpy(psi_np).to(dev)
+    plain = api.apply_pauli_sum(G, sp, psi)
+    psi32 = psi.to(torch.complex64)
+    plain32 = api.apply_pauli_sum(G, sp, psi32.to(torch.complex128))
+    G.factor(sp)
+    out = torch.empty_like(psi)
+    e = api.expval(G, sp, psi, out=out).cpu().numpy()
+    got = out.cpu().numpy()
+    assert rel_err(got, plain.cpu().numpy()) < 1e-12
+    if sp.dim <= 60000:
+        ref = oapply.apply_scatter(ojw.jw_sum(h1, h2), ospace.SectorSpace(n_o, na, nb), psi_np)
+        assert rel_err(got, ref) < 1e-12
+    e_ref = np.vdot(psi_np, plain.cpu().numpy())
+    assert abs(e[0] - e_ref.real) < 1e-12 * max(1.0, abs(e_ref)) and abs(e[2] - 1.0) < 1e-13
+    # the product alone gives the same bits, twice; the energy alone too
+    for _ in range(2):
+        assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi)), torch.view_as_real(out))
+    assert np.array_equal(api.expval(G, sp, psi).cpu().numpy(), e)
+    # a share of the rows that starts and ends inside row blocks
+    a, b = sp.shape()[3] // 3, sp.shape()[3] - sp.shape()[3] // 5
+    part = api.apply_pauli_sum_rows(G, sp, psi, a, b)
+    db = sp.shape()[4]
+    assert torch.equal(torch.view_as_real(part), torch.view_as_real(out[a * db:b * db]))
+    out32 = torch.empty_like(psi32)
+    e32 = api.expval(G, sp, psi32, out=out32).cpu().numpy()
+    assert rel_err(out32.cpu().numpy().astype(np.complex128), plain32.cpu().numpy()) < 1e-6
+    p64 = psi32.cpu().numpy().astype(np.complex128)
+    e32_ref = np.vdot(p64, plain32.cpu().numpy())
+    assert abs(e32[0] - e32_ref.real) < 1e-12 * max(1.0, abs(e32_ref))
+    # switched off, the evaluation is the unfactored one, bit for bit
+    G.set_factored(0)
+    assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi)), torch.view_as_real(plain))
+
+
+def test_panel_reads_an_unaligned_state(dev):
+    """A complex64 state that starts 8 bytes past a 16-byte boundary."""
+    from paper_2606_28952_amd import api
+
+    h1, h2 = synth.molecular_spin_integrals(8, 77)
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(8, 4, 3)
+    G.factor(sp)
+    psi = torch.from_numpy(synth.random_state(sp.dim, 78)).to(dev).to(torch.complex64)
+    base = torch.zeros(sp.dim + 1, dtype=torch.complex64, device=dev)
+    base[1:] = psi
+    assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, base[1:])),
+                       torch.view_as_real(api.apply_pauli_sum(G, sp, psi)))
+
+
+def test_panel_needs_its_operator_structure(dev):
+    """Operators whose X_alpha = 0 pair groups do not split (a term with an
+    alpha Z-mask and another beta parity), or that have other classes, keep
+    the sector kernel: same results as unfactored."""
+    from paper_2606_28952_amd import api
+
+    n_o = 5
+    h1, h2 = synth.molecular_spin_integrals(n_o, 79)
+    H = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev))
+    x, z, c = H.read()
+    # X_0 X_1 on the beta half with a Z on an alpha and on another beta orbital (and its
+    # Y Y partner, so that the pair conserves the number)
+    bx = (0b11 << n_o)
+    extra_z = 0b100 | (0b1000 << n_o)
+    xs = np.concatenate([x.reshape(-1), np.array([bx, bx], np.uint64)])
+    zs = np.concatenate([z.reshape(-1), np.array([extra_z, extra_z | bx], np.uint64)])
+    G = api.PauliSum.create(2 * n_o, xs, zs, np.concatenate([c, [0.3, 0.3]])).canonicalize().group()
+    sp = api.Space.sector(n_o, 2, 3)
+    psi = torch.from_numpy(synth.random_state(sp.dim, 80)).to(dev)
+    plain = api.apply_pauli_sum(G, sp, psi).cpu().numpy()
+    G.factor(sp)
+    assert rel_err(api.apply_pauli_sum(G, sp, psi).cpu().numpy(), plain) < 1e-12
