@@ -3,6 +3,7 @@
 // full-space kernel, launch planning of the sector kernels (whose device code
 // lives in sector.h), and the C ABI entry points, single and batched.
 #include <iterator>
+#include <memory>
 #include <mutex>
 #include <string>
 
@@ -336,16 +337,22 @@ struct PanelShape {
 };
 
 // Arguments and shape of the panel kernel when the operator's factor tables
-// allow it for this sector and every factored part is switched on.
-bool plan_panel(const pbs_grouped& h, const pbs_space& sp, PanelArgs* out, PanelShape* shape) {
-  const FactorPlan* F = h.fplan.get();
-  if (!h.real_coef || F == nullptr || !F->panel || h.fact_on != (kFactZero | kFactMoves | kFactAlpha)) return false;
-  if (F->n_orb != sp.n_orb || F->n_alpha != sp.n_alpha || F->n_beta != sp.n_beta) return false;
+// allow it for this sector and every factored part is switched on.  The
+// alpha side (lists, images) and the beta side (move coefficients, F rows,
+// gather entries) may come from two plans of the same operator.
+bool plan_panel(const pbs_grouped& h, const pbs_space& sp, const FactorPlan* A, const FactorPlan* F, PanelArgs* out,
+                PanelShape* shape) {
+  if (!h.real_coef || A == nullptr || F == nullptr || !A->panel || !F->panel ||
+      h.fact_on != (kFactZero | kFactMoves | kFactAlpha))
+    return false;
+  if (F->n_orb != sp.n_orb || A->n_alpha != sp.n_alpha || F->n_beta != sp.n_beta) return false;
+  shape->variant =
+      panel_variant_for(sp.dim_alpha, sp.dim_beta, h.n_pairs, sp.n_alpha * (sp.n_orb - sp.n_alpha) + 1u);
+  if (shape->variant < 0) return false;
   PanelArgs a{};
   a.dim_alpha = static_cast<uint32_t>(sp.dim_alpha);
   a.dim_beta = static_cast<uint32_t>(sp.dim_beta);
-  shape->variant = F->panel_variant;
-  const PanelVariant& v = kPanelVariants[F->panel_variant];
+  const PanelVariant& v = kPanelVariants[shape->variant];
   a.n_blk = panel_blocks(a.dim_alpha, v.rows, device_cus());
   a.n_tiles = F->n_tiles;
   a.n_img = F->n_img;
@@ -353,15 +360,15 @@ bool plan_panel(const pbs_grouped& h, const pbs_space& sp, PanelArgs* out, Panel
   a.n_bb = F->n_bb;
   a.diag_rank = F->diag_rank;
   a.diag_off = F->diag_off;
-  a.alist_off = F->alist_off.get();
-  a.alist_src = F->alist_src.get();
-  a.alist_c = F->alist_c.get();
-  a.plist_off = F->plist_off.get();
-  a.plist_src = F->plist_src.get();
-  a.plist_cls = F->plist_cls.get();
-  a.pimg = F->pimg.get();
-  a.c0img = F->c0img.get();
-  a.diag_a = F->diag_a.get();
+  a.alist_off = A->alist_off.get();
+  a.alist_src = A->alist_src.get();
+  a.alist_c = A->alist_c.get();
+  a.plist_off = A->plist_off.get();
+  a.plist_src = A->plist_src.get();
+  a.plist_cls = A->plist_cls.get();
+  a.pimg = A->pimg.get();
+  a.c0img = A->c0img.get();
+  a.diag_a = A->diag_a.get();
   a.cls_f = F->cls_f.get();
   a.fz = F->fz.get();
   a.bb_src = F->bb_src.get();
@@ -403,7 +410,7 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     if (o) o = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(o) - row_begin * sp.dim_beta * sizeof(T));
     PanelArgs pa;
     PanelShape ps;
-    if (plan_panel(h, sp, &pa, &ps)) {
+    if (plan_panel(h, sp, h.fplan.get(), h.fplan.get(), &pa, &ps)) {
       pa.row_begin = static_cast<uint32_t>(row_begin);
       pa.row_end = static_cast<uint32_t>(row_end);
       // the blocks that hold rows row_begin and row_end - 1
@@ -604,6 +611,14 @@ struct pbs_batch {
   std::vector<const pbs_space*> sp;
   std::vector<const void*> psi;
   std::vector<void*> out;
+  // factor tables of the caller's (empty, or null for a job: the operator's own)
+  std::vector<const pbs::FactorPlan*> plan_a, plan_b;
+  const pbs::FactorPlan* alpha_plan(uint32_t i) const {
+    return plan_a.empty() || !plan_a[i] ? h[i]->fplan.get() : plan_a[i];
+  }
+  const pbs::FactorPlan* beta_plan(uint32_t i) const {
+    return plan_b.empty() || !plan_b[i] ? h[i]->fplan.get() : plan_b[i];
+  }
   pbs::DevBuf<pbs::BatchJob> jobs;
   pbs::DevBuf<pbs::PanelJob> pjobs;
   pbs::DevBuf<pbs::FinishJob> finish;
@@ -639,7 +654,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   std::vector<uint32_t> sector;
   std::vector<std::vector<uint32_t>> by_variant(std::size(kPanelVariants));
   for (uint32_t i = 0; i < n; ++i) {
-    if (allow_row && qenum && penum && factd && plan_panel(*B.h[i], *B.sp[i], &pj[i].args, &shape[i]))
+    if (allow_row && qenum && penum && factd && plan_panel(*B.h[i], *B.sp[i], B.alpha_plan(i), B.beta_plan(i), &pj[i].args, &shape[i]))
       by_variant[shape[i].variant].push_back(i);
     else
       sector.push_back(i);
@@ -801,6 +816,41 @@ void launch_batch(const pbs_batch& b, double* energies, hipStream_t s) {
 }
 
 }  // namespace
+
+pbs_batch* batch_create(uint32_t n, const pbs_grouped* const* h, const pbs_space* const* sp, pbs_dtype dt,
+                        const void* const* psi, void* const* out, const FactorPlan* const* plan_a,
+                        const FactorPlan* const* plan_b) {
+  PBS_REQUIRE(n >= 1 && h && sp && psi && out, PBS_ERR_ARG, "empty batch or null array");
+  const size_t esz = dt == PBS_C128 ? 16 : 8;
+  for (uint32_t i = 0; i < n; ++i) {
+    validate(h[i], sp[i], dt);
+    PBS_REQUIRE(sp[i]->sector, PBS_ERR_UNSUPPORTED, "batched apply runs on spin-sector spaces");
+    PBS_REQUIRE(psi[i] && out[i], PBS_ERR_ARG, "null state pointer in job " + std::to_string(i));
+    const uint64_t bytes = sp[i]->dim * esz;
+    const auto a = reinterpret_cast<uintptr_t>(psi[i]), b = reinterpret_cast<uintptr_t>(out[i]);
+    PBS_REQUIRE(a + bytes <= b || b + bytes <= a, PBS_ERR_ARG, "out overlaps psi in job " + std::to_string(i));
+  }
+  for (uint32_t i = 0; i < n; ++i) {  // outputs of different jobs must not overlap
+    const uint64_t bi = sp[i]->dim * esz;
+    for (uint32_t j = i + 1; j < n; ++j) {
+      const uint64_t bj = sp[j]->dim * esz;
+      const auto x = reinterpret_cast<uintptr_t>(out[i]), y = reinterpret_cast<uintptr_t>(out[j]);
+      PBS_REQUIRE(x + bi <= y || y + bj <= x, PBS_ERR_ARG, "outputs of jobs overlap");
+    }
+  }
+  auto B = std::make_unique<pbs_batch>();
+  B->n_jobs = n;
+  B->dt = dt;
+  B->h.assign(h, h + n);
+  B->sp.assign(sp, sp + n);
+  B->psi.assign(psi, psi + n);
+  B->out.assign(out, out + n);
+  if (plan_a) B->plan_a.assign(plan_a, plan_a + n);
+  if (plan_b) B->plan_b.assign(plan_b, plan_b + n);
+  fill_batch(*B, 0u);
+  return B.release();
+}
+
 }  // namespace pbs
 
 extern "C" {
@@ -810,38 +860,7 @@ pbs_status pbs_batch_create(uint32_t n, const pbs_grouped* const* h, const pbs_s
   return guarded([&] {
     PBS_REQUIRE(batch != nullptr, PBS_ERR_ARG, "null output handle");
     *batch = nullptr;
-    PBS_REQUIRE(n >= 1 && h && sp && psi && out, PBS_ERR_ARG, "empty batch or null array");
-    const size_t esz = dt == PBS_C128 ? 16 : 8;
-    for (uint32_t i = 0; i < n; ++i) {
-      validate(h[i], sp[i], dt);
-      PBS_REQUIRE(sp[i]->sector, PBS_ERR_UNSUPPORTED, "batched apply runs on spin-sector spaces");
-      PBS_REQUIRE(psi[i] && out[i], PBS_ERR_ARG, "null state pointer in job " + std::to_string(i));
-      const uint64_t bytes = sp[i]->dim * esz;
-      const auto a = reinterpret_cast<uintptr_t>(psi[i]), b = reinterpret_cast<uintptr_t>(out[i]);
-      PBS_REQUIRE(a + bytes <= b || b + bytes <= a, PBS_ERR_ARG, "out overlaps psi in job " + std::to_string(i));
-    }
-    for (uint32_t i = 0; i < n; ++i) {  // outputs of different jobs must not overlap
-      const uint64_t bi = sp[i]->dim * esz;
-      for (uint32_t j = i + 1; j < n; ++j) {
-        const uint64_t bj = sp[j]->dim * esz;
-        const auto x = reinterpret_cast<uintptr_t>(out[i]), y = reinterpret_cast<uintptr_t>(out[j]);
-        PBS_REQUIRE(x + bi <= y || y + bj <= x, PBS_ERR_ARG, "outputs of jobs overlap");
-      }
-    }
-    auto* B = new pbs_batch();
-    try {
-      B->n_jobs = n;
-      B->dt = dt;
-      B->h.assign(h, h + n);
-      B->sp.assign(sp, sp + n);
-      B->psi.assign(psi, psi + n);
-      B->out.assign(out, out + n);
-      fill_batch(*B, 0u);
-    } catch (...) {
-      delete B;
-      throw;
-    }
-    *batch = B;
+    *batch = batch_create(n, h, sp, dt, psi, out, nullptr, nullptr);
   });
 }
 

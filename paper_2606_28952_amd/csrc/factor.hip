@@ -550,7 +550,10 @@ bool panel_lists(const FactorPlan& F, const pbs_grouped& h, const pbs_space& sp,
   return true;
 }
 
-void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
+}  // namespace
+
+std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_space& sp, bool move_tables,
+                                             hipStream_t s) {
   auto plan = std::make_unique<FactorPlan>();
   FactorPlan& F = *plan;
   F.n_orb = sp.n_orb;
@@ -735,7 +738,9 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   bool panel = F.plist && F.panel_variant >= 0 && panel_lists(F, h, sp, T, meta, cls_f, zpair, icls, &L);
 
   // tables whose sizes are known, and the temporaries of this call
+  // (a plan built for the panel kernel alone leaves the sector kernel's move tables out)
   const bool moves = F.c0 != 0xffffffffu;
+  const bool tables = moves && move_tables;
   Slab own, tmp;
   own.upload(F.fu_t0, fu_t0);
   own.upload(F.ft_za, ft_za);
@@ -753,6 +758,8 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   if (moves) {
     tmp.upload(d_pk, pk);
     tmp.upload(d_qk, qk);
+  }
+  if (tables) {
     own.add(F.em, static_cast<uint64_t>(n_moves) * db);
     own.add(F.fp, static_cast<uint64_t>(n_moves) * F.r2 * db);
     own.add(F.eq, n_qmoves * db);
@@ -834,7 +841,7 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
     hipLaunchKernelGGL(k_fact_rows, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n_zrows, db, sp.str_beta.get(),
                        d_qlo.get() + rows_z, d_qzb.get(), d_qc.get(), F.fz.get());
   }
-  if (moves) {
+  if (tables) {
     const uint64_t nm = static_cast<uint64_t>(n_moves) * db, nq = n_qmoves * db;
     hipLaunchKernelGGL(k_fact_moves, dim3(grid_for(nm, 256, 65536)), dim3(256), 0, s, db, sp.n_orb, sp.n_beta, F.r2,
                        sp.str_beta.get(), d_pk.get(), d_qlo.get() + rows_p, d_qzb.get(), d_qc.get(), F.em.get(),
@@ -898,10 +905,9 @@ void build_plan(pbs_grouped& h, const pbs_space& sp, hipStream_t s) {
   }
   PBS_HIP(hipGetLastError());
   PBS_HIP(hipStreamSynchronize(s));
-  h.fplan = std::move(plan);
+  return plan;
 }
 
-}  // namespace
 }  // namespace pbs
 
 using namespace pbs;
@@ -916,7 +922,7 @@ pbs_status pbs_grouped_factor(pbs_grouped* h, const pbs_space* sp, void* stream)
     PBS_REQUIRE(h->real_coef, PBS_ERR_UNSUPPORTED, "factored evaluation needs real sector-form coefficients");
     h->fplan.reset();
     Scratch scratch(as_stream(stream));  // temporaries of this call
-    build_plan(*h, *sp, as_stream(stream));
+    h->fplan = make_factor_plan(*h, *sp, true, as_stream(stream));
   });
 }
 

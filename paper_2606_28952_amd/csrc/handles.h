@@ -217,6 +217,18 @@ struct pbs_space {
 };
 
 namespace pbs {
+// Factor tables of h for the sector's alpha and beta strings (factor.hip);
+// the sector kernel's move tables only when asked for.  Synchronizes; its
+// temporaries come from the thread's open Scratch scope.
+std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_space& sp, bool move_tables,
+                                             hipStream_t s);
+// pbs_batch_create (apply.hip) with factor tables of the caller's: job i uses
+// the alpha side of plan_a[i] and the beta side of plan_b[i] (null: the
+// operator's own tables, if any).  The plans outlive the batch.
+pbs_batch* batch_create(uint32_t n, const pbs_grouped* const* h, const pbs_space* const* sp, pbs_dtype dt,
+                        const void* const* psi, void* const* out, const FactorPlan* const* plan_a,
+                        const FactorPlan* const* plan_b);
+
 uint64_t host_binom(uint32_t n, uint32_t r);  // exact binomial coefficient (space.hip)
 
 inline size_t rank_tab_entries(uint32_t n_orb) {

@@ -510,6 +510,7 @@ struct pbs_vqe {
   uint64_t dim = 0, ref = 0;
   std::vector<Rot> rots;
   std::vector<pbs_space*> spaces;  // one per nonempty (N_alpha, N_beta) block, alpha-major order
+  std::vector<std::unique_ptr<FactorPlan>> plans;  // by string count: factor tables of sector (k, k), or null
   pbs_batch* batch = nullptr;
   uint32_t n_jobs = 0;
   DevBuf<uint32_t> rank_tab, binom_n;
@@ -715,8 +716,29 @@ pbs_status pbs_vqe_create(const pbs_grouped* h, uint32_t n_orb, uint32_t n_rot, 
       }
       PBS_REQUIRE(acc == dim, PBS_ERR_DEVICE, "sector blocks do not tile the full space");
       v->n_jobs = static_cast<uint32_t>(sps.size());
-      const pbs_status st = pbs_batch_create(v->n_jobs, hs.data(), sps.data(), dt, ins.data(), outs.data(), &v->batch);
-      PBS_REQUIRE(st == PBS_OK, st, std::string("batch: ") + pbs_last_error());
+      // factor tables for the panel kernel: the alpha side depends on a
+      // block's alpha string count alone and the beta side on its beta string
+      // count, so one plan per count serves all blocks
+      v->plans.resize(n_orb + 1);
+      std::vector<const FactorPlan*> pa(v->n_jobs, nullptr), pb(v->n_jobs, nullptr);
+      if (h->real_coef) {
+        Scratch scratch(s);
+        auto build = [&](uint32_t k) {  // false: the operator is not one for the panel kernel
+          auto plan = make_factor_plan(*h, *v->spaces[k * (n_orb + 1) + k], false, s);
+          if (!plan->panel) return false;
+          v->plans[k] = std::move(plan);
+          return true;
+        };
+        const uint32_t mid = n_orb / 2;
+        if (n_orb >= 4 && build(mid))
+          for (uint32_t k = 2; k + 2 <= n_orb; ++k)
+            if (k != mid) build(k);
+        for (uint32_t j = 0; j < v->n_jobs; ++j) {
+          pa[j] = v->plans[sps[j]->n_alpha].get();
+          pb[j] = v->plans[sps[j]->n_beta].get();
+        }
+      }
+      v->batch = batch_create(v->n_jobs, hs.data(), sps.data(), dt, ins.data(), outs.data(), pa.data(), pb.data());
       const pbs_space& sp0 = *v->spaces[0];
       v->rank_tab.alloc(sp0.rank_tab.n);
       PBS_HIP(hipMemcpyAsync(v->rank_tab.get(), sp0.rank_tab.get(), sp0.rank_tab.n * 4, hipMemcpyDeviceToDevice, s));
