@@ -320,6 +320,176 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_group(T* __restrict__ psi, T
   }
 }
 
+// ---------------------------------------------------------------- K = 4..6 rotations per pass
+// The same orbits, eight elements per lane and two register stages: a
+// workgroup holds 2,048 elements (2^K of 2,048 >> K consecutive orbits) and
+// exchanges them once through LDS, so the vectors are read and written once
+// per K rotations.  Stage H keeps the orbit bits K-3 .. K-1 in a lane's
+// registers (rotations K-3 .. K-1), stage L the bits 0 .. 2 (rotations
+// 0 .. K-4); the other K-3 bits and the orbit number are the lane.  Orbits
+// are consecutive, so the reads and writes stay contiguous (512 bytes at K =
+// 6) where the pivot bits lie above the orbit number's.
+//
+// Bound by memory: four vectors per adjoint pass.  At 24 qubits, complex128,
+// three rotations per pass take 228 us (4.7 TB/s, a copy's rate); see
+// energy_grad for the measured passes of six.
+constexpr uint32_t kTileElems = 2048;
+
+template <int K>
+struct TileGroup {
+  uint32_t x[K], z[K];
+  uint32_t turn[K];  // parity of z & x
+  uint32_t om[K];    // power of i of the string, 0..3
+  uint32_t piv[K];   // ascending
+  double c[K], s[K];
+};
+
+template <int K>
+__device__ inline uint32_t tile_base(uint32_t i, const TileGroup<K>& G) {
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const uint32_t low = (1u << G.piv[j]) - 1u;
+    i = ((i & ~low) << 1) | (i & low);
+  }
+  return i;
+}
+
+// Image of v under the string, up to the factor i^om (-1)^q of its target:
+// om & 1 exchanges the components, its sign and om & 2 join q.
+__device__ __forceinline__ Cx turned(const Cx& v, bool odd, uint32_t q) {
+  return odd ? Cx{signed_by(v.i, q + 1u), signed_by(v.r, q)} : Cx{signed_by(v.r, q), signed_by(v.i, q)};
+}
+
+// Rotation j on the lane's eight elements at t ^ rc[e], pairs differing in
+// register bit `bit`: v <- c v + i s (P v).  ADJOINT: the same on l, and
+// first ov += Im conj(l) (P v) over the pairs.
+template <bool ADJOINT, int K>
+__device__ __forceinline__ void tile_step(Cx (&v)[8], Cx (&l)[8], uint32_t t, const uint32_t (&rc)[8], int bit,
+                                          const TileGroup<K>& G, int j, double& ov) {
+  const uint32_t q0 = __popc(G.z[j] & t) + (G.om[j] >> 1);
+  const bool odd = G.om[j] & 1u;
+  const double c = G.c[j], s = G.s[j];
+  auto turn = [&](Cx& a, const Cx& p) { a = Cx{fma(c, a.r, -s * p.i), fma(c, a.i, s * p.r)}; };
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int f = e | (1 << bit);
+    if (e == f) continue;
+    const uint32_t qe = q0 + __popc(G.z[j] & rc[e]), qf = qe + G.turn[j];  // parities at the two elements
+    const Cx pe = turned(v[f], odd, qf), pf = turned(v[e], odd, qe);
+    if (ADJOINT) {
+      ov = fma(l[e].r, pe.i, fma(-l[e].i, pe.r, ov));
+      ov = fma(l[f].r, pf.i, fma(-l[f].i, pf.r, ov));
+      const Cx le = turned(l[f], odd, qf), lf = turned(l[e], odd, qe);
+      turn(l[e], le);
+      turn(l[f], lf);
+    }
+    turn(v[e], pe);
+    turn(v[f], pf);
+  }
+}
+
+// psi <- R_{K-1} ... R_0 psi (ADJOINT false), or K adjoint steps from the
+// last rotation to the first (G carries cos, sin of -theta): partial_j =
+// partial + 3 stride j gets Im <lam|P_j|psi> of every workgroup.
+template <class T, bool ADJOINT, int K>
+__global__ __launch_bounds__(kBlock) void k_tile_group(T* __restrict__ psi, T* __restrict__ lam, uint32_t tiles,
+                                                        TileGroup<K> G, double* __restrict__ partial,
+                                                        uint64_t stride) {
+  constexpr int L = K - 3;                   // lane bits of the orbit index
+  constexpr uint32_t B = kTileElems >> K;    // orbits per workgroup
+  static_assert(kBlock * 8 == kTileElems, "eight elements per lane");
+  extern __shared__ __align__(16) unsigned char tile_smem[];
+  double2* s_v = reinterpret_cast<double2*>(tile_smem);
+  double2* s_l = s_v + kTileElems;
+  const uint32_t b = threadIdx.x % B, el = threadIdx.x / B;
+  uint32_t xh = 0, xl = 0, rh[8], rl[8];
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    xh ^= ((el >> j) & 1u) ? G.x[j] : 0u;
+    xl ^= ((el >> j) & 1u) ? G.x[3 + j] : 0u;
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    rh[e] = rl[e] = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      rh[e] ^= (e >> j) & 1 ? G.x[L + j] : 0u;
+      rl[e] ^= (e >> j) & 1 ? G.x[j] : 0u;
+    }
+  }
+  double ov[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) ov[j] = 0.0;
+  for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const uint32_t t0 = tile_base(tile * B + b, G), th = t0 ^ xh, tl = t0 ^ xl;
+    Cx v[8], l[8];
+    const uint32_t first = ADJOINT ? th : tl, last = ADJOINT ? tl : th;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t t = first ^ (ADJOINT ? rh[e] : rl[e]);
+      v[e] = load_cx(psi, t);
+      if (ADJOINT) l[e] = load_cx(lam, t);
+    }
+    if (ADJOINT) {
+#pragma unroll
+      for (int j = K - 1; j >= L; --j) tile_step<true>(v, l, th, rh, j - L, G, j, ov[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < L; ++j) tile_step<false>(v, l, tl, rl, j, G, j, ov[j]);
+    }
+    // element e of stage H is orbit element (e << L) | el, of stage L (el << 3) | e
+    if (tile != blockIdx.x) __syncthreads();  // the previous tile is read
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      const uint32_t at = (ADJOINT ? (e << L) | el : (el << 3) | e) * B + b;
+      s_v[at] = make_double2(v[e].r, v[e].i);
+      if (ADJOINT) s_l[at] = make_double2(l[e].r, l[e].i);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      const uint32_t at = (ADJOINT ? (el << 3) | e : (e << L) | el) * B + b;
+      const double2 w = s_v[at];
+      v[e] = Cx{w.x, w.y};
+      if (ADJOINT) {
+        const double2 m = s_l[at];
+        l[e] = Cx{m.x, m.y};
+      }
+    }
+    if (ADJOINT) {
+#pragma unroll
+      for (int j = L - 1; j >= 0; --j) tile_step<true>(v, l, tl, rl, j, G, j, ov[j]);
+    } else {
+#pragma unroll
+      for (int j = L; j < K; ++j) tile_step<false>(v, l, th, rh, j - L, G, j, ov[j]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t t = last ^ (ADJOINT ? rl[e] : rh[e]);
+      store_cx(psi, t, v[e]);
+      if (ADJOINT) store_cx(lam, t, l[e]);
+    }
+  }
+  if (ADJOINT) {
+    double* red = reinterpret_cast<double*>(tile_smem);  // [K][waves]
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      for (int d = 32; d > 0; d >>= 1) ov[j] += __shfl_xor(ov[j], d, 64);
+      if ((threadIdx.x & 63u) == 0) red[j * (kBlock / 64) + (threadIdx.x >> 6)] = ov[j];
+    }
+    __syncthreads();
+    if (threadIdx.x < K) {
+      double sum = 0.0;
+      for (int w = 0; w < kBlock / 64; ++w) sum += red[threadIdx.x * (kBlock / 64) + w];
+      double* out = partial + 3ull * stride * threadIdx.x + 3ull * blockIdx.x;
+      out[0] = 0.0;  // the real part is not needed
+      out[1] = sum;
+      out[2] = 0.0;
+    }
+  }
+}
+
 // out[k] = (sum of the partials of overlap k, real and imaginary parts), fixed order.
 __global__ __launch_bounds__(kBlock) void k_sum_overlaps(const double* partial, uint32_t nparts, double* out) {
   const double* p = partial + 3ull * nparts * blockIdx.x;
@@ -520,7 +690,7 @@ struct pbs_vqe {
   uint32_t nparts = 0;
   bool evaluated = false;  // blk_in holds psi(theta) of the last evaluation
   uint32_t n_transposed = 0;  // blocks stored as sector (N_beta, N_alpha)
-  uint32_t group_fwd = 3, group_adj = 3;  // most rotations fused per forward / adjoint pass (1..3)
+  uint32_t group_fwd = 6, group_adj = 6;  // most rotations fused per forward / adjoint pass
   ~pbs_vqe() {
     if (batch) pbs_batch_destroy(batch);
     for (pbs_space* sp : spaces) pbs_space_destroy(sp);
@@ -552,6 +722,48 @@ bool make_group(const pbs_vqe& v, uint32_t first, const double* theta, double si
   return true;
 }
 
+// Rotations first .. first+K-1 for k_tile_group, or false when their X masks
+// are not linearly independent.
+template <int K>
+bool make_tile(const pbs_vqe& v, uint32_t first, const double* theta, double sign, TileGroup<K>& G) {
+  RotGroup<K> R;
+  if (!make_group<K>(v, first, theta, sign, R)) return false;
+  for (int j = 0; j < K; ++j) {
+    G.x[j] = static_cast<uint32_t>(R.r[j].x);
+    G.z[j] = static_cast<uint32_t>(R.r[j].z);
+    G.turn[j] = static_cast<uint32_t>(__builtin_popcount(G.x[j] & G.z[j]));
+    G.om[j] = R.r[j].omega;
+    G.piv[j] = R.piv[j];
+    G.c[j] = R.r[j].c;
+    G.s[j] = R.r[j].s;
+  }
+  return true;
+}
+
+// Launches the longest group of 6, 5 or 4 rotations that starts (forward) or
+// ends (ADJOINT) at k; returns their number, or 0 when there is none.
+template <class T, bool ADJOINT, int K = 6>
+uint32_t launch_tile(pbs_vqe& v, const double* theta, uint32_t k, hipStream_t s) {
+  if constexpr (K < 4) {
+    return 0;
+  } else {
+    const uint32_t most = ADJOINT ? v.group_adj : v.group_fwd, left = ADJOINT ? k : v.n_rot - k;
+    TileGroup<K> G;
+    if (most >= K && left >= K && v.dim >= kTileElems &&
+        make_tile<K>(v, ADJOINT ? k - K : k, theta, ADJOINT ? -1.0 : 1.0, G)) {
+      const uint32_t tiles = static_cast<uint32_t>(v.dim / kTileElems);
+      const uint32_t grid = ADJOINT ? v.nparts : std::min(tiles, kVqeGrid);
+      const size_t lds = kTileElems * sizeof(double2) * (ADJOINT ? 2 : 1);
+      hipLaunchKernelGGL((k_tile_group<T, ADJOINT, K>), dim3(grid), dim3(kBlock), lds, s,
+                         reinterpret_cast<T*>(v.psi.get()), reinterpret_cast<T*>(v.lam.get()), tiles, G,
+                         ADJOINT ? v.partial.get() + 3ull * v.nparts * (k - K) : nullptr,
+                         static_cast<uint64_t>(v.nparts));
+      return K;
+    }
+    return launch_tile<T, ADJOINT, K - 1>(v, theta, k, s);
+  }
+}
+
 template <class T>
 void rotate_all(pbs_vqe& v, T* psi, const double* theta, bool inverse, uint32_t k, hipStream_t s) {
   const Rot& r = v.rots[k];
@@ -572,7 +784,9 @@ void energy_grad(pbs_vqe& v, const double* theta, double* energy, double* grad, 
   for (uint32_t k = 0; k < v.n_rot;) {
     RotGroup<3> G3;
     RotGroup<2> G2;
-    if (v.group_fwd >= 3 && k + 2 < v.n_rot && v.dim >= 8 && make_group<3>(v, k, theta, 1.0, G3)) {
+    if (const uint32_t n = launch_tile<T, false>(v, theta, k, s)) {
+      k += n;
+    } else if (v.group_fwd >= 3 && k + 2 < v.n_rot && v.dim >= 8 && make_group<3>(v, k, theta, 1.0, G3)) {
       hipLaunchKernelGGL((k_rotate_group<T, 3>), dim3(grid_for(v.dim / 8, kBlock, kVqeGrid)), dim3(kBlock), 0, s,
                          psi, v.dim, G3);
       k += 3;
@@ -601,7 +815,9 @@ void energy_grad(pbs_vqe& v, const double* theta, double* energy, double* grad, 
     for (uint32_t k = v.n_rot; k > 0;) {
       RotGroup<3> G3;
       RotGroup<2> G2;
-      if (v.group_adj >= 3 && k >= 3 && v.dim >= 8 && make_group<3>(v, k - 3, theta, -1.0, G3)) {
+      if (const uint32_t n = launch_tile<T, true>(v, theta, k, s)) {
+        k -= n;
+      } else if (v.group_adj >= 3 && k >= 3 && v.dim >= 8 && make_group<3>(v, k - 3, theta, -1.0, G3)) {
         hipLaunchKernelGGL((k_adjoint_group<T, 3>), dim3(v.nparts), dim3(kBlock), 0, s, psi, lam, v.dim, G3,
                            v.partial.get() + 3ull * v.nparts * (k - 3), static_cast<uint64_t>(v.nparts));
         k -= 3;
@@ -671,9 +887,6 @@ pbs_status pbs_vqe_create(const pbs_grouped* h, uint32_t n_orb, uint32_t n_rot, 
       v->n_rot = n_rot;
       v->dt = dt;
       v->dim = dim;
-      // measured at 24 qubits: three-rotation adjoint passes need 328 registers
-      // per lane (one wave per SIMD), which pays off for complex128 only
-      v->group_adj = dt == PBS_C128 ? 3u : 2u;
       v->ref = ref;
       for (uint32_t k = 0; k < n_rot; ++k) v->rots.push_back(rot_of(x[k], z[k]));
       const size_t esz = dt == PBS_C128 ? 16 : 8;

@@ -247,3 +247,36 @@ def test_vqe_refuses_sector_changing_operators(dev, extra):
     S.canonicalize()
     with pytest.raises(PbsError, match="N_alpha and N_beta"):
         api.VQE(S.group(), n_orb, np.zeros(0, np.uint64), np.zeros(0, np.uint64), 0b111)
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("n_rot", [4, 5, 6, 7, 11, 29])
+def test_vqe_tile_groups_match_single_rotations(dev, n_rot, dtype):
+    """Passes of four to six rotations (the default from 2^11 amplitudes on)
+    against one rotation per pass, with diagonal strings, repeated masks and
+    low-bit masks in the list so that groups of every length occur.  Both
+    apply the same float64 operations to each amplitude up to one fused
+    multiply-add (complex64 storage rounds less often), so the bars are those
+    of the oracle tests: 1e-12 and 1e-11 (2e-6, 4e-6) of the coefficient sum."""
+    api = _api()
+    n_orb = 6
+    h1, h2 = synth.molecular_spin_integrals(n_orb, seed=83)
+    H = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev))
+    scale = float(np.abs(H.read()[2]).sum())
+    x, z = synth.excitation_masks(n_orb, 3, 3, n_rot)
+    rng = np.random.default_rng(84 + n_rot)
+    if n_rot > 6:
+        x[2], z[2] = 0, 0b1010  # diagonal
+        x[5], z[5] = 0b11, 0b01  # the lowest bits
+        z[n_rot - 1], x[n_rot - 1] = 0, x[n_rot - 2]  # a repeated mask without a Y
+    ref = 0b111 | (0b111 << n_orb)
+    theta = rng.normal(size=n_rot) * 0.4
+    v = api.VQE(H.group(), n_orb, x, z, ref, dtype=dtype)
+    e, g = v.energy_grad(theta)
+    assert np.array_equal(v.energy_grad(theta)[1], g)
+    psi = v.state()
+    v.set_groups(1, 1)
+    e1, g1 = v.energy_grad(theta)
+    tol_e, tol_g = (1e-12 * scale, 1e-11 * scale) if dtype == torch.complex128 else (2e-6 * scale, 4e-6 * scale)
+    assert abs(e - e1) < tol_e and np.abs(g - g1).max() < tol_g
+    assert (psi - v.state()).abs().max().item() < (1e-12 if dtype == torch.complex128 else 2e-6)
