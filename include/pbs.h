@@ -456,7 +456,8 @@ pbs_status pbs_vqe_set_config(pbs_vqe* v, uint32_t config);
 
 /* Most consecutive rotations applied in one pass over the state (forward
  * sweep) and undone in one pass over state and adjoint (gradient sweep), each
- * 1, 2 or 3; rotations are fused when their X masks are linearly
+ * 1, 2 or 3 (a handle that was never told fuses up to 8 where the state has
+ * the size for it); rotations are fused when their X masks are linearly
  * independent.  The results do not depend on it beyond rounding. */
 pbs_status pbs_vqe_set_groups(pbs_vqe* v, uint32_t forward, uint32_t adjoint);
 

@@ -320,28 +320,33 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_group(T* __restrict__ psi, T
   }
 }
 
-// ---------------------------------------------------------------- K = 4..6 rotations per pass
-// The same orbits, eight elements per lane and two register stages: a
-// workgroup holds 2,048 elements (2^K of 2,048 >> K consecutive orbits) and
-// exchanges them once through LDS, so the vectors are read and written once
-// per K rotations.  Stage H keeps the orbit bits K-3 .. K-1 in a lane's
-// registers (rotations K-3 .. K-1), stage L the bits 0 .. 2 (rotations
-// 0 .. K-4); the other K-3 bits and the orbit number are the lane.  Orbits
-// are consecutive, so the reads and writes stay contiguous (512 bytes at K =
-// 6) where the pivot bits lie above the orbit number's.
+// ---------------------------------------------------------------- K = 4..8 rotations per pass
+// The same orbits with two register stages: a lane holds 2^R elements (R = 3
+// for K <= 6, 4 above), a workgroup 256 x 2^R (2^K of each of as many
+// consecutive orbits as that makes), and exchanges them once through LDS, so
+// the vectors are read and written once per K rotations.  Stage H keeps the
+// orbit bits K-R .. K-1 in a lane's registers (rotations K-R .. K-1), stage L
+// the bits 0 .. R-1 (rotations 0 .. K-R-1); the other K-R bits and the orbit
+// number are the lane.  Orbits are consecutive, so the reads and writes stay
+// contiguous (512 bytes at K = 6, 256 at K = 8) where the pivot bits lie above
+// the orbit number's.
 //
 // Bound by memory: four vectors per adjoint pass.  At 24 qubits, complex128,
-// three rotations per pass take 228 us (4.7 TB/s, a copy's rate); see
-// energy_grad for the measured passes of six.
-constexpr uint32_t kTileElems = 2048;
+// an adjoint pass of six takes 205 us (5.2 TB/s, what a copy reaches), of
+// eight 219, and forward passes 71 and 75, where passes of three took 228 and
+// 72: 200 rotations in 14.6 and 4.8 ms before, 5.8 and 1.9 now.
+constexpr uint32_t kMaxTileRot = 8;
+constexpr int tile_regs(int k) { return k <= 6 ? 3 : 4; }
+constexpr uint32_t tile_elems(int k) { return static_cast<uint32_t>(kBlock) << tile_regs(k); }
 
 template <int K>
 struct TileGroup {
   uint32_t x[K], z[K];
   uint32_t turn[K];  // parity of z & x
-  uint32_t om[K];    // power of i of the string, 0..3
   uint32_t piv[K];   // ascending
-  double c[K], s[K];
+  double c[K];
+  double ga[K], gb[K];  // i sin(theta) i^om
+  double ua[K], ub[K];  // i^om
 };
 
 template <int K>
@@ -354,65 +359,78 @@ __device__ inline uint32_t tile_base(uint32_t i, const TileGroup<K>& G) {
   return i;
 }
 
-// Image of v under the string, up to the factor i^om (-1)^q of its target:
-// om & 1 exchanges the components, its sign and om & 2 join q.
-__device__ __forceinline__ Cx turned(const Cx& v, bool odd, uint32_t q) {
-  return odd ? Cx{signed_by(v.i, q + 1u), signed_by(v.r, q)} : Cx{signed_by(v.r, q), signed_by(v.i, q)};
-}
-
-// Rotation j on the lane's eight elements at t ^ rc[e], pairs differing in
-// register bit `bit`: v <- c v + i s (P v).  ADJOINT: the same on l, and
-// first ov += Im conj(l) (P v) over the pairs.
-template <bool ADJOINT, int K>
-__device__ __forceinline__ void tile_step(Cx (&v)[8], Cx (&l)[8], uint32_t t, const uint32_t (&rc)[8], int bit,
+// Rotation j on the lane's elements at t ^ rc[e], pairs differing in
+// register bit `bit`: v <- c v + i s (P v), where (P v)[t] = i^om (-1)^q
+// v[t ^ x] with q the parity of z at t ^ x.  ADJOINT: the same on l, and first
+// ov += Im conj(l) (P v) over the pairs.  ODD: every string of the group has an
+// odd number of Y (excitation strings do), so i s i^om is real; otherwise it
+// is taken as a complex number, without a branch per string.
+template <bool ADJOINT, bool ODD, int K, int E>
+__device__ __forceinline__ void tile_step(Cx (&v)[E], Cx (&l)[E], uint32_t t, const uint32_t (&rc)[E], int bit,
                                           const TileGroup<K>& G, int j, double& ov) {
-  const uint32_t q0 = __popc(G.z[j] & t) + (G.om[j] >> 1);
-  const bool odd = G.om[j] & 1u;
-  const double c = G.c[j], s = G.s[j];
-  auto turn = [&](Cx& a, const Cx& p) { a = Cx{fma(c, a.r, -s * p.i), fma(c, a.i, s * p.r)}; };
+  // (the mask redefined per step: the parities of all steps' elements, held
+  // across the tile loop, would take the registers of the amplitudes)
+  uint32_t z = G.z[j];
+  asm volatile("" : "+s"(z));
+  const uint32_t q0 = __popc(z & t);
+  const double c = G.c[j], ga = G.ga[j], gb = G.gb[j];
+  auto turn = [&](Cx& a, const Cx& w, uint32_t q) {
+    const double ca = signed_by(ga, q);
+    if (ODD) {
+      a = Cx{fma(c, a.r, ca * w.r), fma(c, a.i, ca * w.i)};
+    } else {
+      const double cb = signed_by(gb, q);
+      a = Cx{fma(c, a.r, fma(ca, w.r, -cb * w.i)), fma(c, a.i, fma(ca, w.i, cb * w.r))};
+    }
+  };
+  // Im conj(l) i^om w: i^om = (ga + i gb) / (i s), its components ua, ub
+  auto overlap = [&](const Cx& m, const Cx& w, uint32_t q) {
+    const double same = fma(m.r, w.r, m.i * w.i);
+    const double d = ODD ? same * G.ub[j] : fma(G.ub[j], same, G.ua[j] * fma(m.r, w.i, -m.i * w.r));
+    ov += signed_by(d, q);
+  };
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < E; ++e) {
     const int f = e | (1 << bit);
     if (e == f) continue;
-    const uint32_t qe = q0 + __popc(G.z[j] & rc[e]), qf = qe + G.turn[j];  // parities at the two elements
-    const Cx pe = turned(v[f], odd, qf), pf = turned(v[e], odd, qe);
+    const uint32_t qe = q0 + __popc(z & rc[e]), qf = qe + G.turn[j];  // parities at the two elements
+    const Cx ve = v[e], vf = v[f];
     if (ADJOINT) {
-      ov = fma(l[e].r, pe.i, fma(-l[e].i, pe.r, ov));
-      ov = fma(l[f].r, pf.i, fma(-l[f].i, pf.r, ov));
-      const Cx le = turned(l[f], odd, qf), lf = turned(l[e], odd, qe);
-      turn(l[e], le);
-      turn(l[f], lf);
+      overlap(l[e], vf, qf);
+      overlap(l[f], ve, qe);
+      const Cx le = l[e], lf = l[f];
+      turn(l[e], lf, qf);
+      turn(l[f], le, qe);
     }
-    turn(v[e], pe);
-    turn(v[f], pf);
+    turn(v[e], vf, qf);
+    turn(v[f], ve, qe);
   }
 }
 
 // psi <- R_{K-1} ... R_0 psi (ADJOINT false), or K adjoint steps from the
 // last rotation to the first (G carries cos, sin of -theta): partial_j =
 // partial + 3 stride j gets Im <lam|P_j|psi> of every workgroup.
-template <class T, bool ADJOINT, int K>
-__global__ __launch_bounds__(kBlock) void k_tile_group(T* __restrict__ psi, T* __restrict__ lam, uint32_t tiles,
+template <class T, bool ADJOINT, bool ODD, int K>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!ADJOINT ? 4 : K <= 6 ? 3 : 2))) void k_tile_group(T* __restrict__ psi, T* __restrict__ lam, uint32_t tiles,
                                                         TileGroup<K> G, double* __restrict__ partial,
                                                         uint64_t stride) {
-  constexpr int L = K - 3;                   // lane bits of the orbit index
-  constexpr uint32_t B = kTileElems >> K;    // orbits per workgroup
-  static_assert(kBlock * 8 == kTileElems, "eight elements per lane");
+  constexpr int R = tile_regs(K), E = 1 << R;    // elements per lane
+  constexpr int L = K - R;                       // lane bits of the orbit index
+  constexpr uint32_t B = tile_elems(K) >> K;     // orbits per workgroup
   extern __shared__ __align__(16) unsigned char tile_smem[];
-  double2* s_v = reinterpret_cast<double2*>(tile_smem);
-  double2* s_l = s_v + kTileElems;
+  double2* s_x = reinterpret_cast<double2*>(tile_smem);
   const uint32_t b = threadIdx.x % B, el = threadIdx.x / B;
-  uint32_t xh = 0, xl = 0, rh[8], rl[8];
+  uint32_t xh = 0, xl = 0, rh[E], rl[E];
 #pragma unroll
   for (int j = 0; j < L; ++j) {
     xh ^= ((el >> j) & 1u) ? G.x[j] : 0u;
-    xl ^= ((el >> j) & 1u) ? G.x[3 + j] : 0u;
+    xl ^= ((el >> j) & 1u) ? G.x[R + j] : 0u;
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < E; ++e) {
     rh[e] = rl[e] = 0;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
+    for (int j = 0; j < R; ++j) {
       rh[e] ^= (e >> j) & 1 ? G.x[L + j] : 0u;
       rl[e] ^= (e >> j) & 1 ? G.x[j] : 0u;
     }
@@ -422,49 +440,45 @@ __global__ __launch_bounds__(kBlock) void k_tile_group(T* __restrict__ psi, T* _
   for (int j = 0; j < K; ++j) ov[j] = 0.0;
   for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const uint32_t t0 = tile_base(tile * B + b, G), th = t0 ^ xh, tl = t0 ^ xl;
-    Cx v[8], l[8];
+    Cx v[E], l[E];
     const uint32_t first = ADJOINT ? th : tl, last = ADJOINT ? tl : th;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < E; ++e) {
       const uint32_t t = first ^ (ADJOINT ? rh[e] : rl[e]);
       v[e] = load_cx(psi, t);
       if (ADJOINT) l[e] = load_cx(lam, t);
     }
     if (ADJOINT) {
 #pragma unroll
-      for (int j = K - 1; j >= L; --j) tile_step<true>(v, l, th, rh, j - L, G, j, ov[j]);
+      for (int j = K - 1; j >= L; --j) tile_step<true, ODD>(v, l, th, rh, j - L, G, j, ov[j]);
     } else {
 #pragma unroll
-      for (int j = 0; j < L; ++j) tile_step<false>(v, l, tl, rl, j, G, j, ov[j]);
+      for (int j = 0; j < L; ++j) tile_step<false, ODD>(v, l, tl, rl, j, G, j, ov[j]);
     }
-    // element e of stage H is orbit element (e << L) | el, of stage L (el << 3) | e
-    if (tile != blockIdx.x) __syncthreads();  // the previous tile is read
+    // element e of stage H is orbit element (e << L) | el, of stage L (el << R) | e
+    auto exchange = [&](Cx(&a)[E]) {
+      __syncthreads();  // the previous exchange is read
 #pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) {
-      const uint32_t at = (ADJOINT ? (e << L) | el : (el << 3) | e) * B + b;
-      s_v[at] = make_double2(v[e].r, v[e].i);
-      if (ADJOINT) s_l[at] = make_double2(l[e].r, l[e].i);
-    }
-    __syncthreads();
+      for (uint32_t e = 0; e < E; ++e)
+        s_x[(ADJOINT ? (e << L) | el : (el << R) | e) * B + b] = make_double2(a[e].r, a[e].i);
+      __syncthreads();
 #pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) {
-      const uint32_t at = (ADJOINT ? (el << 3) | e : (e << L) | el) * B + b;
-      const double2 w = s_v[at];
-      v[e] = Cx{w.x, w.y};
-      if (ADJOINT) {
-        const double2 m = s_l[at];
-        l[e] = Cx{m.x, m.y};
+      for (uint32_t e = 0; e < E; ++e) {
+        const double2 w = s_x[(ADJOINT ? (el << R) | e : (e << L) | el) * B + b];
+        a[e] = Cx{w.x, w.y};
       }
-    }
+    };
+    exchange(v);
+    if (ADJOINT) exchange(l);
     if (ADJOINT) {
 #pragma unroll
-      for (int j = L - 1; j >= 0; --j) tile_step<true>(v, l, tl, rl, j, G, j, ov[j]);
+      for (int j = L - 1; j >= 0; --j) tile_step<true, ODD>(v, l, tl, rl, j, G, j, ov[j]);
     } else {
 #pragma unroll
-      for (int j = L; j < K; ++j) tile_step<false>(v, l, th, rh, j - L, G, j, ov[j]);
+      for (int j = L; j < K; ++j) tile_step<false, ODD>(v, l, th, rh, j - L, G, j, ov[j]);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < E; ++e) {
       const uint32_t t = last ^ (ADJOINT ? rl[e] : rh[e]);
       store_cx(psi, t, v[e]);
       if (ADJOINT) store_cx(lam, t, l[e]);
@@ -690,7 +704,7 @@ struct pbs_vqe {
   uint32_t nparts = 0;
   bool evaluated = false;  // blk_in holds psi(theta) of the last evaluation
   uint32_t n_transposed = 0;  // blocks stored as sector (N_beta, N_alpha)
-  uint32_t group_fwd = 6, group_adj = 6;  // most rotations fused per forward / adjoint pass
+  uint32_t group_fwd = kMaxTileRot, group_adj = kMaxTileRot;  // most rotations fused per forward / adjoint pass
   ~pbs_vqe() {
     if (batch) pbs_batch_destroy(batch);
     for (pbs_space* sp : spaces) pbs_space_destroy(sp);
@@ -732,31 +746,37 @@ bool make_tile(const pbs_vqe& v, uint32_t first, const double* theta, double sig
     G.x[j] = static_cast<uint32_t>(R.r[j].x);
     G.z[j] = static_cast<uint32_t>(R.r[j].z);
     G.turn[j] = static_cast<uint32_t>(__builtin_popcount(G.x[j] & G.z[j]));
-    G.om[j] = R.r[j].omega;
     G.piv[j] = R.piv[j];
     G.c[j] = R.r[j].c;
-    G.s[j] = R.r[j].s;
+    const double re[4] = {1.0, 0.0, -1.0, 0.0}, im[4] = {0.0, 1.0, 0.0, -1.0};
+    const uint32_t om = R.r[j].omega & 3u;
+    G.ua[j] = re[om];
+    G.ub[j] = im[om];
+    G.ga[j] = -R.r[j].s * im[om];
+    G.gb[j] = R.r[j].s * re[om];
   }
   return true;
 }
 
-// Launches the longest group of 6, 5 or 4 rotations that starts (forward) or
+// Launches the longest group of 8 .. 4 rotations that starts (forward) or
 // ends (ADJOINT) at k; returns their number, or 0 when there is none.
-template <class T, bool ADJOINT, int K = 6>
+template <class T, bool ADJOINT, int K = static_cast<int>(kMaxTileRot)>
 uint32_t launch_tile(pbs_vqe& v, const double* theta, uint32_t k, hipStream_t s) {
   if constexpr (K < 4) {
     return 0;
   } else {
     const uint32_t most = ADJOINT ? v.group_adj : v.group_fwd, left = ADJOINT ? k : v.n_rot - k;
     TileGroup<K> G;
-    if (most >= K && left >= K && v.dim >= kTileElems &&
+    if (most >= K && left >= K && v.dim >= tile_elems(K) &&
         make_tile<K>(v, ADJOINT ? k - K : k, theta, ADJOINT ? -1.0 : 1.0, G)) {
-      const uint32_t tiles = static_cast<uint32_t>(v.dim / kTileElems);
+      const uint32_t tiles = static_cast<uint32_t>(v.dim / tile_elems(K));
       const uint32_t grid = ADJOINT ? v.nparts : std::min(tiles, kVqeGrid);
-      const size_t lds = kTileElems * sizeof(double2) * (ADJOINT ? 2 : 1);
-      hipLaunchKernelGGL((k_tile_group<T, ADJOINT, K>), dim3(grid), dim3(kBlock), lds, s,
-                         reinterpret_cast<T*>(v.psi.get()), reinterpret_cast<T*>(v.lam.get()), tiles, G,
-                         ADJOINT ? v.partial.get() + 3ull * v.nparts * (k - K) : nullptr,
+      const size_t lds = tile_elems(K) * sizeof(double2);
+      bool odd = true;
+      for (int j = 0; j < K; ++j) odd = odd && G.ub[j] != 0.0;
+      hipLaunchKernelGGL((odd ? k_tile_group<T, ADJOINT, true, K> : k_tile_group<T, ADJOINT, false, K>), dim3(grid),
+                         dim3(kBlock), lds, s, reinterpret_cast<T*>(v.psi.get()), reinterpret_cast<T*>(v.lam.get()),
+                         tiles, G, ADJOINT ? v.partial.get() + 3ull * v.nparts * (k - K) : nullptr,
                          static_cast<uint64_t>(v.nparts));
       return K;
     }

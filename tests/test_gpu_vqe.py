@@ -250,9 +250,9 @@ def test_vqe_refuses_sector_changing_operators(dev, extra):
 
 
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
-@pytest.mark.parametrize("n_rot", [4, 5, 6, 7, 11, 29])
+@pytest.mark.parametrize("n_rot", [4, 5, 6, 7, 8, 11, 41])
 def test_vqe_tile_groups_match_single_rotations(dev, n_rot, dtype):
-    """Passes of four to six rotations (the default from 2^11 amplitudes on)
+    """Passes of four to eight rotations (the default from 2^11 amplitudes on)
     against one rotation per pass, with diagonal strings, repeated masks and
     low-bit masks in the list so that groups of every length occur.  Both
     apply the same float64 operations to each amplitude up to one fused
