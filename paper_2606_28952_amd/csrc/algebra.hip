@@ -34,17 +34,6 @@ __global__ void k_pauli_mul(uint64_t n, int W, const uint64_t* xa, const uint64_
   }
 }
 
-// i^g * (re, im)
-__device__ inline void rotate(uint32_t g, double& re, double& im) {
-  const double r = re, m = im;
-  switch (g & 3u) {
-    case 0: break;
-    case 1: re = -m; im = r; break;
-    case 2: re = -r; im = -m; break;
-    default: re = m; im = -r; break;
-  }
-}
-
 // AoS strings + interleaved coefficients -> SoA keys (z words, then x words) and re/im.
 __global__ void k_to_soa(uint64_t m, int W, const uint64_t* x, const uint64_t* z, const double* c, uint64_t* keys,
                          double* re, double* im) {
@@ -59,67 +48,136 @@ __global__ void k_to_soa(uint64_t m, int W, const uint64_t* x, const uint64_t* z
   }
 }
 
-__global__ void k_segment_starts(const uint32_t* heads, const uint32_t* segid, uint64_t m, uint32_t* start) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    if (heads[i]) start[segid[i]] = static_cast<uint32_t>(i);
+// Rows that one sorted item stands for.  Array rows: item v is row v.
+struct ArrayRows {
+  static constexpr uint32_t kRows = 1;
+  const double *re, *im;
+  template <class F>
+  __device__ void visit(uint32_t v, F&& f) const {
+    f(re[v], im[v]);
+  }
+};
+
+// i^g * (re, im)
+__device__ inline void rotate(uint32_t g, double& re, double& im) {
+  const double r = re, m = im;
+  switch (g & 3u) {
+    case 0: break;
+    case 1: re = -m; im = r; break;
+    case 2: re = -r; im = -m; break;
+    default: re = m; im = -r; break;
+  }
 }
 
-// Fast path of the correctly rounded segment sums.  Cascaded TWO-SUM (the
-// Sum2 scheme of Ogita, Rump and Oishi, 2005) gives s = fl(sum x) and the
+// Product rows: item v is the term pair v mod 2^30 = k nb + l with phase
+// exponent v >> 30.  a_k b_l is the exact sum of four rows of TWO-PRODUCT
+// pieces (p = fl(a b), e = fma(a, b, -p)), so the canonical reduction rounds
+// the exact pair sums once.  They are formed again wherever they are summed:
+// sorting pairs instead of their rows moves a quarter of the bytes.
+struct PairRows {
+  static constexpr uint32_t kRows = 4;
+  const double *a, *b;
+  uint32_t nb;
+  template <class F>
+  __device__ void visit(uint32_t v, F&& f) const {
+    const uint32_t t = v & 0x3fffffffu, g = v >> 30;
+    const uint32_t k = t / nb, l = t - k * nb;
+    const double ar = a[2 * k], ai = a[2 * k + 1], br = b[2 * l], bi = b[2 * l + 1];
+    const double p1 = ar * br, e1 = fma(ar, br, -p1);
+    const double p2 = ai * bi, e2 = fma(ai, bi, -p2);
+    const double p3 = ar * bi, e3 = fma(ar, bi, -p3);
+    const double p4 = ai * br, e4 = fma(ai, br, -p4);
+    double r0 = p1, i0 = p3, r1 = e1, i1 = e3, r2 = -p2, i2 = p4, r3 = -e2, i3 = e4;
+    rotate(g, r0, i0);
+    rotate(g, r1, i1);
+    rotate(g, r2, i2);
+    rotate(g, r3, i3);
+    f(r0, i0);
+    f(r1, i1);
+    f(r2, i2);
+    f(r3, i3);
+  }
+};
+
+// Fast path of the correctly rounded segment sums.  Cascaded TWO-SUM (after
+// the Sum2 scheme of Ogita, Rump and Oishi, 2005) gives s = fl(sum x) and the
 // exact rounding errors q_j, so the exact sum is T = s + sum q_j.  The lanes
 // of a wave sum strided parts of a run and are merged by TWO-SUM as well, so
-// at most N = n + 64 error terms arise; any summation tree of them gives
-// |fl(sum q_j) - sum q_j| <= gamma_N sum |q_j| and sum |q_j| <= e / (1 - gamma_N)
-// for e = fl(sum |q_j|), gamma_N = N u / (1 - N u), u = 2^-53, so for N u <= 1/4
-// the compensation c is within 2 N u e.  With r = fl(s + c) and its exact
-// error er, |T - r| <= |er| + 2 N u e; when this (rounded upward) is below
-// half the smaller gap next to r, r is the round-to-nearest value of T.  T is
-// also a multiple of g, the smallest unit in the last place among the
-// inputs, so r = 0 with a bound below g proves T = 0.  When every q_j is
-// zero, s is exact.
+// at most N = n + 64 error terms arise.  Their sum is cascaded the same way:
+// c = fl(sum q) with exact errors p_j, so T = s + c + sum p_j, and any
+// summation tree of at most 2 N of them gives |fl(sum p_j) - sum p_j| <=
+// gamma sum |p_j| and sum |p_j| <= e / (1 - gamma) for e = fl(sum |p_j|),
+// gamma = 2 N u / (1 - 2 N u), u = 2^-53, so for 2 N u <= 1/4 the second
+// compensation d is within 4 N u e.
+//  * When every p_j is zero (e = 0), T = s + c and r = fl(s + c) is its
+//    correctly rounded value, also at a tie: the common case, since the q_j of
+//    one run share an exponent range.
+//  * Otherwise, with r = fl(s + c) and its exact error er, |T - r| <=
+//    |fl(er + d)| (1 + u) + 4 N u e; when this (rounded upward) is below half
+//    the smaller gap next to r, r is the round-to-nearest value of T.  T is
+//    also a multiple of g, the smallest unit in the last place among the
+//    inputs, so r = 0 with a bound below g proves T = 0.
 struct Sum2 {
-  double s = 0.0, c = 0.0, e = 0.0;
+  double s = 0.0, c = 0.0, d = 0.0, e = 0.0;
   int emin = 2047;  // smallest max(biased exponent, 1) over nonzero inputs
 };
 
+__device__ inline void sum2_err(Sum2& a, double q) {
+  double t, p;
+  two_sum(a.c, q, t, p);
+  a.c = t;
+  a.d += p;
+  a.e += fabs(p);
+}
+
+// Adding a zero changes nothing; where no lane has anything else (half the
+// parts of a real operator's rows) the step is skipped.
 __device__ inline void sum2_add(Sum2& a, double v) {
+  if (v == 0.0) return;
   double t, q;
   two_sum(a.s, v, t, q);
   a.s = t;
-  a.c += q;
-  a.e += fabs(q);
+  sum2_err(a, q);
   const int be = static_cast<int>((static_cast<uint64_t>(__double_as_longlong(v)) >> 52) & 0x7ffu);
-  if (v != 0.0) a.emin = min(a.emin, max(be, 1));
+  a.emin = min(a.emin, max(be, 1));
 }
 
-__device__ inline void sum2_merge(Sum2& a, double s, double c, double e, int emin) {
+__device__ inline void sum2_merge(Sum2& a, const Sum2& b) {
   double t, q;
-  two_sum(a.s, s, t, q);
+  two_sum(a.s, b.s, t, q);
   a.s = t;
-  a.c = (a.c + c) + q;
-  a.e = (a.e + e) + fabs(q);
-  a.emin = min(a.emin, emin);
+  sum2_err(a, b.c);
+  sum2_err(a, q);
+  a.d += b.d;
+  a.e += b.e;
+  a.emin = min(a.emin, b.emin);
 }
 
-__device__ inline void sum2_wave_merge(Sum2& a) {
-  for (int d = 32; d > 0; d >>= 1)
-    sum2_merge(a, __shfl_xor(a.s, d, 64), __shfl_xor(a.c, d, 64), __shfl_xor(a.e, d, 64),
-               __shfl_xor(a.emin, d, 64));
+// Merges the sums of groups of `lanes` adjacent lanes (a power of two).
+__device__ inline void sum2_merge_lanes(Sum2& a, int lanes) {
+  for (int d = lanes / 2; d > 0; d >>= 1) {
+    Sum2 b;
+    b.s = __shfl_xor(a.s, d, 64);
+    b.c = __shfl_xor(a.c, d, 64);
+    b.d = __shfl_xor(a.d, d, 64);
+    b.e = __shfl_xor(a.e, d, 64);
+    b.emin = __shfl_xor(a.emin, d, 64);
+    sum2_merge(a, b);
+  }
 }
 
 // True when r is proven to be the correctly rounded sum (N error terms at most).
 __device__ inline bool sum2_round(const Sum2& a, uint32_t N, double& r) {
-  if (a.e == 0.0) {
-    r = a.s + 0.0;
-    return true;
-  }
-  if (N >= (1u << 30)) return false;
   double rr, er;
   two_sum(a.s, a.c, rr, er);
-  if (!isfinite(rr)) return false;
-  const double two_nu = static_cast<double>(N) * 0x1p-52;  // exact: N < 2^30
-  const double bound = (fabs(er) + two_nu * a.e * (1.0 + 0x1p-50)) * (1.0 + 0x1p-50);
+  if (!isfinite(rr) || !isfinite(a.e)) return false;
+  if (a.e == 0.0) {
+    r = rr + 0.0;
+    return true;
+  }
+  if (N >= (1u << 29)) return false;
+  const double four_nu = static_cast<double>(N) * 0x1p-51;  // exact: N < 2^29
+  const double bound = (fabs(er + a.d) * (1.0 + 0x1p-50) + four_nu * a.e * (1.0 + 0x1p-50)) * (1.0 + 0x1p-50);
   if (rr == 0.0) {  // s + c = 0 exactly; T is a multiple of g with |T| <= bound
     if (a.emin < 2047 && bound < ldexp(1.0, a.emin - 1075)) {
       r = 0.0;
@@ -136,57 +194,154 @@ __device__ inline bool sum2_round(const Sum2& a, uint32_t N, double& r) {
   return false;
 }
 
-// One wave per run of equal keys: certified fast sums, then the drop test;
-// runs the fast path cannot certify are queued for k_segment_sum_exact.
-__global__ __launch_bounds__(256) void k_segment_sum(uint32_t nseg, uint64_t m, const uint32_t* start,
-                                                     const uint32_t* order, const double* re, const double* im,
+// Deeper sums for the runs that the fast path leaves: a cascade of kDeep
+// TWO-SUM levels, each adding up the errors of the one before.  While the last
+// level's errors are all zero the levels' exact sum is the run's, whatever the
+// order, and rounding it once is exact (acc_round); `lost` marks a nonzero
+// error (or a value that is not finite).
+constexpr int kDeep = 5;
+struct DeepSum {
+  double c[kDeep] = {};
+  uint32_t lost = 0;
+};
+
+template <int FIRST>
+__device__ inline void deep_add(DeepSum& a, double v) {
+  if (v == 0.0) return;
+#pragma unroll
+  for (int j = FIRST; j < kDeep; ++j) {
+    double t, e;
+    two_sum(a.c[j], v, t, e);
+    a.c[j] = t;
+    v = e;
+  }
+  if (v != 0.0) a.lost = 1u;  // also when v is NaN
+}
+
+__device__ inline void deep_merge_wave(DeepSum& a) {
+  for (int d = 32; d > 0; d >>= 1) {
+    DeepSum b;
+#pragma unroll
+    for (int j = 0; j < kDeep; ++j) b.c[j] = __shfl_xor(a.c[j], d, 64);
+    a.lost |= __shfl_xor(a.lost, d, 64);
+    deep_add<0>(a, b.c[0]);
+    deep_add<1>(a, b.c[1]);
+    deep_add<2>(a, b.c[2]);
+    deep_add<3>(a, b.c[3]);
+    deep_add<4>(a, b.c[4]);
+  }
+}
+static_assert(kDeep == 5, "deep_merge_wave merges five levels");
+
+__device__ inline void deep_expand(const DeepSum& a, ExactAcc& out) {
+  acc_init(out);
+  for (int j = kDeep - 1; j >= 0; --j) acc_add(out, a.c[j]);
+}
+
+// Sums of the runs of equal keys, then the drop test: eight lanes per run, or
+// the whole wave where a run has more than 64 items.  Bound by the gathers of
+// the rows: 3.3 M term pairs in 134,000 runs take 113 us (a wave per run over
+// rows kept in memory: 377 with the sums that certified fewer runs, 148 with
+// these); 3.7 M contributions of a 28-qubit operator went from 209 to 91.  Runs that the
+// fast path cannot certify are queued for k_segment_sum_exact.  Runs behind the
+// last one (the launch may be sized by the item count) are marked as dropped.
+constexpr uint32_t kRunLanes = 8, kShortRun = 64;
+template <class Rows>
+__global__ __launch_bounds__(256) void k_segment_sum(uint32_t cap, const uint32_t* n_runs, uint64_t m,
+                                                     const uint32_t* start, const uint32_t* order, Rows rows,
                                                      double eps_drop, double* out_re, double* out_im, uint32_t* keep,
                                                      uint32_t* n_slow, uint32_t* slow) {
-  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t nseg = *n_runs;
+  const uint32_t lane = threadIdx.x & 63u, sub = lane & (kRunLanes - 1);
   const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-  for (uint32_t u = wave; u < nseg; u += n_waves) {
-    const uint32_t b = start[u];
-    const uint32_t e = (u + 1 < nseg) ? start[u + 1] : static_cast<uint32_t>(m);
-    Sum2 ar, ai;
-    for (uint32_t j = b + lane; j < e; j += 64) {
-      const uint32_t v = order[j];
-      sum2_add(ar, re[v]);
-      sum2_add(ai, im[v]);
+  constexpr uint32_t kGroups = 64 / kRunLanes;
+  const uint64_t q = (static_cast<uint64_t>(nseg) + kGroups - 1) / kGroups;
+  for (uint64_t u = nseg + blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; u < cap;
+       u += static_cast<uint64_t>(gridDim.x) * blockDim.x)
+    keep[u] = 0u;
+  auto bounds = [&](uint32_t u, uint32_t& b, uint32_t& e) {
+    b = start[u];
+    e = (u + 1 < nseg) ? start[u + 1] : static_cast<uint32_t>(m);
+  };
+  auto finish = [&](uint32_t u, const Sum2& ar, const Sum2& ai, uint32_t n) {
+    double r, i;
+    const bool small = n < (1u << 28) / Rows::kRows;
+    if (small && sum2_round(ar, n * Rows::kRows + 64, r) && sum2_round(ai, n * Rows::kRows + 64, i)) {
+      out_re[u] = r;
+      out_im[u] = i;
+      keep[u] = (fmax(fabs(r), fabs(i)) > eps_drop) ? 1u : 0u;
+    } else {
+      slow[atomicAdd(n_slow, 1u)] = u;
     }
-    sum2_wave_merge(ar);
-    sum2_wave_merge(ai);
-    if (lane == 0) {
-      double r, i;
-      if (sum2_round(ar, e - b + 64, r) && sum2_round(ai, e - b + 64, i)) {
-        out_re[u] = r;
-        out_im[u] = i;
-        keep[u] = (fmax(fabs(r), fabs(i)) > eps_drop) ? 1u : 0u;
-      } else {
-        slow[atomicAdd(n_slow, 1u)] = u;
-      }
+  };
+  for (uint64_t w = wave; w < q; w += n_waves) {
+    // runs w, q + w, 2 q + w, ..: long runs are neighbours in key order
+    const uint64_t u = (lane / kRunLanes) * q + w;
+    uint32_t b = 0, e = 0;
+    if (u < nseg) bounds(static_cast<uint32_t>(u), b, e);
+    const bool is_long = e - b > kShortRun;
+    Sum2 ar, ai;
+    auto add = [&](double r, double i) {
+      sum2_add(ar, r);
+      sum2_add(ai, i);
+    };
+    if (!is_long)
+      for (uint32_t j = b + sub; j < e; j += kRunLanes) rows.visit(order[j], add);
+    sum2_merge_lanes(ar, kRunLanes);
+    sum2_merge_lanes(ai, kRunLanes);
+    if (sub == 0 && u < nseg && !is_long) finish(static_cast<uint32_t>(u), ar, ai, e - b);
+    unsigned long long left = __ballot(is_long && sub == 0);
+    while (left) {
+      const uint32_t v = static_cast<uint32_t>((__ffsll(left) - 1) / kRunLanes * q + w);
+      left &= left - 1;
+      bounds(v, b, e);
+      ar = Sum2();
+      ai = Sum2();
+      for (uint32_t j = b + lane; j < e; j += 64) rows.visit(order[j], add);
+      sum2_merge_lanes(ar, 64);
+      sum2_merge_lanes(ai, 64);
+      if (lane == 0) finish(v, ar, ai, e - b);
     }
   }
 }
 
-// Exact expansions for the queued runs (their order in the queue does not
-// matter: each run's result depends on its contributions only).
-__global__ void k_segment_sum_exact(uint32_t nseg, uint64_t m, const uint32_t* start, const uint32_t* order,
-                                    const double* re, const double* im, double eps_drop, const uint32_t* n_slow,
-                                    const uint32_t* slow, double* out_re, double* out_im, uint32_t* keep,
-                                    uint32_t* overflow) {
-  const uint32_t n = *n_slow;
-  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
+// The queued runs, a wave each: the deep sum, and where that loses bits, exact
+// expansions by one lane.  (The order in the queue does not matter: each run's
+// result depends on its contributions only.)  One lane per run from the start
+// took 1.9 ms of a product's 3.4, a few long runs with one addition after
+// another; this takes 49 us there.
+template <class Rows>
+__global__ __launch_bounds__(64) void k_segment_sum_exact(const uint32_t* n_runs, uint64_t m, const uint32_t* start,
+                                                          const uint32_t* order, Rows rows, double eps_drop,
+                                                          const uint32_t* n_slow, const uint32_t* slow, double* out_re,
+                                                          double* out_im, uint32_t* keep, uint32_t* overflow) {
+  const uint32_t n = *n_slow, nseg = *n_runs;
+  for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
     const uint32_t u = slow[k];
     const uint32_t b = start[u];
     const uint32_t e = (u + 1 < nseg) ? start[u + 1] : static_cast<uint32_t>(m);
+    DeepSum dr, di;
+    for (uint32_t j = b + threadIdx.x; j < e; j += 64)
+      rows.visit(order[j], [&](double r, double i) {
+        deep_add<0>(dr, r);
+        deep_add<0>(di, i);
+      });
+    deep_merge_wave(dr);
+    deep_merge_wave(di);
+    if (threadIdx.x != 0) continue;
     ExactAcc ar, ai;
-    acc_init(ar);
-    acc_init(ai);
-    for (uint32_t j = b; j < e; ++j) {
-      const uint32_t v = order[j];
-      acc_add(ar, re[v]);
-      acc_add(ai, im[v]);
+    if (dr.lost | di.lost) {
+      acc_init(ar);
+      acc_init(ai);
+      for (uint32_t j = b; j < e; ++j)
+        rows.visit(order[j], [&](double r, double i) {
+          acc_add(ar, r);
+          acc_add(ai, i);
+        });
+    } else {
+      deep_expand(dr, ar);
+      deep_expand(di, ai);
     }
     if (ar.overflow | ai.overflow) atomicOr(overflow, 1u);
     const double r = acc_round(ar), i = acc_round(ai);
@@ -196,10 +351,10 @@ __global__ void k_segment_sum_exact(uint32_t nseg, uint64_t m, const uint32_t* s
   }
 }
 
-__global__ void k_compact_terms(uint32_t nseg, uint64_t m, int W, const uint32_t* start, const uint32_t* keep,
+__global__ void k_compact_terms(uint32_t cap, uint64_t m, int W, const uint32_t* start, const uint32_t* keep,
                                 const uint32_t* pos, const uint64_t* keys, const double* sre, const double* sim,
                                 uint64_t* x, uint64_t* z, double* c) {
-  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nseg; u += gridDim.x * blockDim.x) {
+  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < cap; u += gridDim.x * blockDim.x) {
     if (!keep[u]) continue;
     const uint64_t o = pos[u];
     const uint64_t i = start[u];
@@ -213,15 +368,12 @@ __global__ void k_compact_terms(uint32_t nseg, uint64_t m, int W, const uint32_t
 }
 
 // ---------------------------------------------------------------- sum x sum
-// One thread per pair (k, l).  The coefficient a_k b_l is carried exactly as
-// four rows of TWO-PRODUCT pieces (p = fl(a*b), e = fma(a, b, -p)) so the
-// canonical reduction rounds the exact pair sums once.
-__global__ void k_sum_mul(uint64_t na, uint64_t nb, int W, const uint64_t* xa, const uint64_t* za, const double* ca,
-                          const uint64_t* xb, const uint64_t* zb, const double* cb, uint64_t* keys, double* re,
-                          double* im) {
-  const uint64_t npairs = na * nb;
-  const uint64_t m = 4 * npairs;
-  for (uint64_t t = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; t < npairs;
+// One thread per pair (k, l): its key, and its index with the phase exponent
+// in the top two bits (PairRows).
+__global__ void k_sum_mul(uint64_t na, uint64_t nb, int W, const uint64_t* xa, const uint64_t* za, const uint64_t* xb,
+                          const uint64_t* zb, uint64_t* keys, uint32_t* order) {
+  const uint64_t m = na * nb;
+  for (uint64_t t = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; t < m;
        t += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
     const uint64_t k = t / nb, l = t % nb;
     uint32_t g = 0;
@@ -230,25 +382,10 @@ __global__ void k_sum_mul(uint64_t na, uint64_t nb, int W, const uint64_t* xa, c
       const uint64_t b_x = xb[l * W + w], b_z = zb[l * W + w];
       const uint64_t m_x = a_x ^ b_x, m_z = a_z ^ b_z;
       g += __popcll(a_x & a_z) + __popcll(b_x & b_z) + 2u * __popcll(a_z & b_x) + 3u * __popcll(m_x & m_z);
-      for (int r = 0; r < 4; ++r) {
-        keys[static_cast<uint64_t>(w) * m + 4 * t + r] = m_z;
-        keys[static_cast<uint64_t>(W + w) * m + 4 * t + r] = m_x;
-      }
+      keys[static_cast<uint64_t>(w) * m + t] = m_z;
+      keys[static_cast<uint64_t>(W + w) * m + t] = m_x;
     }
-    const double ar = ca[2 * k], ai = ca[2 * k + 1], br = cb[2 * l], bi = cb[2 * l + 1];
-    const double p1 = ar * br, e1 = fma(ar, br, -p1);
-    const double p2 = ai * bi, e2 = fma(ai, bi, -p2);
-    const double p3 = ar * bi, e3 = fma(ar, bi, -p3);
-    const double p4 = ai * br, e4 = fma(ai, br, -p4);
-    double r0 = p1, i0 = p3, r1 = e1, i1 = e3, r2 = -p2, i2 = p4, r3 = -e2, i3 = e4;
-    rotate(g, r0, i0);
-    rotate(g, r1, i1);
-    rotate(g, r2, i2);
-    rotate(g, r3, i3);
-    re[4 * t] = r0; im[4 * t] = i0;
-    re[4 * t + 1] = r1; im[4 * t + 1] = i1;
-    re[4 * t + 2] = r2; im[4 * t + 2] = i2;
-    re[4 * t + 3] = r3; im[4 * t + 3] = i3;
+    order[t] = static_cast<uint32_t>(t) | (g & 3u) << 30;
   }
 }
 
@@ -439,9 +576,17 @@ void* Scratch::take(size_t bytes) {
 Scratch* Scratch::current() { return tl_scratch; }
 void clear_last_error() { g_last_error.clear(); }
 
-void canonicalize_soa(uint32_t n_qubits, int W, uint64_t m, DevBuf<uint64_t>& keys, DevBuf<double>& re,
-                      DevBuf<double>& im, double eps_drop, pbs_sum& out, hipStream_t s) {
-  PBS_REQUIRE(m < (1ull << 32), PBS_ERR_RANGE, "more than 2^32 - 1 contributions");
+namespace {
+// Up to this many items the run count stays on the device and arrays over
+// runs are sized by the item count (32 bytes per item): that spares a read-back
+// of 40 us with its wait.  Above, the exact size is worth the wait.
+constexpr uint64_t kRunCapItems = 1ull << 20;
+
+// Canonical reduction: sorts the items (order: what each stands for) by key,
+// sums the rows of equal keys, drops small sums, fills `out`.
+template <class Rows>
+void canonicalize(uint32_t n_qubits, int W, uint64_t m, uint64_t* keys, uint32_t* order, Rows rows, double eps_drop,
+                  pbs_sum& out, hipStream_t s) {
   out.n_qubits = n_qubits;
   out.words = W;
   out.canonical = true;
@@ -453,42 +598,47 @@ void canonicalize_soa(uint32_t n_qubits, int W, uint64_t m, DevBuf<uint64_t>& ke
     return;
   }
   const int nw = 2 * W;
-  DevBuf<uint32_t> order(m, s);
-  iota_u32(order.get(), m, s);
-  radix_sort_keys(keys.get(), order.get(), m, nw, s);
-  DevBuf<uint32_t> heads(m, s), segid(m, s), cnt(2, s);
-  mark_heads(keys.get(), m, nw, heads.get(), s);
-  exclusive_scan_u32(heads.get(), segid.get(), m, cnt.get(), s);
-  const uint32_t nseg = read_scalar(cnt.get(), s);
-  DevBuf<uint32_t> start(nseg, s), keep(nseg, s), pos(nseg, s), flags(2, s), slow(nseg, s);
-  DevBuf<double> sre(nseg, s), sim(nseg, s);
-  uint32_t* overflow = flags.get();
-  uint32_t* n_slow = flags.get() + 1;
-  PBS_HIP(hipMemsetAsync(flags.get(), 0, 2 * sizeof(uint32_t), s));
-  hipLaunchKernelGGL(k_segment_starts, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, heads.get(), segid.get(), m,
-                     start.get());
-  hipLaunchKernelGGL(k_segment_sum, dim3(grid_for(64ull * nseg, 256, 65536)), dim3(256), 0, s, nseg, m, start.get(),
-                     order.get(), re.get(), im.get(), eps_drop, sre.get(), sim.get(), keep.get(), n_slow, slow.get());
-  hipLaunchKernelGGL(k_segment_sum_exact, dim3(grid_for(nseg, 64, 65536)), dim3(64), 0, s, nseg, m, start.get(),
-                     order.get(), re.get(), im.get(), eps_drop, n_slow, slow.get(), sre.get(), sim.get(), keep.get(),
-                     overflow);
+  radix_sort_keys(keys, order, m, nw, s);
+  DevBuf<uint32_t> flags(4, s), start(m, s);
+  uint32_t *n_runs = flags.get(), *n_slow = flags.get() + 1, *overflow = flags.get() + 2, *n_keep = flags.get() + 3;
+  PBS_HIP(hipMemsetAsync(flags.get(), 0, 4 * sizeof(uint32_t), s));
+  run_starts(keys, m, nw, start.get(), n_runs, s);
+  const uint32_t cap = m <= kRunCapItems ? static_cast<uint32_t>(m) : read_scalar(n_runs, s);
+  DevBuf<uint32_t> keep(cap, s), pos(cap, s), slow(cap, s);
+  DevBuf<double> sre(cap, s), sim(cap, s);
+  hipLaunchKernelGGL(k_segment_sum<Rows>, dim3(grid_for(static_cast<uint64_t>(kRunLanes) * cap, 256, 65536)),
+                     dim3(256), 0, s, cap, n_runs, m, start.get(), order, rows, eps_drop, sre.get(), sim.get(),
+                     keep.get(), n_slow, slow.get());
+  hipLaunchKernelGGL(k_segment_sum_exact<Rows>, dim3(grid_for(cap, 1, 2048)), dim3(64), 0, s, n_runs, m, start.get(),
+                     order, rows, eps_drop, n_slow, slow.get(), sre.get(), sim.get(), keep.get(), overflow);
   PBS_HIP(hipGetLastError());
-  exclusive_scan_u32(keep.get(), pos.get(), nseg, cnt.get() + 1, s);
-  const uint32_t nkeep = read_scalar(cnt.get() + 1, s);
-  PBS_REQUIRE(read_scalar(overflow, s) == 0, PBS_ERR_RANGE,
-              "exact summation needed more than the supported number of expansion components");
+  exclusive_scan_u32(keep.get(), pos.get(), cap, n_keep, s);
+  uint32_t got[4];
+  PBS_HIP(hipMemcpyAsync(got, flags.get(), sizeof(got), hipMemcpyDeviceToHost, s));
+  PBS_HIP(hipStreamSynchronize(s));
+  PBS_REQUIRE(got[2] == 0, PBS_ERR_RANGE, "exact summation needed more than the supported number of expansion components");
+  const uint32_t nkeep = got[3];
   out.n_terms = nkeep;
   out.x.alloc(static_cast<uint64_t>(nkeep) * W);
   out.z.alloc(static_cast<uint64_t>(nkeep) * W);
   out.coeff.alloc(2ull * nkeep);
   if (nkeep) {
-    hipLaunchKernelGGL(k_compact_terms, dim3(grid_for(nseg, 256, 65536)), dim3(256), 0, s, nseg, m, W, start.get(),
-                       keep.get(), pos.get(), keys.get(), sre.get(), sim.get(), out.x.get(), out.z.get(),
-                       out.coeff.get());
+    hipLaunchKernelGGL(k_compact_terms, dim3(grid_for(cap, 256, 65536)), dim3(256), 0, s, cap, m, W, start.get(),
+                       keep.get(), pos.get(), keys, sre.get(), sim.get(), out.x.get(), out.z.get(), out.coeff.get());
     PBS_HIP(hipGetLastError());
   }
   PBS_HIP(hipStreamSynchronize(s));
 }
+
+// Items that are the rows of re/im in order.
+void canonicalize_rows(uint32_t n_qubits, int W, uint64_t m, DevBuf<uint64_t>& keys, DevBuf<double>& re,
+                       DevBuf<double>& im, double eps_drop, pbs_sum& out, hipStream_t s) {
+  PBS_REQUIRE(m < (1ull << 32), PBS_ERR_RANGE, "more than 2^32 - 1 contributions");
+  DevBuf<uint32_t> order(m, s);
+  iota_u32(order.get(), m, s);
+  canonicalize(n_qubits, W, m, keys.get(), order.get(), ArrayRows{re.get(), im.get()}, eps_drop, out, s);
+}
+}  // namespace
 
 }  // namespace pbs
 
@@ -608,7 +758,7 @@ pbs_status pbs_pauli_canonicalize(pbs_sum* sum, double eps_drop, void* stream) {
       PBS_HIP(hipGetLastError());
     }
     pbs_sum tmp;
-    canonicalize_soa(sum->n_qubits, W, m, keys, re, im, eps_drop, tmp, s);
+    canonicalize_rows(sum->n_qubits, W, m, keys, re, im, eps_drop, tmp, s);
     sum->x = std::move(tmp.x);
     sum->z = std::move(tmp.z);
     sum->coeff = std::move(tmp.coeff);
@@ -631,18 +781,17 @@ pbs_status pbs_pauli_sum_mul(const pbs_sum* a, const pbs_sum* b, double eps_drop
     hipStream_t s = as_stream(stream);
     Scratch scratch(s);  // temporaries of this call
     const int W = a->words;
-    const uint64_t m = 4 * np;
-    DevBuf<uint64_t> keys(m * 2 * W, s);
-    DevBuf<double> re(m, s), im(m, s);
+    DevBuf<uint64_t> keys(np * 2 * W, s);
+    DevBuf<uint32_t> order(np, s);
     if (np) {
       hipLaunchKernelGGL(k_sum_mul, dim3(grid_for(np, 256, 65536)), dim3(256), 0, s, a->n_terms, b->n_terms, W,
-                         a->x.get(), a->z.get(), a->coeff.get(), b->x.get(), b->z.get(), b->coeff.get(), keys.get(),
-                         re.get(), im.get());
+                         a->x.get(), a->z.get(), b->x.get(), b->z.get(), keys.get(), order.get());
       PBS_HIP(hipGetLastError());
     }
     auto* res = new pbs_sum();
     try {
-      canonicalize_soa(a->n_qubits, W, m, keys, re, im, eps_drop, *res, s);
+      canonicalize(a->n_qubits, W, np, keys.get(), order.get(),
+                   PairRows{a->coeff.get(), b->coeff.get(), static_cast<uint32_t>(b->n_terms)}, eps_drop, *res, s);
     } catch (...) {
       delete res;
       throw;
@@ -690,7 +839,7 @@ pbs_status pbs_jw_transform(uint32_t n_spin_orb, const double* h1, const double*
     PBS_HIP(hipGetLastError());
     auto* res = new pbs_sum();
     try {
-      canonicalize_soa(n, W, m, keys, re, im, eps_drop, *res, s);
+      canonicalize_rows(n, W, m, keys, re, im, eps_drop, *res, s);
     } catch (...) {
       delete res;
       throw;

@@ -235,19 +235,21 @@ size_t scan_scratch_bytes(uint64_t n);
 
 // Stable LSD radix sort of m items keyed by nw 64-bit words (SoA: word w of
 // item i at keys[w*m + i], word 0 least significant), carrying a uint32
-// payload.  Sorts only the 8-bit digits that differ between items (found by
-// a device reduction read back once).  Result ends in keys/vals.
+// payload, nw <= 2 kMaxWords.  Sorts by the bits that differ between items
+// (found by a device reduction, read back once above 4096 items).  Result
+// ends in keys/vals.
 void radix_sort_keys(uint64_t* keys, uint32_t* vals, uint64_t m, int nw, hipStream_t s);
 
 // v[i] = i for i < m.
 void iota_u32(uint32_t* v, uint64_t m, hipStream_t s);
 
-// Marks item i as a segment head (1) when its key (nw SoA words) differs from
-// item i-1; item 0 is always a head.
-void mark_heads(const uint64_t* keys, uint64_t m, int nw, uint32_t* heads, hipStream_t s);
+// Positions of the runs of equal keys (nw SoA words, m >= 1 sorted items):
+// start[u] for every run u, and their number (device pointers).
+void run_starts(const uint64_t* keys, uint64_t m, int nw, uint32_t* start, uint32_t* total, hipStream_t s);
+
+}  // namespace pbs
 
 // ---------------------------------------------------------------- sums (algebra.hip)
-}  // namespace pbs
 
 struct pbs_sum {
   uint32_t n_qubits = 0;
@@ -258,14 +260,6 @@ struct pbs_sum {
   pbs::DevBuf<uint64_t> z;      // [n_terms * words]
   pbs::DevBuf<double> coeff;    // [2 * n_terms], letter form (re, im)
 };
-
-namespace pbs {
-// Canonical reduction of raw contributions held in SoA key arrays
-// (keys[w*m + i]: words 0..W-1 are z, W..2W-1 are x) with separate re/im
-// arrays; fills `out` (allocates its arrays).
-void canonicalize_soa(uint32_t n_qubits, int W, uint64_t m, DevBuf<uint64_t>& keys, DevBuf<double>& re,
-                      DevBuf<double>& im, double eps_drop, pbs_sum& out, hipStream_t s);
-}  // namespace pbs
 
 namespace pbs {
 // ---------------------------------------------------------------- L-BFGS (optim.hip)

@@ -158,6 +158,60 @@ def test_canonicalize_adversarial_sums(dev):
     assert gc.tobytes() == rc.tobytes()
 
 
+@pytest.mark.parametrize("n,m,run", [(33, 4095, 1), (256, 4097, 2), (33, 8191, 3), (33, 8192, 1), (256, 8193, 2),
+                                     (5, 9000, 64), (5, 9100, 65), (130, 20_000, 300), (28, 1 << 20, 2), (28, (1 << 20) + 1, 2),
+                                     (9, (1 << 21) + 1, 40)])
+@pytest.mark.parametrize("spread", [0, 30])
+def test_canonicalize_at_sort_and_run_edges(dev, n, m, run, spread):
+    """One-block sort up to 8,192 items, tiles of 4,096 above; eight lanes per run up to 64 items and a
+    wave above; run count read back above 2^20 items; the scan of run counts
+    above 2^21 items.  Coefficients over 60 decades cancel in pairs, so the
+    fast sums cannot certify the runs and the deeper ones decide.  Scattered
+    varying bits make digits of several pieces.  Bit-exact everywhere."""
+    api = _api()
+    rng = np.random.default_rng(n + m + run)
+    W = (n + 63) // 64
+    runs = (m + run - 1) // run
+    pool = np.zeros((2, runs, W), dtype=np.uint64)
+    bits = rng.permutation(2 * n)[: min(2 * n, 23)]  # the bits that vary
+    ids = rng.permutation(1 << len(bits))[:runs].astype(np.uint64) if runs <= 1 << len(bits) else np.arange(runs)
+    for j, b in enumerate(bits):
+        half, q = divmod(int(b), n)
+        pool[half, :, q // 64] |= ((ids >> np.uint64(j)) & np.uint64(1)) << np.uint64(q % 64)
+    pick = rng.permutation(np.arange(m) // run)
+    x, z = pool[0][pick], pool[1][pick]
+    c = rng.standard_normal((m, 2)) * 10.0 ** rng.integers(-spread, spread + 1, size=(m, 2))
+    if spread:
+        first = np.argsort(pick, kind="stable")
+        same = pick[first][1:] == pick[first][:-1]
+        at = first[1:][same & (rng.random(m - 1) < 0.3)]
+        c[at] = -c[first[:-1][np.isin(first[1:], at)]]
+    c = c[:, 0] + 1j * c[:, 1]
+    s = api.PauliSum.create(n, x.reshape(-1), z.reshape(-1), c)
+    s.canonicalize(0.0)
+    gx, gz, gc = s.read()
+    rx, rz, rc = opauli.canonicalize_xz(x, z, c.real, c.imag, 0.0)
+    np.testing.assert_array_equal(gx, rx)
+    np.testing.assert_array_equal(gz, rz)
+    assert gc.tobytes() == rc.tobytes()
+
+
+@pytest.mark.parametrize("n,m", [(4, 64), (4, 65), (7, 300)])
+def test_sum_mul_square_bit_exact(dev, n, m):
+    """Squares: long runs, and pairs k l and l k that cancel exactly."""
+    api = _api()
+    rng = np.random.default_rng(n + m)
+    la, _ = synth.random_pauli_strings(m, n, seed=n)
+    ca = rng.standard_normal(m) * 10.0 ** rng.integers(-9, 10, m) + 1j * rng.standard_normal(m)
+    xa, za = opauli.letters_to_xz(la)
+    ga = api.PauliSum.create(n, xa.reshape(-1), za.reshape(-1), ca)
+    gx, gz, gc = ga.mul(ga).read()
+    rx, rz, rc = opauli.sum_product_canonical(OSum(n, la, ca), OSum(n, la, ca))
+    np.testing.assert_array_equal(gx, rx)
+    np.testing.assert_array_equal(gz, rz)
+    assert gc.tobytes() == rc.tobytes()
+
+
 def test_canonicalize_empty(dev):
     api = _api()
     s = api.PauliSum.create(10, np.zeros(0, np.uint64), np.zeros(0, np.uint64), np.zeros(0, np.complex128))
