@@ -19,7 +19,9 @@ __global__ __launch_bounds__(kBlock) void k_apply_full(uint64_t dim, uint32_t n_
                                                        const uint32_t* __restrict__ off,
                                                        const uint64_t* __restrict__ zk,
                                                        const double2* __restrict__ ck, const T* __restrict__ psi,
-                                                       T* __restrict__ out, double* __restrict__ partial) {
+                                                       T* __restrict__ out, double* __restrict__ partial,
+                                                       const uint32_t* skip) {
+  if (skip && *skip) return;
   double e_re = 0.0, e_im = 0.0, nrm = 0.0;
   for (uint64_t t = blockIdx.x * static_cast<uint64_t>(kBlock) + threadIdx.x; t < dim;
        t += static_cast<uint64_t>(gridDim.x) * kBlock) {
@@ -385,17 +387,17 @@ bool plan_panel(const pbs_grouped& h, const pbs_space& sp, const FactorPlan* A, 
 // Launches the apply (EXPVAL: with the energy partials) for target alpha
 // rows [row_begin, row_end) of a sector space (the whole space by default);
 // out holds those rows only, from row_begin's first column.  Returns the
-// number of energy partials written.
+// number of energy partials written.  skip: see SectorArgs::skip.
 template <class T, bool EXPVAL>
 uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void* out, double* partial,
-                hipStream_t s, uint64_t row_begin = 0, uint64_t row_end = ~0ull) {
+                hipStream_t s, uint64_t row_begin = 0, uint64_t row_end = ~0ull, const uint32_t* skip = nullptr) {
   const T* p = static_cast<const T*>(psi);
   T* o = static_cast<T*>(out);
   if (!sp.sector) {
     const dim3 grid(grid_for(sp.dim, kBlock, kFullGridCap));
     hipLaunchKernelGGL((k_apply_full<T, EXPVAL>), grid, dim3(kBlock), 0, s, sp.dim,
                        static_cast<uint32_t>(h.n_groups), h.xg.get(), h.off.get(), h.zk.get(),
-                       reinterpret_cast<const double2*>(h.ck.get()), p, o, partial);
+                       reinterpret_cast<const double2*>(h.ck.get()), p, o, partial, skip);
   } else {
     SectorArgs a;
     bool r16 = false;
@@ -405,6 +407,7 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     const uint64_t rows = row_end - row_begin;
     if (rows == 0) return 0;
     a.row_begin = static_cast<uint32_t>(row_begin);
+    a.skip = skip;
     // the kernels store target t = row * dim_beta + column at out[t]: shift
     // the base so that row_begin's first column lands at out[0]
     if (o) o = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(o) - row_begin * sp.dim_beta * sizeof(T));
@@ -413,6 +416,7 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     if (plan_panel(h, sp, h.fplan.get(), h.fplan.get(), &pa, &ps)) {
       pa.row_begin = static_cast<uint32_t>(row_begin);
       pa.row_end = static_cast<uint32_t>(row_end);
+      pa.skip = skip;
       // the blocks that hold rows row_begin and row_end - 1
       auto block_of = [&](uint64_t row) { return static_cast<uint32_t>(((row + 1) * pa.n_blk - 1) / pa.dim_alpha); };
       pa.blk0 = block_of(row_begin);
@@ -447,13 +451,13 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
 
 }  // namespace
 
-void apply_launch(const pbs_grouped& h, const pbs_space& sp, pbs_dtype dt, const void* psi, void* out,
-                  hipStream_t s) {
+void apply_launch(const pbs_grouped& h, const pbs_space& sp, pbs_dtype dt, const void* psi, void* out, hipStream_t s,
+                  const uint32_t* skip) {
   validate(&h, &sp, dt);
   if (dt == PBS_C128)
-    launch<double2, false>(h, sp, psi, out, nullptr, s);
+    launch<double2, false>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
   else
-    launch<float2, false>(h, sp, psi, out, nullptr, s);
+    launch<float2, false>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
 }
 
 }  // namespace pbs

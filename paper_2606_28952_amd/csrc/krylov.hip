@@ -9,7 +9,12 @@
 // all basis vectors (two multi-axpy sweeps: the first subtracts the
 // recurrence terms and returns the projections, the second subtracts those
 // and returns the norm), and a scale.  Inner products accumulate in float64 with a fixed-order two-stage
-// reduction (deterministic).  The k x k tridiagonal matrix (k <= 16) is
+// reduction (deterministic).  Norms, alpha, beta and the coefficients of the
+// sweeps stay on the device (LanczosState), so all m vectors are queued
+// without a wait: at 24 qubits in double precision (0.85 M amplitudes, m = 12)
+// the 37 round trips to the host took 1.1 ms of a 3.06 ms step.  A run that
+// ends early (zero norm, breakdown) sets a flag that turns the queued kernels
+// into empty ones.  The k x k tridiagonal matrix (k <= 16) is
 // diagonalised on the host by cyclic Jacobi rotations and exp(-i T dt) e_1
 // combines the basis vectors on the device.
 #include <cmath>
@@ -17,8 +22,9 @@
 #include "handles.h"
 
 namespace pbs {
-// the apply launcher lives in apply.hip
-void apply_launch(const pbs_grouped& h, const pbs_space& sp, pbs_dtype dt, const void* psi, void* out, hipStream_t s);
+// the apply launcher lives in apply.hip; nothing is done when *skip is not zero
+void apply_launch(const pbs_grouped& h, const pbs_space& sp, pbs_dtype dt, const void* psi, void* out, hipStream_t s,
+                  const uint32_t* skip);
 
 namespace {
 
@@ -54,8 +60,24 @@ struct Coeffs {
   double im[kMaxK];
 };
 
+// What a step keeps on the device between its kernels.
+struct LanczosState {
+  Coeffs c;                           // coefficients of the next sweep
+  double alpha[kMaxK], beta[kMaxK];
+  double nrm, scale, last_b, inv;     // |psi|; largest |alpha|, b so far; last b; 1 / (norm to divide by)
+  uint32_t k, done;                   // vectors so far; the run has ended
+};
+
+// Blocks of the kernels that end in a reduction.  Each thread sums several
+// elements before its block reduces (24 sums by shuffles at 12 vectors).  A
+// step of 12 vectors of 0.85 M double-precision amplitudes takes 2520 us with an
+// element per thread (3336 blocks), 2166 with 2048 blocks, 1984 with 1024, 1881
+// with 512 and 1829 with 256; 512 keep enough loads in flight for the
+// single-vector sums of large states.
+constexpr unsigned kDotGrid = 512;
+
 // Block partials of ND complex sums held by every thread (ar, ai):
-// partial[b * 2 * ND + 2i + {0,1}], wave shuffles then a fixed-order sum over
+// partial[(2i + {0,1}) * blocks + b], wave shuffles then a fixed-order sum over
 // the block's waves.
 template <int ND>
 __device__ inline void block_partials(const double (&ar)[ND], const double (&ai)[ND], double* __restrict__ partial) {
@@ -77,16 +99,18 @@ __device__ inline void block_partials(const double (&ar)[ND], const double (&ai)
   if (threadIdx.x < 2 * ND) {
     double s = 0.0;
     for (int w = 0; w < kKB / 64; ++w) s += red[threadIdx.x][w];
-    partial[static_cast<uint64_t>(blockIdx.x) * 2 * ND + threadIdx.x] = s;
+    partial[static_cast<uint64_t>(threadIdx.x) * gridDim.x + blockIdx.x] = s;
   }
 }
 
-// partial[b * 2 * NV + 2i + {0,1}] = sum over block b's elements of conj(x_i) * y.
+// Block partials (2i, 2i + 1) of conj(x_i) * y.
 // The vector count is a template argument so that the kernel holds exactly
 // NV accumulator pairs (registers, hence resident waves, follow NV).
 template <class T, int NV>
 __global__ __launch_bounds__(kKB) void k_multidot(uint64_t n, const T* __restrict__ xbase, uint64_t stride,
-                                                  const T* __restrict__ y, double* __restrict__ partial) {
+                                                  const T* __restrict__ y, double* __restrict__ partial,
+                                                  const uint32_t* done) {
+  if (done && *done) return;
   double ar[NV], ai[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) ar[i] = ai[i] = 0.0;
@@ -103,20 +127,68 @@ __global__ __launch_bounds__(kKB) void k_multidot(uint64_t n, const T* __restric
   block_partials<NV>(ar, ai, partial);
 }
 
-// out[j] = sum over blocks of partial[b * nvals + j], fixed order.
-__global__ __launch_bounds__(kKB) void k_sum_partials(const double* partial, int nblocks, int nvals, double* out) {
-  __shared__ double red[kKB];
-  for (int j = 0; j < nvals; ++j) {
+// What the sums of block partials update in the state.
+enum : int { kSumNorm = 0, kSumAlpha = 1, kSumProject = 2, kSumBeta = 3 };
+
+// Value v = sum over blocks of partial[v * nblocks + b] in a fixed order (a
+// wave per value), then thread 0 turns the values into the state's next
+// entries.  One wave per value, where one block that took the values in turn
+// needed 66 us for 24 values of 3336 blocks; this takes 5 (of 512 blocks).
+constexpr int kSumBlock = 1024;
+template <int MODE>
+__global__ __launch_bounds__(kSumBlock) void k_sum_partials(const double* partial, int nblocks, int nvals, uint32_t j,
+                                                            LanczosState* st) {
+  if (MODE != kSumNorm && st->done) return;
+  __shared__ double val[2 * kMaxK];
+  const int lane = threadIdx.x & 63;
+  for (int v = threadIdx.x >> 6; v < nvals; v += kSumBlock / 64) {
     double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += kKB) s += partial[static_cast<uint64_t>(b) * nvals + j];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = kKB / 2; h > 0; h >>= 1) {
-      if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-      __syncthreads();
+    for (int b = lane; b < nblocks; b += 64) s += partial[static_cast<uint64_t>(v) * nblocks + b];
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    if (lane == 0) val[v] = s;
+  }
+  __syncthreads();
+  if (MODE == kSumAlpha || MODE == kSumProject) {
+    // sweep coefficients: the recurrence terms, or minus the projections
+    const uint32_t i = threadIdx.x;
+    if (i <= j) {
+      double re = 0.0, im = 0.0;
+      if (MODE == kSumProject || i == j) {
+        const uint32_t at = MODE == kSumProject ? i : 0u;
+        re = -val[2 * at];
+        im = -val[2 * at + 1];
+      } else if (i + 1 == j) {
+        re = -st->beta[i];
+      }
+      st->c.re[i] = re;
+      st->c.im[i] = im;
     }
-    if (threadIdx.x == 0) out[j] = red[0];
-    __syncthreads();
+    if (MODE == kSumAlpha && i == 0) st->alpha[j] = val[0];
+    return;
+  }
+  if (threadIdx.x != 0) return;
+  if (MODE == kSumNorm) {
+    const double nrm = sqrt(val[0]);
+    st->nrm = nrm;
+    st->inv = 1.0 / nrm;
+    st->scale = 0.0;
+    st->last_b = 0.0;
+    st->k = 0;
+    st->done = nrm > 0.0 ? 0u : 1u;
+    return;
+  }
+  const double b = sqrt(val[0] < 0.0 ? 0.0 : val[0]);
+  const double a = fabs(st->alpha[j]);
+  const double big = a < b ? b : a;  // a where b is NaN
+  const double scale = st->scale < big ? big : st->scale;
+  st->scale = scale;
+  st->last_b = b;
+  st->k = j + 1;
+  if (b <= 1e-14 * scale) {
+    st->done = 1u;
+  } else {
+    st->beta[j] = b;
+    st->inv = 1.0 / b;
   }
 }
 
@@ -154,7 +226,10 @@ __global__ __launch_bounds__(kKB) void k_multiaxpy(uint64_t n, int nv, const T* 
 // written once.
 template <class T, bool NORM, int NV>
 __global__ __launch_bounds__(kKB) void k_multiaxpy_dot(uint64_t n, const T* __restrict__ xbase, uint64_t stride,
-                                                       Coeffs c, T* __restrict__ y, double* __restrict__ partial) {
+                                                       const LanczosState* __restrict__ st, T* __restrict__ y,
+                                                       double* __restrict__ partial) {
+  if (st->done) return;
+  const Coeffs& c = st->c;
   constexpr int kD = NORM ? 1 : NV;
   double ar[kD], ai[kD];
 #pragma unroll
@@ -214,8 +289,12 @@ struct AxpyDotK {
   };
 };
 
+// y <- x / (norm in the state)
 template <class T>
-__global__ __launch_bounds__(kKB) void k_scale_copy(uint64_t n, const T* __restrict__ x, double s, T* __restrict__ y) {
+__global__ __launch_bounds__(kKB) void k_scale_copy(uint64_t n, const T* __restrict__ x,
+                                                    const LanczosState* __restrict__ st, T* __restrict__ y) {
+  if (st->done) return;
+  const double s = st->inv;
   for (uint64_t t = blockIdx.x * static_cast<uint64_t>(kKB) + threadIdx.x; t < n;
        t += static_cast<uint64_t>(gridDim.x) * kKB) {
     const double2 v = KAmp<T>::ld(x, t);
@@ -265,7 +344,9 @@ void jacobi_eigen(int k, std::vector<double>& a, std::vector<double>& u) {
 
 size_t elem_size(pbs_dtype dt) { return dt == PBS_C128 ? 16 : 8; }
 
+// block partials (kDotGrid of them are used), then the state
 size_t partial_doubles() { return static_cast<size_t>(kKGrid) * 2 * kMaxK; }
+static_assert((kKGrid - kDotGrid) * 2 * kMaxK * sizeof(double) >= sizeof(LanczosState), "the state follows the partials");
 
 uint64_t workspace_bytes(const pbs_space& sp, pbs_dtype dt, uint32_t m) {
   const uint64_t vec = sp.dim * elem_size(dt);
@@ -281,36 +362,25 @@ class Lanczos {
     V_ = reinterpret_cast<T*>(work);
     W_ = reinterpret_cast<T*>(work + m * stride_);
     partial_ = reinterpret_cast<double*>(work + (m + 1) * stride_);
-    dots_ = partial_ + partial_doubles();
+    st_ = reinterpret_cast<LanczosState*>(partial_ + static_cast<size_t>(kDotGrid) * 2 * kMaxK);
     grid_ = grid_for(n_, kKB, kKGrid);
+    dot_grid_ = grid_for(n_, kKB, kDotGrid);
   }
   T* vec(uint32_t i) const { return reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(V_) + i * stride_); }
   uint64_t stride_elems() const { return stride_ / sizeof(T); }
 
-  // returns sum_i conj(x_i) y for x_0..x_{nv-1} starting at xbase
-  void dots(const T* xbase, int nv, const T* y, double* host) {
-    launch_nv<DotK<T>::template K>(nv, dim3(grid_), s_, n_, xbase, stride_elems(), y, partial_);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kKB), 0, s_, partial_, static_cast<int>(grid_), 2 * nv, dots_);
+  // sums the partials of the last kernel into the state
+  template <int MODE>
+  void sum(int nvals, uint32_t j) {
+    hipLaunchKernelGGL(k_sum_partials<MODE>, dim3(1), dim3(kSumBlock), 0, s_, partial_, static_cast<int>(dot_grid_),
+                       nvals, j, st_);
     PBS_HIP(hipGetLastError());
-    PBS_HIP(hipMemcpyAsync(host, dots_, 2 * nv * sizeof(double), hipMemcpyDeviceToHost, s_));
-    PBS_HIP(hipStreamSynchronize(s_));
   }
-  // y <- y + sum_i c_i x_i, then (host) sum_i conj(x_i) y, or |y|^2 with norm
-  void axpy_dots(const T* xbase, int nv, const double* cre, const double* cim, T* y, bool norm, double* host) {
-    Coeffs c{};
-    for (int i = 0; i < nv; ++i) {
-      c.re[i] = cre[i];
-      c.im[i] = cim[i];
-    }
-    if (norm)
-      launch_nv<AxpyDotK<T, true>::template K>(nv, dim3(grid_), s_, n_, xbase, stride_elems(), c, y, partial_);
-    else
-      launch_nv<AxpyDotK<T, false>::template K>(nv, dim3(grid_), s_, n_, xbase, stride_elems(), c, y, partial_);
-    const int nd = norm ? 1 : nv;
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kKB), 0, s_, partial_, static_cast<int>(grid_), 2 * nd, dots_);
-    PBS_HIP(hipGetLastError());
-    PBS_HIP(hipMemcpyAsync(host, dots_, 2 * nd * sizeof(double), hipMemcpyDeviceToHost, s_));
-    PBS_HIP(hipStreamSynchronize(s_));
+  // y <- y + sum_i c_i x_i with the state's coefficients, then the partials of
+  // sum_i conj(x_i) y, or of |y|^2
+  template <bool NORM>
+  void sweep(int nv, T* y) {
+    launch_nv<AxpyDotK<T, NORM>::template K>(nv, dim3(dot_grid_), s_, n_, vec(0), stride_elems(), st_, y, partial_);
   }
   void axpy(const T* xbase, int nv, const double* cre, const double* cim, double y_scale, T* y) {
     Coeffs c{};
@@ -323,9 +393,30 @@ class Lanczos {
   }
 
   void step(T* psi, double dt, double* info) {
-    double d[2 * kMaxK];
-    dots(psi, 1, psi, d);
-    const double nrm = std::sqrt(d[0]);
+    launch_nv<DotK<T>::template K>(1, dim3(dot_grid_), s_, n_, psi, stride_elems(), psi, partial_,
+                                   static_cast<const uint32_t*>(nullptr));
+    sum<kSumNorm>(2, 0);
+    hipLaunchKernelGGL((k_scale_copy<T>), dim3(grid_), dim3(kKB), 0, s_, n_, psi, st_, vec(0));
+    PBS_HIP(hipGetLastError());
+    for (uint32_t j = 0; j < m_; ++j) {
+      apply_launch(h_, sp_, dt_, vec(j), W_, s_, &st_->done);
+      // the three-term recurrence: alpha_j = <v_j, w> on the fresh product
+      // (H is Hermitian, so w has no other component in exact arithmetic)
+      launch_nv<DotK<T>::template K>(1, dim3(dot_grid_), s_, n_, vec(j), stride_elems(), W_, partial_, &st_->done);
+      sum<kSumAlpha>(2, j);
+      // subtract alpha_j v_j + beta_{j-1} v_{j-1}, and in the same sweep the
+      // projections on every basis vector (full re-orthogonalisation)
+      sweep<false>(static_cast<int>(j + 1), W_);
+      sum<kSumProject>(2 * static_cast<int>(j + 1), j);
+      // subtract those, and in the same sweep |w|^2
+      sweep<true>(static_cast<int>(j + 1), W_);
+      sum<kSumBeta>(2, j);
+      if (j + 1 == m_) break;
+      hipLaunchKernelGGL((k_scale_copy<T>), dim3(grid_), dim3(kKB), 0, s_, n_, W_, st_, vec(j + 1));
+      PBS_HIP(hipGetLastError());
+    }
+    const LanczosState st = read_scalar(st_, s_);
+    const double nrm = st.nrm;
     info[0] = nrm;
     if (!(nrm > 0.0)) {
       info[1] = 0.0;
@@ -333,39 +424,8 @@ class Lanczos {
       info[3] = 0.0;
       return;
     }
-    hipLaunchKernelGGL((k_scale_copy<T>), dim3(grid_), dim3(kKB), 0, s_, n_, psi, 1.0 / nrm, vec(0));
-    PBS_HIP(hipGetLastError());
-    std::vector<double> alpha, beta;
-    double scale = 0.0, last_b = 0.0;
-    uint32_t k = 0;
-    for (uint32_t j = 0; j < m_; ++j) {
-      apply_launch(h_, sp_, dt_, vec(j), W_, s_);
-      // the three-term recurrence: alpha_j = <v_j, w> on the fresh product
-      // (H is Hermitian, so w has no other component in exact arithmetic)
-      dots(vec(j), 1, W_, d);
-      alpha.push_back(d[0]);
-      double nre[kMaxK] = {}, nim[kMaxK] = {};
-      nre[j] = -d[0];
-      nim[j] = -d[1];
-      if (j > 0) nre[j - 1] = -beta[j - 1];
-      // subtract alpha_j v_j + beta_{j-1} v_{j-1}, and in the same sweep the
-      // projections on every basis vector (full re-orthogonalisation)
-      axpy_dots(vec(0), static_cast<int>(j + 1), nre, nim, W_, false, d);
-      for (uint32_t i = 0; i <= j; ++i) {
-        nre[i] = -d[2 * i];
-        nim[i] = -d[2 * i + 1];
-      }
-      // subtract those, and in the same sweep |w|^2
-      axpy_dots(vec(0), static_cast<int>(j + 1), nre, nim, W_, true, d);
-      const double b = std::sqrt(std::max(d[0], 0.0));
-      last_b = b;
-      scale = std::max(scale, std::max(std::fabs(alpha.back()), b));
-      k = j + 1;
-      if (j + 1 == m_ || b <= 1e-14 * scale) break;
-      beta.push_back(b);
-      hipLaunchKernelGGL((k_scale_copy<T>), dim3(grid_), dim3(kKB), 0, s_, n_, W_, 1.0 / b, vec(j + 1));
-      PBS_HIP(hipGetLastError());
-    }
+    const uint32_t k = st.k;
+    const double *alpha = st.alpha, *beta = st.beta;
     // exp(-i T dt) e_1 from the eigen-decomposition of the tridiagonal T
     std::vector<double> a(static_cast<size_t>(k) * k, 0.0), u;
     for (uint32_t i = 0; i < k; ++i) a[i * k + i] = alpha[i];
@@ -387,7 +447,7 @@ class Lanczos {
     PBS_HIP(hipStreamSynchronize(s_));
     info[1] = alpha[0];
     info[2] = static_cast<double>(k);
-    info[3] = last_b;
+    info[3] = st.last_b;
   }
 
  private:
@@ -401,8 +461,8 @@ class Lanczos {
   T* V_ = nullptr;
   T* W_ = nullptr;
   double* partial_ = nullptr;
-  double* dots_ = nullptr;
-  unsigned grid_ = 1;
+  LanczosState* st_ = nullptr;
+  unsigned grid_ = 1, dot_grid_ = 1;
 };
 
 }  // namespace

@@ -261,6 +261,7 @@ struct SectorArgs {
   const double* fp;
   const uint32_t* eq;
   const double* fq;
+  const uint32_t* skip;  // single launches: nothing is done when this is set and not zero
 };
 
 // Combinatorial rank of a spin string: uint16 tables in LDS (n_orb <= 16,
@@ -1171,6 +1172,7 @@ template <class T, bool EXPVAL>
 __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 8 : 1, 8))) void k_apply_rows(SectorArgs P, RowsLayout Lr, const T* __restrict__ psi,
                                                     T* __restrict__ out, double* __restrict__ partial) {
   extern __shared__ __align__(16) unsigned char smem[];
+  if (P.skip && *P.skip) return;
   const uint32_t ia = blockIdx.x + P.row_begin;
   const uint64_t db = P.dim_beta;
   uint16_t* s_rank = reinterpret_cast<uint16_t*>(smem + Lr.off_rank);
@@ -1314,6 +1316,7 @@ __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 template <class T, bool EXPVAL, bool R16, bool ROWLDS, bool REALC>
 __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_apply_sector(
     SectorArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial) {
+  if (P.skip && *P.skip) return;
   const uint32_t chunks = (P.dim_beta + kSB - 1) / kSB;
   uint32_t row, chunk;
   row_chunk_of(blockIdx.x, gridDim.x / chunks, chunks, P.row_lds != 0, row, chunk);
