@@ -7,6 +7,7 @@
 #include <mutex>
 #include <string>
 
+#include "lists.h"
 #include "panel.h"
 #include "sector.h"
 
@@ -333,6 +334,34 @@ bool plan_rows(const pbs_grouped& h, const SectorArgs& a, bool r16, bool expval,
   return true;
 }
 
+// Arguments of the lists kernel when it applies (see lists.h): a row too long
+// for the sector kernel's staging that fits in LDS here.
+bool plan_lists(const pbs_grouped& h, const pbs_space& sp, const SectorArgs& a, bool r16, size_t elem_bytes,
+                ListsArgs* out, size_t* lds) {
+  const FactorPlan* F = h.fplan.get();
+  if (!r16 || a.row_lds || a.alist_off == nullptr || F == nullptr || !F->blist || !(h.fact_on & kFactMoves) ||
+      F->n_beta != sp.n_beta || F->dim_beta != sp.dim_beta)
+    return false;
+  ListsArgs L{};
+  const uint32_t nu = F->bl_ub - F->bl_ua;
+  const uint64_t row = (sp.dim_beta + 1) * elem_bytes;
+  const uint64_t limit = static_cast<uint64_t>(device_lds_limit()) - 1024u;  // static shared arrays
+  if (row + 16 + 4096 + 12ull * nu + 64 + 8ull * F->n_mag > limit) return false;
+  L.off_tab = align16(static_cast<uint32_t>(row));
+  L.off_f = L.off_tab + 4096u;
+  L.off_z = L.off_f + align16(8u * nu);
+  L.off_mag = L.off_z + align16(4u * nu);
+  *lds = L.off_mag + align16(8u * F->n_mag);
+  L.bl_off = F->bl_off.get();
+  L.bl_ent = F->bl_ent.get();
+  L.bl_mag = F->bl_mag.get();
+  L.n_mag = F->n_mag;
+  L.ua = F->bl_ua;
+  L.ub = F->bl_ub;
+  *out = L;
+  return true;
+}
+
 struct PanelShape {
   int variant = 0;  // of kPanelVariants
   size_t lds = 0;
@@ -427,8 +456,17 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
       PBS_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(kPanelLanes), args, ps.lds, s));
       return rows;
     }
-    RowsLayout Lr;
+    ListsArgs la;
     size_t lds_rows = 0;
+    if (h.real_coef && plan_lists(h, sp, a, r16, sizeof(T), &la, &lds_rows)) {
+      void* kern = h.fplan->bl_narrow ? reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, true>)
+                                 : reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, false>);
+      void* args[] = {&a, &la, &p, &o, &partial};
+      PBS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_rows)));
+      PBS_HIP(hipLaunchKernel(kern, dim3(static_cast<unsigned>(rows)), dim3(kLB), args, lds_rows, s));
+      return rows;
+    }
+    RowsLayout Lr;
     if (h.real_coef && plan_rows(h, a, r16, EXPVAL, &Lr, &lds_rows)) {
       // one workgroup per alpha row, sweeping all of its columns
       hipLaunchKernelGGL((k_apply_rows<T, EXPVAL>), dim3(static_cast<unsigned>(rows)), dim3(kSB), lds_rows, s, a, Lr,

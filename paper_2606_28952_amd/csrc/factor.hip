@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <vector>
 
@@ -380,6 +381,38 @@ __global__ __launch_bounds__(64) void k_pull_offsets(uint32_t n_tiles, const uin
   }
 }
 
+// Column lists of the pair groups (xb, zb, code = magnitude index | sign << 15
+// of their single coefficient): one wave per 64 columns.  Pass 0 writes the
+// slots of four entries that the longest list needs; pass 1 writes the
+// entries in group order and fills up with entries that read a zero.
+__global__ __launch_bounds__(64) void k_column_lists(uint32_t pass, uint32_t db, const uint32_t* str_b,
+                                                     const uint32_t* xb, const uint32_t* zb, const uint32_t* code,
+                                                     uint32_t n_grp, bool narrow, uint32_t* slots,
+                                                     const uint32_t* off, void* ent) {
+  const uint32_t grp = blockIdx.x, lane = threadIdx.x, col = grp * 64u + lane;
+  const uint32_t tb = col < db ? str_b[col] : 0u;
+  const uint64_t base = pass ? off[grp] : 0u;
+  uint32_t n = 0;
+  auto put = [&](uint32_t w) {
+    const uint64_t at = ((base + n / 4u) * 64u + lane) * 4u + n % 4u;
+    if (pass && narrow) static_cast<uint16_t*>(ent)[at] = static_cast<uint16_t>((w & 0x7fffu) | (w >> 16));
+    if (pass && !narrow) static_cast<uint32_t*>(ent)[at] = w;
+    ++n;
+  };
+  if (col < db)
+    for (uint32_t g = 0; g < n_grp; ++g) {
+      if (__popc(tb & xb[g]) != 1) continue;
+      put(colex_rank(tb ^ xb[g]) | ((code[g] ^ ((__popc(zb[g] & tb) & 1u) << 15)) << 16));
+    }
+  if (pass) {
+    const uint32_t all = 4u * (off[grp + 1] - off[grp]);
+    while (n < all) put(db);
+    return;
+  }
+  for (int d = 32; d > 0; d >>= 1) n = max(n, static_cast<uint32_t>(__shfl_xor(n, d, 64)));
+  if (lane == 0) slots[grp] = (n + 3u) / 4u;
+}
+
 __global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
@@ -548,6 +581,35 @@ bool panel_lists(const FactorPlan& F, const pbs_grouped& h, const pbs_space& sp,
     L->al_lo.push_back(static_cast<uint32_t>(L->al_za.size()));
   }
   return true;
+}
+
+// Pair groups of the lists kernel; false when the operator is not one that it
+// evaluates (see lists.h).
+struct ColumnGroups {
+  std::vector<uint32_t> xb, zb, code;
+  std::vector<double> mag;
+};
+constexpr size_t kMaxMagnitudes = 256;
+bool column_groups(const HostTables& T, const ClassMeta& m, ColumnGroups* C) {
+  if (m.xa != 0 || m.p1 != m.g1) return false;
+  std::map<double, uint32_t> index;
+  for (uint32_t g = m.zg >= 0 ? m.g0 + 1 : m.g0; g < m.g1; ++g) {
+    const uint32_t u = T.pg_u0[g];
+    if (T.pg_u0[g + 1] != u + 1) return false;
+    double c = 0.0;
+    for (uint32_t t = T.u_t0[u]; t < T.u_t0[u + 1]; ++t) {
+      if (T.pt_za[t] != 0u) return false;
+      c += T.pt_c[t];
+    }
+    if (!std::isfinite(c)) return false;
+    const auto at = index.emplace(std::fabs(c), static_cast<uint32_t>(index.size())).first;
+    if (at->second == C->mag.size()) C->mag.push_back(std::fabs(c));
+    if (C->mag.size() > kMaxMagnitudes) return false;
+    C->xb.push_back(T.pg_xb[g]);
+    C->zb.push_back(T.u_zb[u]);
+    C->code.push_back(at->second | (std::signbit(c) ? 0x8000u : 0u));
+  }
+  return !C->xb.empty();
 }
 
 }  // namespace
@@ -737,6 +799,11 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
   F.panel_variant = panel_variant_for(sp.dim_alpha, sp.dim_beta, h.n_pairs, sp.n_alpha * (sp.n_orb - sp.n_alpha) + 1u);
   bool panel = F.plist && F.panel_variant >= 0 && panel_lists(F, h, sp, T, meta, cls_f, zpair, icls, &L);
 
+  ColumnGroups cols;
+  const bool blist = F.alist && F.c0 == 0xffffffffu && ns.size() == 1 && sp.n_orb <= 16 && db < 65536 &&
+                     column_groups(T, meta[ns[0]], &cols);
+  const uint32_t col_groups = static_cast<uint32_t>((db + 63) / 64);
+
   // tables whose sizes are known, and the temporaries of this call
   // (a plan built for the panel kernel alone leaves the sector kernel's move tables out)
   const bool moves = F.c0 != 0xffffffffu;
@@ -804,13 +871,34 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
     own.add(F.diag_a, da * F.diag_rank);
     own.add(F.pull_cnt, n_rec);
   }
+  DevBuf<uint32_t> d_bx, d_bz, d_bcode, bl_slots;
+  if (blist) {
+    const ClassMeta& m = meta[ns[0]];
+    F.bl_ua = m.ua;
+    F.bl_ub = m.zg >= 0 ? m.u_z : m.ua;
+    F.n_mag = static_cast<uint32_t>(cols.mag.size());
+    F.bl_narrow = F.n_mag == 1 && db < 32768;
+    tmp.upload(d_bx, cols.xb);
+    tmp.upload(d_bz, cols.zb);
+    tmp.upload(d_bcode, cols.code);
+    tmp.add(bl_slots, col_groups);
+    own.add(F.bl_off, col_groups + 1);
+    own.upload(F.bl_mag, cols.mag);
+  }
   DevBuf<char> tmp_mem;
   st.commit(own, F.mem[0], false);
   st.commit(tmp, tmp_mem, true);
 
   // counts first: they come back while the other tables are built
   const unsigned row_grid = static_cast<unsigned>(std::min<uint64_t>(da, 65536));
-  std::vector<uint32_t> ca, cp, slots;
+  std::vector<uint32_t> ca, cp, slots, col_slots;
+  if (blist) {
+    hipLaunchKernelGGL(k_column_lists, dim3(col_groups), dim3(64), 0, s, 0u, static_cast<uint32_t>(db),
+                       sp.str_beta.get(), d_bx.get(), d_bz.get(), d_bcode.get(),
+                       static_cast<uint32_t>(cols.xb.size()), F.bl_narrow, bl_slots.get(), nullptr, nullptr);
+    st.fetch(col_slots, bl_slots, col_groups);
+    exclusive_scan_u32(bl_slots.get(), F.bl_off.get(), col_groups, F.bl_off.get() + col_groups, s);
+  }
   if (F.alist) {
     hipLaunchKernelGGL(k_alpha_list, dim3(row_grid), dim3(256), 0, s, 0u, da, sp.n_alpha, sp.str_alpha.get(),
                        d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
@@ -874,17 +962,28 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
   // absent entries read V's zero; a tile's copy may run past the last slot
   const uint64_t pull_words = panel ? 32ull * (slots[0] + kPanelPullSlots) : 0u;
   Slab lists;
-  lists.add(F.alist_src, n_list);
-  lists.add(F.alist_c, n_list);
+  // (the lists kernel reads a fixed number of entries, past the last list too)
+  lists.add(F.alist_src, n_list + (blist ? kListRowsAhead : 0u));
+  lists.add(F.alist_c, n_list + (blist ? kListRowsAhead : 0u));
   lists.add(F.plist_src, n_ent);
   lists.add(F.plist_cls, n_ent);
   lists.add(F.pimg, n_ent * F.n_img);
   lists.add(F.pull, pull_words / 4);
+  uint64_t n_slots = 0;
+  for (uint32_t v : col_slots) n_slots += v;
+  // a wave loads a fixed number of slots, past the last list too
+  if (blist) lists.add(F.bl_ent, 64ull * (n_slots + kListSlotsAhead) * (F.bl_narrow ? 1u : 2u));
   st.commit(lists, F.mem[1], false);
   if (n_list)
     hipLaunchKernelGGL(k_alpha_list, dim3(row_grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),
                        d_simple.get(), static_cast<uint32_t>(simple.size()), h.cls_meta.get(), h.u_t0.get(),
                        h.pt_za.get(), h.pt_c.get(), F.alist_off.get(), nullptr, F.alist_src.get(), F.alist_c.get());
+  if (blist) {
+    hipLaunchKernelGGL(k_column_lists, dim3(col_groups), dim3(64), 0, s, 1u, static_cast<uint32_t>(db),
+                       sp.str_beta.get(), d_bx.get(), d_bz.get(), d_bcode.get(),
+                       static_cast<uint32_t>(cols.xb.size()), F.bl_narrow, nullptr, F.bl_off.get(), F.bl_ent.get());
+    F.blist = true;
+  }
   if (n_ent) {
     ent_row = DevBuf<uint32_t>(n_ent, s);
     hipLaunchKernelGGL(k_pair_list, dim3(row_grid), dim3(256), 0, s, 1u, da, sp.n_alpha, sp.str_alpha.get(),

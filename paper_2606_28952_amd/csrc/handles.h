@@ -151,6 +151,16 @@ struct FactorPlan {
   // slots of its target groups (a byte each, x and y), the wave's first slot
   // in the tile (z) and the tile's first slot (w)
   DevBuf<uint4> pull, pull_cnt;
+  // Column lists of the lists kernel (lists.h), when the operator is one it
+  // evaluates: per 64 columns, slots of four entries per column, entry =
+  // source column (dim_beta: none) | magnitude index << 16 | sign << 31; with
+  // one magnitude and narrow columns 16 bits, source | sign << 15.
+  bool blist = false, bl_narrow = false;
+  uint32_t n_mag = 0;                // distinct magnitudes
+  uint32_t bl_ua = 0, bl_ub = 0;     // uniques of the diagonal group
+  DevBuf<uint32_t> bl_off;           // [ceil(dim_beta / 64) + 1]
+  DevBuf<uint2> bl_ent;              // [slots][64] of four 16- or 32-bit entries
+  DevBuf<double> bl_mag;
   // sizes for the rows kernel: longest alpha list, and the uniques and
   // groups of all non-simple classes
   uint32_t alist_max = 0, ns_uniques = 0, ns_groups = 0;

@@ -15,6 +15,8 @@ namespace pbs {
 
 // ------------------------------------------------------ sector LDS layout
 constexpr int kMaxMoves = 56;         // pair moves cached per lane (N_beta (n_orb - N_beta) <= 56)
+constexpr uint32_t kListSlotsAhead = 6;  // lists kernel: slots of column entries in flight
+constexpr uint32_t kListRowsAhead = 20;  // and gathers of the simple classes at most
 constexpr uint32_t kRowCapBytes = 64u * 1024u;
 constexpr uint32_t kListMinBytes = 4096u;  // simple-class row list when no row is staged
 // LDS copy of the uint16 rank tables (n_orb <= 16): chunk 0 with no ones

@@ -153,3 +153,60 @@ def test_rows_kernel_hubbard_long_rows(dev):
     e32_ref = np.vdot(psi32_np.astype(np.complex128), ref32)
     assert abs(e32[0] - e32_ref.real) < 1e-12 * max(1.0, abs(e32_ref))
     assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi32)), torch.view_as_real(out32))
+
+
+def _chain_integrals(n, kind, rng):
+    """Nearest-neighbour hops on a ring and density-density terms, per kind:
+    equal hops with on-site terms, random hops with terms of all ranges and
+    spins (diagonal masks across both bytes), hops alone."""
+    h1, h2 = np.zeros((2 * n, 2 * n)), np.zeros((2 * n,) * 4)
+    for spin in (0, n):
+        for p in range(n):
+            q = (p + 1) % n
+            t = -1.0 if kind != "random" else rng.standard_normal()
+            h1[spin + p, spin + q] = h1[spin + q, spin + p] = t
+    if kind == "equal":
+        pairs = [(p, n + p, 4.0) for p in range(n)]
+    elif kind == "random":
+        pairs = [(p, q, rng.standard_normal()) for p in range(2 * n) for q in range(p) if rng.random() < 0.3]
+    else:
+        pairs = []
+    for p, q, v in pairs:
+        h2[p, q, q, p] = h2[q, p, p, q] = v
+    return h1, h2
+
+
+@pytest.mark.parametrize("n,na,nb,dtype,kind", [(15, 1, 6, "c128", "random"), (16, 2, 5, "c128", "equal"),
+                                                (16, 1, 6, "c128", "random"), (16, 1, 7, "c64", "hops"),
+                                                (16, 1, 8, "c64", "equal"), (16, 1, 8, "c64", "random"),
+                                                (16, 1, 7, "c128", "equal")])
+def test_lists_kernel_long_rows(dev, n, na, nb, dtype, kind):
+    """Column lists over rows staged in LDS: the shortest and longest rows of
+    each storage type (and one too long, which stays with the rows kernel),
+    one and many magnitudes, no diagonal group, a last group of 64 columns that
+    is not full; against the oracle and the evaluation without move tables.
+    Every target sums some forty float64 products of one sign each, so 1e-12;
+    single-precision storage rounds inputs exactly and outputs to 2^-24."""
+    api = _api()
+    rng = np.random.default_rng(n * nb)
+    h1, h2 = _chain_integrals(n, kind, rng)
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(n, na, nb)
+    psi_np = synth.random_state(sp.dim, 5)
+    if dtype == "c64":
+        psi_np = psi_np.astype(np.complex64).astype(np.complex128)
+    tol = 1e-12 if dtype == "c128" else 2.0 ** -23
+    ref = oapply.apply_scatter(ojw.jw_sum(h1, h2), ospace.SectorSpace(n, na, nb), psi_np)
+    psi = torch.from_numpy(psi_np).to(dev).to(torch.complex128 if dtype == "c128" else torch.complex64)
+    G.factor(sp)
+    out = torch.empty_like(psi)
+    e = api.expval(G, sp, psi, out=out).cpu().numpy()
+    assert rel_err(out.cpu().numpy().astype(np.complex128), ref) < tol
+    e_ref = np.vdot(psi_np, ref)
+    assert abs(e[0] - e_ref.real) < 1e-12 * max(1.0, abs(e_ref))
+    assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi)), torch.view_as_real(out))
+    rows = sp.shape()[3]
+    parts = [api.apply_pauli_sum_rows(G, sp, psi, a, b) for a, b in ((0, 1), (1, rows - 1), (rows - 1, rows))]
+    assert torch.equal(torch.view_as_real(torch.cat(parts)), torch.view_as_real(out))
+    G.set_factored(5)  # without the move tables
+    assert rel_err(api.apply_pauli_sum(G, sp, psi).cpu().numpy().astype(np.complex128), ref) < tol
