@@ -15,47 +15,186 @@ namespace pbs {
 namespace {
 
 // ---------------------------------------------------------------- full space
-template <class T, bool EXPVAL>
-__global__ __launch_bounds__(kBlock) void k_apply_full(uint64_t dim, uint32_t n_groups, const uint64_t* __restrict__ xg,
-                                                       const uint32_t* __restrict__ off,
-                                                       const uint64_t* __restrict__ zk,
-                                                       const double2* __restrict__ ck, const T* __restrict__ psi,
-                                                       T* __restrict__ out, double* __restrict__ partial,
-                                                       const uint32_t* skip) {
-  if (skip && *skip) return;
-  double e_re = 0.0, e_im = 0.0, nrm = 0.0;
-  for (uint64_t t = blockIdx.x * static_cast<uint64_t>(kBlock) + threadIdx.x; t < dim;
-       t += static_cast<uint64_t>(gridDim.x) * kBlock) {
-    double acc_r = 0.0, acc_i = 0.0;
-    for (uint32_t g = 0; g < n_groups; ++g) {
-      const uint64_t s = t ^ xg[g];
-      double fr = 0.0, fi = 0.0;
-      const uint32_t k1 = off[g + 1];
-      for (uint32_t k = off[g]; k < k1; ++k) {
-        const uint32_t par = static_cast<uint32_t>(__popcll(zk[k] & s));
-        const double2 c = ck[k];
-        fr += signed_by(c.x, par);
-        fi += signed_by(c.y, par);
+// A workgroup owns a tile of R * 256 consecutive targets, R per lane (256
+// apart), and holds the tile's amplitudes in LDS: groups whose X-mask stays
+// within the tile gather from there, the others gather the same places of one
+// other tile, coalesced.  The R targets of a lane share the scalar
+// loads and the signs of a group's terms: they differ in log2 R bits, so the
+// terms are summed per pattern of their masks' bits there and a Walsh transform
+// gives the R phase sums.  A group of one term without Z bits costs two FMAs per
+// target.
+// Workgroups of consecutive tiles run on one XCD (workgroup w runs on XCD w mod
+// 8), so that gathers across tiles find most of their sources in its L2.
+// Bound by the gathers across tiles: a 22-site transverse-field Ising chain in
+// complex64 (11 of its 23 groups cross tiles, 0.44 GB through L2) takes 52 us,
+// 8.4 TB/s, and 83 in complex128; a target per lane that gathered every group
+// from memory took 117 and 120.  At 18 sites, where most of the time is latency,
+// 10.5 against 10.7.  Tiles of 512 or 1024 lanes, 16 targets per lane, or four
+// gathers in flight per lane are all slower (53 to 61 us).
+constexpr uint32_t kFullLanes = 256;
+
+// f[j] <- sum over p of (-1)^popcount(p & j) f[p]
+template <int R>
+__device__ inline void walsh(double (&f)[R]) {
+#pragma unroll
+  for (int h = 1; h < R; h *= 2)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (!(j & h)) {
+        const double a = f[j], b = f[j | h];
+        f[j] = a + b;
+        f[j | h] = a - b;
       }
-      double ar, ai;
-      Amp<T>::load(psi, s, ar, ai);
-      acc_r = fma(ar, fr, fma(-ai, fi, acc_r));
-      acc_i = fma(ar, fi, fma(ai, fr, acc_i));
-    }
-    if (EXPVAL) {
-      double pr, pi;
-      Amp<T>::load(psi, t, pr, pi);
-      e_re = fma(pr, acc_r, fma(pi, acc_i, e_re));
-      e_im = fma(pr, acc_i, fma(-pi, acc_r, e_im));
-      nrm = fma(pr, pr, fma(pi, pi, nrm));
-      if (out) Amp<T>::store(out, t, acc_r, acc_i);
-    } else {
-      Amp<T>::store(out, t, acc_r, acc_i);
-    }
-  }
-  if (EXPVAL) block_reduce3_store<kBlock>(e_re, e_im, nrm, partial + 3ull * blockIdx.x);
 }
 
+template <class T, bool EXPVAL, int R>
+__global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_t n_groups,
+                                                           const uint64_t* __restrict__ xg,
+                                                           const uint32_t* __restrict__ off,
+                                                           const uint64_t* __restrict__ zk,
+                                                           const double* __restrict__ ck, const T* __restrict__ psi,
+                                                           T* __restrict__ out, double* __restrict__ partial,
+                                                           const uint32_t* skip) {
+  if (skip && *skip) return;
+  constexpr uint32_t kTile = kFullLanes * R;
+  __shared__ T s_psi[kTile];
+  const uint32_t tid = threadIdx.x;
+  const uint64_t n_tiles = (dim + kTile - 1) / kTile;
+  double e_re = 0.0, e_im = 0.0, nrm = 0.0;
+  for (uint64_t w = blockIdx.x; w < n_tiles; w += gridDim.x) {
+    const uint64_t per = n_tiles / kXcds;
+    const uint64_t tile = (w < per * kXcds ? w % kXcds * per + w / kXcds : w) * kTile;
+    // a space smaller than one tile: the lanes behind it repeat its targets
+    const uint32_t lane = dim < kTile ? tid & static_cast<uint32_t>(dim - 1) : tid;
+    const uint32_t step = dim < kTile ? 0u : kFullLanes;
+    if (w != blockIdx.x) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < R; ++j) s_psi[tid + kFullLanes * j] = psi[tile + lane + step * j];
+    __syncthreads();
+    double ar[R], ai[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) ar[j] = ai[j] = 0.0;
+    const uint64_t t0 = tile + lane;
+    // a group's mask, end and first term are read while the group before it is
+    // evaluated
+    uint32_t g = 0, k = 0, k1 = n_groups ? off[1] : 0u, k1_next = 0;
+    uint64_t x = n_groups ? xg[0] : 0u, z0 = n_groups ? zk[0] : 0u, x_next = 0, z_next = 0;
+    double c0 = n_groups ? ck[0] : 0.0, d0 = n_groups ? ck[1] : 0.0, c_next = 0.0, d_next = 0.0;
+    // the current group's amplitudes, the next group's scalars first
+    auto gather = [&](T (&a)[R]) {
+      const uint32_t next = min(g + 1u, n_groups - 1u), kn = min(k1, off[n_groups] - 1u);
+      x_next = xg[next];
+      z_next = zk[kn];
+      k1_next = off[next + 1u];
+      c_next = ck[2 * kn];
+      d_next = ck[2 * kn + 1];
+      const uint32_t xl = static_cast<uint32_t>(x) & (kTile - 1), place = lane ^ (xl & (kFullLanes - 1));
+      if (x < kTile) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) a[j] = s_psi[place + (kFullLanes * j ^ (xl & ~(kFullLanes - 1)))];
+      } else {
+        const T* from = psi + (tile ^ (x & ~static_cast<uint64_t>(kTile - 1)));
+#pragma unroll
+        for (int j = 0; j < R; ++j) a[j] = (from + (kFullLanes * j ^ (xl & ~(kFullLanes - 1))))[place];
+      }
+    };
+    auto advance = [&] {
+      ++g;
+      k = k1;
+      k1 = k1_next;
+      x = x_next;
+      z0 = z_next;
+      c0 = c_next;
+      d0 = d_next;
+    };
+    while (g < n_groups) {
+      T a[R];
+      // runs of groups of one real term without Z bits, in a loop of their own
+      while (g < n_groups && k1 - k == 1 && z0 == 0 && d0 == 0.0) {
+        gather(a);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          ar[j] = fma(c0, static_cast<double>(a[j].x), ar[j]);
+          ai[j] = fma(c0, static_cast<double>(a[j].y), ai[j]);
+        }
+        advance();
+      }
+      if (g == n_groups) break;
+      gather(a);
+      // phase sums at the sources s = t ^ x, four terms read at a time: sums per
+      // pattern of the mask's bits that tell the lane's targets apart, then
+      // for target j the sum over patterns p of (-1)^popcount(p & j)
+      double fr[R], fi[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) fr[j] = fi[j] = 0.0;
+      bool imag = false;
+      auto add = [&](uint64_t z, double c, double d) {
+        const uint32_t par = static_cast<uint32_t>(__popcll(z & (t0 ^ x)));
+        const uint32_t p = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(z / kFullLanes)) & (R - 1);
+        const double cs = signed_by(c, par);
+#pragma unroll
+        for (uint32_t q = 0; q < R; ++q)
+          if (p == q) {
+            fr[q] += cs;
+            asm volatile("" : "+v"(fr[q]));  // one add behind a scalar branch, not R selects
+          }
+        if (d != 0.0) {
+          imag = true;
+          const double ds = signed_by(d, par);
+#pragma unroll
+          for (uint32_t q = 0; q < R; ++q)
+            if (p == q) {
+              fi[q] += ds;
+              asm volatile("" : "+v"(fi[q]));
+            }
+        }
+      };
+      add(z0, c0, d0);
+      for (++k; k + 4 <= k1; k += 4) {
+        uint64_t z[4];
+        double c[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          z[i] = zk[k + i];
+          c[2 * i] = ck[2 * (k + i)];
+          c[2 * i + 1] = ck[2 * (k + i) + 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) add(z[i], c[2 * i], c[2 * i + 1]);
+      }
+      for (; k < k1; ++k) add(zk[k], ck[2 * k], ck[2 * k + 1]);
+      walsh<R>(fr);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        ar[j] = fma(static_cast<double>(a[j].x), fr[j], ar[j]);
+        ai[j] = fma(static_cast<double>(a[j].y), fr[j], ai[j]);
+      }
+      if (imag) {
+        walsh<R>(fi);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          ar[j] = fma(-static_cast<double>(a[j].y), fi[j], ar[j]);
+          ai[j] = fma(static_cast<double>(a[j].x), fi[j], ai[j]);
+        }
+      }
+      advance();
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const uint64_t t = tile + tid + kFullLanes * j;
+      if (t >= dim) continue;
+      if (EXPVAL) {
+        const T own = s_psi[tid + kFullLanes * j];
+        const double pr = static_cast<double>(own.x), pi = static_cast<double>(own.y);
+        e_re = fma(pr, ar[j], fma(pi, ai[j], e_re));
+        e_im = fma(pr, ai[j], fma(-pi, ar[j], e_im));
+        nrm = fma(pr, pr, fma(pi, pi, nrm));
+      }
+      if (!EXPVAL || out) Amp<T>::store(out, t, ar[j], ai[j]);
+    }
+  }
+  if (EXPVAL) block_reduce3_store<kFullLanes>(e_re, e_im, nrm, partial + 3ull * blockIdx.x);
+}
 
 // Per-job sums of workgroup partials (one workgroup per job, fixed order).
 struct FinishJob {
@@ -423,10 +562,21 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
   const T* p = static_cast<const T*>(psi);
   T* o = static_cast<T*>(out);
   if (!sp.sector) {
-    const dim3 grid(grid_for(sp.dim, kBlock, kFullGridCap));
-    hipLaunchKernelGGL((k_apply_full<T, EXPVAL>), grid, dim3(kBlock), 0, s, sp.dim,
-                       static_cast<uint32_t>(h.n_groups), h.xg.get(), h.off.get(), h.zk.get(),
-                       reinterpret_cast<const double2*>(h.ck.get()), p, o, partial, skip);
+    // as many targets per lane as leave a workgroup per compute unit; eight of
+    // 16 bytes cost too many registers (102 us at 22 sites, 83 with four)
+    const uint64_t lanes = sp.dim / kFullLanes, want = device_cus();
+    auto go = [&](auto kern, uint32_t r) {
+      const unsigned grid = grid_for(sp.dim, kFullLanes * r, kFullGridCap);
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(kFullLanes), 0, s, sp.dim, static_cast<uint32_t>(h.n_groups),
+                         h.xg.get(), h.off.get(), h.zk.get(), h.ck.get(), p, o, partial, skip);
+      PBS_HIP(hipGetLastError());
+      return static_cast<uint64_t>(grid);
+    };
+    if constexpr (sizeof(T) == 8)
+      if (lanes >= 8 * want) return go(k_apply_full<T, EXPVAL, 8>, 8);
+    if (lanes >= 4 * want) return go(k_apply_full<T, EXPVAL, 4>, 4);
+    if (lanes >= 2 * want) return go(k_apply_full<T, EXPVAL, 2>, 2);
+    return go(k_apply_full<T, EXPVAL, 1>, 1);
   } else {
     SectorArgs a;
     bool r16 = false;

@@ -65,6 +65,40 @@ def test_full_space_random_operator(dev, n, m):
     assert rel_err(_run(dev, G, sp, psi32, np.complex64), ref32) < 1e-6
 
 
+@pytest.mark.parametrize("n", [7, 8, 9, 16, 17, 18, 19])
+def test_full_space_targets_per_lane(dev, n):
+    """Full-space kernel at the sizes where the targets per lane change (2 from
+    17 sites, 4 from 18, 8 in single precision from 19) and below, at and above
+    one tile: single real X terms inside and across tiles, many-term groups
+    whose Z-masks touch every bit, complex coefficients."""
+    api = _api()
+    rng = np.random.default_rng(n)
+    letters = np.zeros((n + 40, n), dtype=np.uint8)
+    other, _ = synth.random_pauli_strings(20, n, seed=n)
+    letters[n:n + 20] = other
+    letters[:n][np.arange(n), np.arange(n)] = 1  # X on every site
+    zs = rng.integers(0, 2, (20, n)).astype(np.uint8) * 3  # Z strings, and Z behind one X-mask
+    flips = (other[0] == 1) | (other[0] == 2)
+    zs[10:][:, flips] = 1
+    letters[n + 20:] = zs
+    c = rng.standard_normal(n + 40).astype(np.complex128)
+    c[n:n + 10] += 1j * rng.standard_normal(10)
+    op = opauli.PauliSum(n, letters, c)
+    G = _gpu_op(dev, op)
+    sp = api.Space.full(n)
+    for dtype, tol in ((np.complex128, 1e-12), (np.complex64, 1e-6)):
+        psi = synth.random_state(1 << n, seed=n).astype(dtype)
+        ref = oapply.apply_scatter(op, ospace.FullSpace(n), psi.astype(np.complex128))
+        got = _run(dev, G, sp, psi, dtype)
+        assert rel_err(got.astype(np.complex128), ref) < tol
+        t = torch.from_numpy(psi).to(dev)
+        out = torch.empty_like(t)
+        e = api.expval(G, sp, t, out=out).cpu().numpy()
+        assert np.array_equal(out.cpu().numpy(), got)
+        e_ref = np.vdot(psi.astype(np.complex128), ref)
+        assert abs(complex(e[0], e[1]) - e_ref) < 1e-10 * max(1.0, abs(e_ref))
+
+
 def test_twelve_qubit_molecular_full_and_sector(dev):
     api = _api()
     h1, h2 = synth.molecular_spin_integrals(6, seed=1001)
