@@ -1,6 +1,7 @@
 // Grouping of a canonical Pauli sum by X-mask (Section 2.4,
 // Eq. topological_group) and the tables of the spin-sector kernel.
 #include "handles.h"
+#include "staging.h"
 
 namespace pbs {
 namespace {
@@ -11,16 +12,12 @@ __global__ void k_x_heads(const uint64_t* x, uint64_t m, uint32_t* heads) {
     heads[i] = (i == 0 || x[i] != x[i - 1]) ? 1u : 0u;
 }
 
-// CSR fill: group masks and offsets from heads; XZ-form coefficients
-// C_k = c_k * i^popcount(x_k & z_k) (Section 2.3).
-__global__ void k_csr_fill(const uint64_t* x, const uint64_t* z, const double* c, uint64_t m, const uint32_t* heads,
-                           const uint32_t* gid, uint64_t* xg, uint32_t* off, uint64_t* zk, double* ck) {
+// CSR terms: Z-masks and XZ-form coefficients C_k = c_k * i^popcount(x_k & z_k)
+// (Section 2.3).
+__global__ void k_csr_terms(const uint64_t* x, const uint64_t* z, const double* c, uint64_t m, uint64_t* zk,
+                            double* ck) {
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
-    if (heads[i]) {
-      xg[gid[i]] = x[i];
-      off[gid[i]] = static_cast<uint32_t>(i);
-    }
     zk[i] = z[i];
     const uint32_t y = static_cast<uint32_t>(__popcll(x[i] & z[i])) & 3u;
     const double r = c[2 * i], im = c[2 * i + 1];
@@ -33,14 +30,27 @@ __global__ void k_csr_fill(const uint64_t* x, const uint64_t* z, const double* c
   }
 }
 
+// CSR groups: masks and offsets from heads, then the end of the last group.
+__global__ void k_csr_groups(const uint64_t* x, uint64_t m, const uint32_t* heads, const uint32_t* gid, uint64_t* xg,
+                             uint32_t* off, uint64_t n_groups) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) off[n_groups] = static_cast<uint32_t>(m);
+  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
+       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
+    if (heads[i]) {
+      xg[gid[i]] = x[i];
+      off[gid[i]] = static_cast<uint32_t>(i);
+    }
+}
+
 __global__ void k_set_u32(uint32_t* p, uint32_t v) { *p = v; }
 
 // Sector rewrite of every term: alive flag, sort keys and signed coefficient
 // (the exact rewrites listed with pbs_grouped).  Keys, most significant word
 // first: (X_alpha << 6 | popcount(X_beta)), (X_beta << 32 | z_beta'), z_alpha.
+// any_imag is set when an alive term has an imaginary part.
 __global__ void k_sector_terms(const uint64_t* x, const uint64_t* zk, const double* ck, uint64_t m, uint32_t h,
                                uint32_t* alive, uint64_t* k2, uint64_t* k1, uint64_t* k0, double* cre,
-                               double* cim) {
+                               double* cim, uint32_t* any_imag) {
   const uint64_t mask = (h == 32) ? 0xffffffffull : ((1ull << h) - 1ull);
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
@@ -48,7 +58,8 @@ __global__ void k_sector_terms(const uint64_t* x, const uint64_t* zk, const doub
     const uint64_t za = zk[i] & mask;
     uint64_t zb = (zk[i] >> h) & mask;
     const uint32_t pa = __popcll(xa), pb = __popcll(xb);
-    alive[i] = ((pa & 1u) == 0 && (pb & 1u) == 0) ? 1u : 0u;
+    const bool live = (pa & 1u) == 0 && (pb & 1u) == 0;
+    alive[i] = live ? 1u : 0u;
     uint32_t flips = 0;
     if (xb != 0 && (zb & (xb & (~xb + 1ull)))) {
       zb ^= xb;
@@ -61,11 +72,14 @@ __global__ void k_sector_terms(const uint64_t* x, const uint64_t* zk, const doub
     k0[i] = za;
     cre[i] = sgn * ck[2 * i];
     cim[i] = sgn * ck[2 * i + 1];
+    if (live && cim[i] != 0.0) *any_imag = 1u;  // (every writer stores the same value)
   }
 }
 
+// Keys of the alive terms, their places for the sort, and where they came from.
 __global__ void k_compact_alive(const uint32_t* alive, const uint32_t* pos, uint64_t m, const uint64_t* k2,
-                                const uint64_t* k1, const uint64_t* k0, uint64_t* keys_soa, uint64_t ma) {
+                                const uint64_t* k1, const uint64_t* k0, uint64_t* keys_soa, uint64_t ma,
+                                uint32_t* order) {
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
     if (!alive[i]) continue;
@@ -73,13 +87,8 @@ __global__ void k_compact_alive(const uint32_t* alive, const uint32_t* pos, uint
     keys_soa[o] = k0[i];
     keys_soa[ma + o] = k1[i];
     keys_soa[2 * ma + o] = k2[i];
+    order[o] = static_cast<uint32_t>(i);
   }
-}
-
-__global__ void k_alive_index(const uint32_t* alive, const uint32_t* pos, uint64_t m, uint32_t* src) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    if (alive[i]) src[pos[i]] = static_cast<uint32_t>(i);
 }
 
 // Heads of classes (X_alpha), plan groups (X_alpha, X_beta) and uniques
@@ -101,11 +110,17 @@ __global__ void k_plan_heads(const uint64_t* keys_soa, uint64_t ma, uint32_t* hc
   }
 }
 
-__global__ void k_plan_fill(const uint64_t* keys_soa, uint64_t ma, const uint32_t* order, const uint32_t* src,
-                            const double* cre, const double* cim, const uint32_t* hc, const uint32_t* hg,
+// (and the end of the last class, group and unique)
+__global__ void k_plan_fill(const uint64_t* keys_soa, uint64_t ma, const uint32_t* order, const double* cre, const double* cim, const uint32_t* hc, const uint32_t* hg,
                             const uint32_t* hu, const uint32_t* cid, const uint32_t* gid, const uint32_t* uid,
                             uint32_t* cls_xa, uint32_t* cls_g0, uint32_t* pg_xb, uint32_t* pg_pc, uint32_t* pg_u0,
-                            uint32_t* u_zb, uint32_t* u_t0, uint32_t* pt_za, double* pt_c) {
+                            uint32_t* u_zb, uint32_t* u_t0, uint32_t* pt_za, double* pt_c, uint32_t n_class,
+                            uint32_t n_pgroup, uint32_t n_unique) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    cls_g0[n_class] = n_pgroup;
+    pg_u0[n_pgroup] = n_unique;
+    u_t0[n_unique] = static_cast<uint32_t>(ma);
+  }
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < ma;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
     const uint64_t w2 = keys_soa[2 * ma + i], w1 = keys_soa[ma + i], w0 = keys_soa[i];
@@ -123,17 +138,10 @@ __global__ void k_plan_fill(const uint64_t* keys_soa, uint64_t ma, const uint32_
       u_t0[uid[i]] = static_cast<uint32_t>(i);
     }
     pt_za[i] = static_cast<uint32_t>(w0);
-    const uint32_t s = src[order[i]];
+    const uint32_t s = order[i];
     pt_c[2 * i] = cre[s];
     pt_c[2 * i + 1] = cim[s];
   }
-}
-
-// Flags any coefficient with a nonzero imaginary part.
-__global__ void k_any_imag(const double* c, uint64_t m, uint32_t* flag) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    if (c[2 * i + 1] != 0.0) atomicOr(flag, 1u);
 }
 
 // Per class: the X_beta = 0 group, the popcount-2 and popcount-4 ranges,
@@ -193,9 +201,12 @@ __global__ void k_quad_map(uint32_t n_class, const int32_t* p1, const int32_t* q
   }
 }
 
-__global__ void k_pair_rows(uint32_t n_class, const uint32_t* has_pairs, const uint32_t* slot, int32_t* pm) {
-  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n_class; c += gridDim.x * blockDim.x)
-    pm[c] = has_pairs[c] ? static_cast<int32_t>(slot[c]) : -1;
+__global__ void k_map_rows(uint32_t n_class, const uint32_t* has_pairs, const uint32_t* pair_slot,
+                           const uint32_t* has_quads, const uint32_t* quad_slot, int32_t* pm, int32_t* qm) {
+  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n_class; c += gridDim.x * blockDim.x) {
+    pm[c] = has_pairs[c] ? static_cast<int32_t>(pair_slot[c]) : -1;
+    qm[c] = has_quads[c] ? static_cast<int32_t>(quad_slot[c]) : -1;
+  }
 }
 
 __global__ void k_class_pack(uint32_t n_class, const uint32_t* cls_xa, const uint32_t* cls_g0, const int32_t* zg,
@@ -235,12 +246,13 @@ __global__ void k_fill_i32(int32_t* p, uint64_t n, int32_t v) {
     p[i] = v;
 }
 
-// Pair map: the group of each popcount-2 X_beta in its class.
+// Pair map: the group of each popcount-2 X_beta in its class (one workgroup per
+// class, its threads over the class's pair groups).
 __global__ void k_pair_map(uint32_t n_class, const int32_t* p0, const int32_t* p1, const int32_t* pm,
                            const uint32_t* pg_xb, uint32_t n_pairs, int32_t* pmap) {
-  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n_class; c += gridDim.x * blockDim.x) {
+  for (uint32_t c = blockIdx.x; c < n_class; c += gridDim.x) {
     if (pm[c] < 0) continue;
-    for (int32_t g = p0[c]; g < p1[c]; ++g) {
+    for (int32_t g = p0[c] + static_cast<int32_t>(threadIdx.x); g < p1[c]; g += static_cast<int32_t>(blockDim.x)) {
       const uint32_t xb = pg_xb[g];
       const uint32_t p = __ffs(xb) - 1;
       const uint32_t q = 31 - __clz(xb);
@@ -251,21 +263,35 @@ __global__ void k_pair_map(uint32_t n_class, const int32_t* p0, const int32_t* p
 
 }  // namespace
 
-static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s) {
+// Sector tables of the m >= 0 terms x, g.zk, g.ck.  What decides the sizes comes
+// back in three waits (alive terms, with the caller's CSR group count in
+// n_groups; classes, groups and uniques; maps and class records), through
+// pinned staging: at 16 qubits the eleven waits and twelve pageable copies it
+// took before were half of the grouping's time.
+static void build_sector_tables(pbs_grouped& g, const uint64_t* x, const uint32_t* n_groups, hipStream_t s,
+                                const std::function<void(uint64_t)>& groups_known) {
   const uint64_t m = g.n_terms;
   const uint32_t h = g.n_qubits / 2;
   g.half = h;
   g.n_pairs = h * (h - 1) / 2;
-  DevBuf<uint32_t> alive(m, s), apos(m, s), cnt(4, s);
+  Staging st(s);
+  DevBuf<uint32_t> alive(m, s), apos(m, s), cnt(8, s);
   DevBuf<uint64_t> k2(m, s), k1(m, s), k0(m, s);
   DevBuf<double> cre(m, s), cim(m, s);
+  uint32_t *n_alive = cnt.get(), *imag = cnt.get() + 1, *n_heads = cnt.get() + 2, *n_maps = cnt.get() + 5;
+  PBS_HIP(hipMemsetAsync(cnt.get(), 0, 8 * sizeof(uint32_t), s));
   if (m) {
     hipLaunchKernelGGL(k_sector_terms, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, x, g.zk.get(), g.ck.get(), m,
-                       h, alive.get(), k2.get(), k1.get(), k0.get(), cre.get(), cim.get());
+                       h, alive.get(), k2.get(), k1.get(), k0.get(), cre.get(), cim.get(), imag);
     PBS_HIP(hipGetLastError());
+    exclusive_scan_u32(alive.get(), apos.get(), m, n_alive, s);
   }
-  exclusive_scan_u32(alive.get(), apos.get(), m, cnt.get(), s);
-  const uint64_t ma = read_scalar(cnt.get(), s);
+  uint32_t groups = 0, first[2] = {0u, 0u};
+  if (m) st.fetch(&groups, n_groups, 1);
+  st.fetch(first, n_alive, 2);
+  st.wait();
+  groups_known(groups);
+  const uint64_t ma = first[0];
   g.n_pterm = static_cast<uint32_t>(ma);
   g.has_sector = true;
   if (ma == 0) {
@@ -281,27 +307,25 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s
     PBS_HIP(hipStreamSynchronize(s));
     return;
   }
+  g.real_coef = first[1] == 0u;
   DevBuf<uint64_t> keys(3 * ma, s);
-  DevBuf<uint32_t> src(ma, s), order(ma, s);
+  DevBuf<uint32_t> order(ma, s);
   hipLaunchKernelGGL(k_compact_alive, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, alive.get(), apos.get(), m,
-                     k2.get(), k1.get(), k0.get(), keys.get(), ma);
-  hipLaunchKernelGGL(k_alive_index, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, alive.get(), apos.get(), m,
-                     src.get());
+                     k2.get(), k1.get(), k0.get(), keys.get(), ma, order.get());
   PBS_HIP(hipGetLastError());
-  iota_u32(order.get(), ma, s);
   radix_sort_keys(keys.get(), order.get(), ma, 3, s);
   DevBuf<uint32_t> hc(ma, s), hg(ma, s), hu(ma, s), cid(ma, s), gid(ma, s), uid(ma, s);
   hipLaunchKernelGGL(k_plan_heads, dim3(grid_for(ma, 256, 65536)), dim3(256), 0, s, keys.get(), ma, hc.get(),
                      hg.get(), hu.get());
-  exclusive_scan_u32(hc.get(), cid.get(), ma, cnt.get() + 1, s);
-  exclusive_scan_u32(hg.get(), gid.get(), ma, cnt.get() + 2, s);
-  exclusive_scan_u32(hu.get(), uid.get(), ma, cnt.get() + 3, s);
-  uint32_t counts[4];
-  PBS_HIP(hipMemcpyAsync(counts, cnt.get(), sizeof(counts), hipMemcpyDeviceToHost, s));
-  PBS_HIP(hipStreamSynchronize(s));
-  g.n_class = counts[1];
-  g.n_pgroup = counts[2];
-  g.n_unique = counts[3];
+  exclusive_scan_u32(hc.get(), cid.get(), ma, n_heads, s);
+  exclusive_scan_u32(hg.get(), gid.get(), ma, n_heads + 1, s);
+  exclusive_scan_u32(hu.get(), uid.get(), ma, n_heads + 2, s);
+  uint32_t counts[3];
+  st.fetch(counts, n_heads, 3);
+  st.wait();
+  g.n_class = counts[0];
+  g.n_pgroup = counts[1];
+  g.n_unique = counts[2];
   g.cls_xa.alloc(g.n_class);
   g.cls_g0.alloc(g.n_class + 1);
   g.pg_xb.alloc(g.n_pgroup);
@@ -312,16 +336,10 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s
   g.pt_za.alloc(ma);
   g.pt_c.alloc(2 * ma);
   hipLaunchKernelGGL(k_plan_fill, dim3(grid_for(ma, 256, 65536)), dim3(256), 0, s, keys.get(), ma, order.get(),
-                     src.get(), cre.get(), cim.get(), hc.get(), hg.get(), hu.get(), cid.get(), gid.get(), uid.get(),
+                     cre.get(), cim.get(), hc.get(), hg.get(), hu.get(), cid.get(), gid.get(), uid.get(),
                      g.cls_xa.get(), g.cls_g0.get(), g.pg_xb.get(), g.pg_pc.get(), g.pg_u0.get(), g.u_zb.get(),
-                     g.u_t0.get(), g.pt_za.get(), g.pt_c.get());
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, g.cls_g0.get() + g.n_class, g.n_pgroup);
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, g.pg_u0.get() + g.n_pgroup, g.n_unique);
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, g.u_t0.get() + g.n_unique, static_cast<uint32_t>(ma));
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, cnt.get(), 0u);
-  hipLaunchKernelGGL(k_any_imag, dim3(grid_for(ma, 256, 65536)), dim3(256), 0, s, g.pt_c.get(), ma, cnt.get());
+                     g.u_t0.get(), g.pt_za.get(), g.pt_c.get(), g.n_class, g.n_pgroup, g.n_unique);
   PBS_HIP(hipGetLastError());
-  g.real_coef = read_scalar(cnt.get(), s) == 0u;
 
   // bucket metadata, the pair map and the quad map
   g.cls_zg.alloc(g.n_class);
@@ -332,26 +350,40 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s
   g.cls_qm.alloc(g.n_class);
   const uint64_t n_quads = host_binom(h, 4);
   g.n_quads = n_quads <= kMaxQuads ? static_cast<uint32_t>(n_quads) : 0u;
-  DevBuf<uint32_t> has_pairs(g.n_class, s), has_quads(g.n_class, s), slot(g.n_class, s);
+  DevBuf<uint32_t> has_pairs(g.n_class, s), has_quads(g.n_class, s), pslot(g.n_class, s), qslot(g.n_class, s);
   hipLaunchKernelGGL(k_class_meta, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class,
                      g.cls_g0.get(), g.pg_pc.get(), g.n_quads > 0, g.cls_zg.get(), g.cls_p0.get(), g.cls_p1.get(),
                      g.cls_q1.get(), has_pairs.get(), has_quads.get());
-  exclusive_scan_u32(has_pairs.get(), slot.get(), g.n_class, cnt.get(), s);
-  g.n_pmap = read_scalar(cnt.get(), s);
-  hipLaunchKernelGGL(k_pair_rows, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class, has_pairs.get(),
-                     slot.get(), g.cls_pm.get());
+  exclusive_scan_u32(has_pairs.get(), pslot.get(), g.n_class, n_maps, s);
+  exclusive_scan_u32(has_quads.get(), qslot.get(), g.n_class, n_maps + 1, s);
+  hipLaunchKernelGGL(k_map_rows, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class, has_pairs.get(),
+                     pslot.get(), has_quads.get(), qslot.get(), g.cls_pm.get(), g.cls_qm.get());
+  g.cls_meta.alloc(g.n_class);
+  hipLaunchKernelGGL(k_class_pack, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class,
+                     g.cls_xa.get(), g.cls_g0.get(), g.cls_zg.get(), g.cls_p1.get(), g.cls_pm.get(), g.cls_q1.get(),
+                     g.cls_qm.get(), g.pg_u0.get(), g.cls_meta.get(), n_maps + 2);
+  PBS_HIP(hipGetLastError());
+  // the class schedule is made on the host, once per operator
+  uint32_t maps[3];
+  std::vector<ClassMeta> meta;
+  std::vector<uint32_t> u0, xb, zb;
+  st.fetch(maps, n_maps, 3);
+  st.fetch(meta, g.cls_meta, g.n_class);
+  st.fetch(u0, g.pg_u0, g.n_pgroup + 1);
+  st.fetch(xb, g.pg_xb, g.n_pgroup);
+  st.fetch(zb, g.u_zb, g.n_unique);
+  st.wait();
+  g.n_pmap = maps[0];
+  g.n_qmap = maps[1];
+  g.max_quad_uniques = maps[2];
   const uint64_t pm_entries = static_cast<uint64_t>(g.n_pmap) * g.n_pairs;
   g.pmap.alloc(pm_entries);
   if (pm_entries) {
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(pm_entries, 256, 65536)), dim3(256), 0, s, g.pmap.get(), pm_entries,
                        -1);
-    hipLaunchKernelGGL(k_pair_map, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class,
+    hipLaunchKernelGGL(k_pair_map, dim3(std::min<uint32_t>(g.n_class, 65536u)), dim3(128), 0, s, g.n_class,
                        g.cls_p0.get(), g.cls_p1.get(), g.cls_pm.get(), g.pg_xb.get(), g.n_pairs, g.pmap.get());
   }
-  exclusive_scan_u32(has_quads.get(), slot.get(), g.n_class, cnt.get(), s);
-  g.n_qmap = read_scalar(cnt.get(), s);
-  hipLaunchKernelGGL(k_pair_rows, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class, has_quads.get(),
-                     slot.get(), g.cls_qm.get());
   const uint64_t qm_entries = static_cast<uint64_t>(g.n_qmap) * g.n_quads;
   g.qmap.alloc(qm_entries);
   if (qm_entries) {
@@ -360,22 +392,7 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s
     hipLaunchKernelGGL(k_quad_map, dim3(std::min<uint32_t>(g.n_class, 65536u)), dim3(256), 0, s, g.n_class,
                        g.cls_p1.get(), g.cls_q1.get(), g.cls_qm.get(), g.pg_xb.get(), g.n_quads, g.qmap.get());
   }
-  g.cls_meta.alloc(g.n_class);
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, cnt.get(), 0u);
-  hipLaunchKernelGGL(k_class_pack, dim3(grid_for(g.n_class, 256, 65536)), dim3(256), 0, s, g.n_class,
-                     g.cls_xa.get(), g.cls_g0.get(), g.cls_zg.get(), g.cls_p1.get(), g.cls_pm.get(), g.cls_q1.get(),
-                     g.cls_qm.get(), g.pg_u0.get(), g.cls_meta.get(), cnt.get());
   PBS_HIP(hipGetLastError());
-  g.max_quad_uniques = read_scalar(cnt.get(), s);
-
-  // class schedule (host side, once per operator)
-  std::vector<ClassMeta> meta(g.n_class);
-  std::vector<uint32_t> u0(g.n_pgroup + 1), xb(g.n_pgroup), zb(g.n_unique);
-  PBS_HIP(hipMemcpyAsync(meta.data(), g.cls_meta.get(), meta.size() * sizeof(ClassMeta), hipMemcpyDeviceToHost, s));
-  PBS_HIP(hipMemcpyAsync(u0.data(), g.pg_u0.get(), u0.size() * 4, hipMemcpyDeviceToHost, s));
-  if (!xb.empty()) PBS_HIP(hipMemcpyAsync(xb.data(), g.pg_xb.get(), xb.size() * 4, hipMemcpyDeviceToHost, s));
-  if (!zb.empty()) PBS_HIP(hipMemcpyAsync(zb.data(), g.u_zb.get(), zb.size() * 4, hipMemcpyDeviceToHost, s));
-  PBS_HIP(hipStreamSynchronize(s));
   std::vector<uint32_t> runs, ns;
   int64_t qcnt = -1;
   for (uint32_t c = 0; c < g.n_class; ++c) {
@@ -425,13 +442,11 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, hipStream_t s
   g.n_runs = static_cast<uint32_t>(runs.size() / 2);
   g.n_ns = static_cast<uint32_t>(ns.size());
   g.quad_cnt = qcnt > 0 ? static_cast<uint32_t>(qcnt) : 0u;
-  g.zpair.alloc(zp.size());
-  g.runs.alloc(runs.size());
-  g.ns_list.alloc(ns.size());
-  PBS_HIP(hipMemcpyAsync(g.zpair.get(), zp.data(), zp.size() * 4, hipMemcpyHostToDevice, s));
-  if (!runs.empty()) PBS_HIP(hipMemcpyAsync(g.runs.get(), runs.data(), runs.size() * 4, hipMemcpyHostToDevice, s));
-  if (!ns.empty()) PBS_HIP(hipMemcpyAsync(g.ns_list.get(), ns.data(), ns.size() * 4, hipMemcpyHostToDevice, s));
-  PBS_HIP(hipStreamSynchronize(s));  // the host vectors end here
+  Slab tables;
+  tables.upload(g.zpair, zp);
+  tables.upload(g.runs, runs);
+  tables.upload(g.ns_list, ns);
+  st.commit(tables, g.mem, false);
 }
 
 }  // namespace pbs
@@ -455,25 +470,27 @@ pbs_status pbs_group_by_xmask(const pbs_sum* hs, void* stream, pbs_grouped** out
       g->n_qubits = hs->n_qubits;
       g->n_terms = m;
       DevBuf<uint32_t> heads(m, s), gid(m, s), cnt(1, s);
-      uint64_t G = 0;
-      if (m) {
-        hipLaunchKernelGGL(k_x_heads, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), m, heads.get());
-        exclusive_scan_u32(heads.get(), gid.get(), m, cnt.get(), s);
-        G = read_scalar(cnt.get(), s);
-      }
-      g->n_groups = G;
-      g->xg.alloc(G);
-      g->off.alloc(G + 1);
       g->zk.alloc(m);
       g->ck.alloc(2 * m);
-      hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, g->off.get() + G, static_cast<uint32_t>(m));
-      if (m)
-        hipLaunchKernelGGL(k_csr_fill, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), hs->z.get(),
-                           hs->coeff.get(), m, heads.get(), gid.get(), g->xg.get(), g->off.get(), g->zk.get(),
-                           g->ck.get());
-      PBS_HIP(hipGetLastError());
+      if (m) {
+        hipLaunchKernelGGL(k_csr_terms, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), hs->z.get(),
+                           hs->coeff.get(), m, g->zk.get(), g->ck.get());
+        hipLaunchKernelGGL(k_x_heads, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), m, heads.get());
+        exclusive_scan_u32(heads.get(), gid.get(), m, cnt.get(), s);
+      }
+      auto groups_known = [&](uint64_t G) {
+        g->n_groups = G;
+        g->xg.alloc(G);
+        g->off.alloc(G + 1);
+        hipLaunchKernelGGL(k_csr_groups, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), m, heads.get(),
+                           gid.get(), g->xg.get(), g->off.get(), G);
+        PBS_HIP(hipGetLastError());
+      };
+      if ((g->n_qubits % 2) == 0)
+        build_sector_tables(*g, hs->x.get(), cnt.get(), s, groups_known);
+      else
+        groups_known(m ? read_scalar(cnt.get(), s) : 0u);
       PBS_HIP(hipStreamSynchronize(s));
-      if ((g->n_qubits % 2) == 0) build_sector_tables(*g, hs->x.get(), s);
     } catch (...) {
       delete g;
       throw;

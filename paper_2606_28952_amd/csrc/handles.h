@@ -176,6 +176,8 @@ struct pbs_grouped {
   pbs::DevBuf<uint64_t> zk;
   pbs::DevBuf<double> ck;
 
+  pbs::DevBuf<char> mem;  // of zpair, runs and ns_list
+
   bool has_sector = false;
   uint32_t half = 0;
   uint32_t n_class = 0, n_pgroup = 0, n_unique = 0, n_pterm = 0;
