@@ -14,15 +14,18 @@ second stream) overlaps the previous step's fused pass; the serial figure,
 each build waiting for the previous pass, is reported beside it
 (ms_per_step_serial).
 
-The dominant kernel (the sector apply; for the Hubbard sector the rows
-kernel) is timed with HIP events on the stream it runs on.  On the molecular
-sector it is bound by vector-ALU issue:
+The dominant kernel (the panel kernel on molecular sectors, the lists kernel on
+the Hubbard sector) is timed with HIP events on the stream it runs on.  On the
+molecular sector it is bound by the vector ALUs and the matrix cores together:
 its roofline is its VALU wave-instructions per launch (from the committed
 rocprofv3 counters of the same kernel source) per second against 614.4 G/s,
-with the measured HBM traffic and the method's algorithmic gather bytes,
-D * b * (1 + G_conn) (b = 8 bytes per complex64 amplitude, G_conn connected
-groups per target), reported beside it.  On the Hubbard sector it is bound by
-HBM bandwidth and the algorithmic bytes are the roofline.  The complex128
+with the share of time the float64 matrix instructions need, the measured HBM
+traffic and the method's algorithmic gather bytes, D * b * (1 + G_conn)
+(b = 8 bytes per complex64 amplitude, G_conn connected groups per target),
+reported beside it.  On the Hubbard sector it is bound by the way of other rows'
+amplitudes through the caches: its roofline is the bytes that cannot come from
+the staged row, D * b * (1 + G_alpha) (G_alpha connected groups that leave the
+beta string alone), against the HBM peak.  The complex128
 (FP64 plain) apply is timed beside it, and the oracle's C twin is timed on a
 bounded sample of the same workload on the host cores.
 
@@ -50,10 +53,10 @@ WORKLOADS = {
                                                bound="alu")),
     "molecular-12q-sector": ("molecular", dict(n_orb=6, n_alpha=3, n_beta=3, h_seed=1001, psi_seed=1102,
                                                bound="alu")),
-    # the Hubbard sector's rows (103 KB) are too long to stage: with the
-    # factor tables its apply is the rows kernel
+    # the Hubbard sector's rows (103 KB) are too long for the sector kernel's
+    # staging: with the factor tables its apply is the lists kernel
     "hubbard-32q-sector": ("hubbard", dict(rows=4, cols=4, n_alpha=8, n_beta=8, psi_seed=4101, bound="hbm",
-                                           kernel="rows")),
+                                           kernel="lists")),
 }
 
 
@@ -618,9 +621,10 @@ def main():
     e64 = api.expval(G, sp, psi64).cpu().numpy()
     e32 = api.expval(G, sp, psi32).cpu().numpy()
 
-    # roofline of the dominant kernel.  The sector apply is bound by vector-ALU
-    # issue (one wave64 VALU instruction per 4 cycles per SIMD: 256 CUs x 4
-    # SIMDs x 2.4 GHz / 4 = 614.4 G wave-instructions/s); its VALU count and
+    # roofline of the dominant kernel.  The panel kernel is bound by vector-ALU
+    # and matrix issue (one wave64 VALU instruction per 4 cycles per SIMD: 256 CUs x 4
+    # SIMDs x 2.4 GHz / 4 = 614.4 G wave-instructions/s; a 16 x 16 x 4 float64
+    # matrix instruction holds its SIMD for 64 cycles); its VALU count and
     # HBM bytes per launch come from the committed counter runs of the same
     # kernel source (null when the kernel has changed since).  The method's
     # algorithmic gather bytes per launch, D * 8 B * (1 + G_conn), are
@@ -640,16 +644,20 @@ def main():
     del cp_src, cp_dst
     bytes_per_launch = D * 8 * (1.0 + g_conn)
     gather_gbs = bytes_per_launch / (apply_ms * 1e-3) / 1e9
-    kernel_tag = f"apply_{prm.get('kernel', 'sector') if not args.no_factor else 'sector'}_c64_{args.workload}"
+    kernel_tag = f"apply_{prm.get('kernel', 'panel') if not args.no_factor else 'sector'}_c64_{args.workload}"
     ctr = _counters(kernel_tag)
     traffic = ctr.get("hbm_bytes_per_launch") if ctr else None
     valu = ctr.get("valu_wave_insts_per_launch") if ctr else None
+    mfma = ctr.get("mfma_insts_per_launch") if ctr else None
     valu_peak = VALU_PEAK_GINST
     if prm["bound"] == "hbm":
-        # bandwidth-bound (few groups per target, rows too long for LDS): the
-        # algorithmic gather bytes against the HBM peak
-        roofline = {"bound": "hbm", "achieved": gather_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                    "frac": gather_gbs / HBM_PEAK_GBS, "measured_copy_GBs": copy_gbs, "traffic": traffic,
+        # bandwidth-bound (few groups per target): the gathers of other rows and
+        # the output against the HBM peak
+        own = np.array([int(x) >> n_orb == 0 for x in xg.tolist()], dtype=bool)
+        g_alpha = _connected_groups(xg[own], n_orb, na, nb)
+        row_gbs = D * 8 * (1.0 + g_alpha) / (apply_ms * 1e-3) / 1e9
+        roofline = {"bound": "hbm", "achieved": row_gbs, "algorithmic_gather_GBs": gather_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": row_gbs / HBM_PEAK_GBS, "measured_copy_GBs": copy_gbs, "traffic": traffic,
                     "hbm_GBs": traffic / (apply_ms * 1e-3) / 1e9 if traffic else None,
                     "valu_frac": valu / (apply_ms * 1e-3) / 1e9 / valu_peak if valu else None,
                     "apply_ms": apply_ms, "apply_ms_serial_steps": apply_ms_serial}
@@ -658,6 +666,7 @@ def main():
                     "achieved": valu / (apply_ms * 1e-3) / 1e9 if valu else None, "peak": valu_peak,
                     "unit": "G VALU wave-instructions/s",
                     "frac": valu / (apply_ms * 1e-3) / 1e9 / valu_peak if valu else None,
+                    "matrix_frac": mfma * 64 / (1024 * 2.4e9 * apply_ms * 1e-3) if mfma else None,
                     "traffic": traffic,
                     "hbm_GBs": traffic / (apply_ms * 1e-3) / 1e9 if traffic else None,
                     "hbm_frac": traffic / (apply_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if traffic else None,

@@ -1108,6 +1108,8 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
       const uint32_t ord = best & PBS_BATCH_ORDER_MASK;
       for (uint32_t f = 1; f < kBatchConfigs; ++f) {
         if (f & PBS_BATCH_ORDER_MASK) continue;
+        // (tables that the batch's owner brought are not an operator's own to ignore)
+        if ((f & PBS_BATCH_NO_FACTORED) && !b->plan_a.empty()) continue;
         const double t = time_config(ord | f);
         if (t < best_ms) {
           best = ord | f;

@@ -13,8 +13,8 @@
 // group's folded coefficients become two 256-entry tables over the bytes of the
 // target string.  Bound by the alpha gathers' way through the caches (17 rows
 // read per row written): the 4 x 4 Hubbard sector in complex64 takes 3.74 ms, in
-// which 25.5 GB come from behind L2 (6.9 TB/s) and 11.8 GB from memory; without
-// the alpha gathers it takes 2.06 ms, without the column lists 3.63.  Evaluating
+// which 25.5 GB come from behind L2 (6.9 TB/s); without the alpha gathers it
+// takes 2.06 ms, without the column lists 3.63.  Evaluating
 // every pair group per target with its rank lookup and phase sum, and gathering
 // the row through L2 (the rows kernel), took 7.45 ms.  Loads issued where they
 // are used, not ahead of the column's evaluation: 5.09 ms.
