@@ -17,10 +17,9 @@ each build waiting for the previous pass, is reported beside it
 The dominant kernel (the panel kernel on molecular sectors, the lists kernel on
 the Hubbard sector) is timed with HIP events on the stream it runs on.  On the
 molecular sector it is bound by the vector ALUs and the matrix cores together:
-its roofline is its VALU wave-instructions per launch (from the committed
-rocprofv3 counters of the same kernel source) per second against 614.4 G/s,
-with the share of time the float64 matrix instructions need, the measured HBM
-traffic and the method's algorithmic gather bytes, D * b * (1 + G_conn)
+its roofline is the SIMD cycles that its vector and matrix instructions hold
+(counts from the committed rocprofv3 counters of the same kernel source) against
+1024 SIMDs at 2.4 GHz, with the two shares, the measured HBM traffic and the method's algorithmic gather bytes, D * b * (1 + G_conn)
 (b = 8 bytes per complex64 amplitude, G_conn connected groups per target),
 reported beside it.  On the Hubbard sector it is bound by the way of other rows'
 amplitudes through the caches: its roofline is the bytes that cannot come from
@@ -662,11 +661,16 @@ def main():
                     "valu_frac": valu / (apply_ms * 1e-3) / 1e9 / valu_peak if valu else None,
                     "apply_ms": apply_ms, "apply_ms_serial_steps": apply_ms_serial}
     else:
-        roofline = {"bound": "alu", "resource": "VALU issue (wave64 instructions)",
-                    "achieved": valu / (apply_ms * 1e-3) / 1e9 if valu else None, "peak": valu_peak,
-                    "unit": "G VALU wave-instructions/s",
-                    "frac": valu / (apply_ms * 1e-3) / 1e9 / valu_peak if valu else None,
-                    "matrix_frac": mfma * 64 / (1024 * 2.4e9 * apply_ms * 1e-3) if mfma else None,
+        # SIMD cycles that the launch's instructions hold: 4 per vector
+        # instruction, 64 per float64 matrix instruction
+        cycles = 4.0 * (valu - (mfma or 0.0)) + 64.0 * (mfma or 0.0) if valu else None
+        simd_peak = 1024 * 2.4  # G cycles/s
+        roofline = {"bound": "alu", "resource": "SIMD cycles of vector and matrix instructions",
+                    "achieved": cycles / (apply_ms * 1e-3) / 1e9 if valu else None, "peak": simd_peak,
+                    "unit": "G SIMD cycles/s",
+                    "frac": cycles / (apply_ms * 1e-3) / 1e9 / simd_peak if valu else None,
+                    "valu_frac": valu / (apply_ms * 1e-3) / 1e9 / valu_peak if valu else None,
+                    "matrix_frac": mfma * 64 / (simd_peak * 1e9 * apply_ms * 1e-3) if mfma else None,
                     "traffic": traffic,
                     "hbm_GBs": traffic / (apply_ms * 1e-3) / 1e9 if traffic else None,
                     "hbm_frac": traffic / (apply_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if traffic else None,

@@ -71,6 +71,36 @@ def test_krylov_breakdown_on_eigenvector(dev):
     assert rel_err(t.cpu().numpy(), np.exp(-1j * w[0] * 0.05) * v) < 1e-12
 
 
+@pytest.mark.parametrize("kind", ["full", "panel", "sector"])
+def test_krylov_ends_early_on_every_apply(dev, kind):
+    """A run that ends after one vector leaves the queued kernels empty: the
+    result is the eigenvector's phase, whichever kernel applies H; a zero state
+    ends before the first vector and stays as it is."""
+    api = _api()
+    n_o = 4
+    h1, h2 = synth.molecular_spin_integrals(n_o, 3)
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    full = kind == "full"
+    osp = ospace.FullSpace(2 * n_o) if full else ospace.SectorSpace(n_o, 2, 2)
+    sp = api.Space.full(2 * n_o) if full else api.Space.sector(n_o, 2, 2)
+    if kind == "panel":
+        G.factor(sp)
+    op = ojw.jw_sum(h1, h2)
+    eye = np.eye(osp.dim, dtype=np.complex128)
+    Hd = np.stack([oapply.apply_scatter(op, osp, eye[i]) for i in range(osp.dim)], axis=1)
+    w, U = np.linalg.eigh(Hd)
+    v = U[:, 0].astype(np.complex128)
+    prop = api.KrylovPropagator(G, sp, dtype=torch.complex128, m=12)
+    t = torch.from_numpy(v).to(dev)
+    info = prop.step(t, 0.05)
+    assert info[2] == 1.0
+    # the residual of a one-vector space: |H v - w v| dt, some 1e-14 of |H|
+    assert rel_err(t.cpu().numpy(), np.exp(-1j * w[0] * 0.05) * v) < 1e-12
+    t.zero_()
+    assert list(prop.step(t, 0.05)) == [0.0, 0.0, 0.0, 0.0]
+    assert torch.count_nonzero(torch.view_as_real(t)) == 0
+
+
 def test_krylov_rejects_bad_arguments(dev):
     api = _api()
     from paper_2606_28952_amd._abi import PbsError
