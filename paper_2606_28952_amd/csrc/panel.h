@@ -73,7 +73,7 @@ struct PanelArgs {
   const uint4* pull;         // per tile, wave and target group: slots of 64 two-byte entries
   const uint4* pull_cnt;     // [n_tiles][waves]: slots per target group (a byte each, x and y), first slot of the
                              // wave in its tile (z), first slot of the tile (w)
-  const uint32_t* skip;      // single launches: nothing is done when this is set and not zero
+  const uint32_t* skip;      // nothing is done when this is set and not zero
 };
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -145,7 +145,9 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
         const T* rowg = psi + static_cast<uint64_t>(ia + g + r) * db;
         for (uint32_t c = tid; c < db; c += kPB) s_st[c * kS + r] = rowg[c];
       }
+    const bool skip = g == 0 && P.skip && *P.skip;
     __syncthreads();
+    if (skip) return;
     // beta-only part, two moves per step, the next two loading
     auto gather = [&](uint32_t col, double c, int j) {
 #pragma unroll
@@ -493,7 +495,6 @@ __device__ inline uint32_t panel_block_of(uint32_t w, uint32_t n) {
 template <class T, bool EXPVAL, int NT, int MT, int KS, int R>
 __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_panel(
     PanelArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial) {
-  if (P.skip && *P.skip) return;
   const uint64_t b = P.blk0 + panel_block_of(blockIdx.x, gridDim.x);
   const uint32_t r0 = max(static_cast<uint32_t>(b * P.dim_alpha / P.n_blk), P.row_begin);
   const uint32_t r1 = min(static_cast<uint32_t>((b + 1) * P.dim_alpha / P.n_blk), P.row_end);

@@ -261,7 +261,7 @@ struct SectorArgs {
   const double* fp;
   const uint32_t* eq;
   const double* fq;
-  const uint32_t* skip;  // single launches: nothing is done when this is set and not zero
+  const uint32_t* skip;  // nothing is done when this is set and not zero
 };
 
 // Combinatorial rank of a spin string: uint16 tables in LDS (n_orb <= 16,
@@ -635,7 +635,10 @@ __device__ __forceinline__ void sector_body(const SectorArgs& P, const T* __rest
     s_F[f_cap + threadIdx.x] = C::zero();
     s_Fz[f_cap + threadIdx.x] = 0u;
   }
+  // (read among the prologue's loads: in front of them it costs 0.2 us a launch)
+  const bool skip = P.skip && *P.skip;
   __syncthreads();
+  if (skip) return;
 
   const uint32_t db = P.dim_beta;
   const uint32_t col = chunk * kSB + threadIdx.x;
@@ -1316,7 +1319,6 @@ __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 template <class T, bool EXPVAL, bool R16, bool ROWLDS, bool REALC>
 __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_apply_sector(
     SectorArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial) {
-  if (P.skip && *P.skip) return;
   const uint32_t chunks = (P.dim_beta + kSB - 1) / kSB;
   uint32_t row, chunk;
   row_chunk_of(blockIdx.x, gridDim.x / chunks, chunks, P.row_lds != 0, row, chunk);
