@@ -711,7 +711,9 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
   own.upload(F.cls_f, cls_f);
   for (int k = 0; k < 3; ++k) own.upload(F.ns_rest[k], rest[k]);
   if (F.plist) own.upload(F.pimg_flag, flag);
-  own.add(F.fz, static_cast<uint64_t>(n_zrows) * db);
+  // (the panel kernel loads a first F row for every image class, also where
+  // no class has one: then a row of zeros, which its evaluation leaves out)
+  own.add(F.fz, static_cast<uint64_t>(panel ? std::max(n_zrows, 1u) : n_zrows) * db);
   DevBuf<uint32_t> d_qlo, d_qzb, d_simple, d_icls, cnt_a, cnt_p, ent_row;
   DevBuf<double> d_qc;
   DevBuf<int32_t> d_pk, d_qk;
@@ -820,6 +822,9 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
     st.fetch(slots, pull_total, 2);
   }
   PBS_HIP(hipGetLastError());
+  if (panel && n_zrows == 0)
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(2 * db, 256, 4096)), dim3(256), 0, s,
+                       reinterpret_cast<uint32_t*>(F.fz.get()), 2 * db, 0u);
   if (n_zrows) {
     const uint64_t n = static_cast<uint64_t>(n_zrows) * db;
     hipLaunchKernelGGL(k_fact_rows, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n_zrows, db, sp.str_beta.get(),

@@ -107,3 +107,30 @@ def test_panel_needs_its_operator_structure(dev):
     plain = api.apply_pauli_sum(G, sp, psi).cpu().numpy()
     G.factor(sp)
     assert rel_err(api.apply_pauli_sum(G, sp, psi).cpu().numpy(), plain) < 1e-12
+
+
+@pytest.mark.parametrize("n_o,na,nb", [(4, 2, 2), (6, 3, 2), (6, 2, 4), (8, 4, 4)])
+def test_panel_without_diagonal_factors(dev, n_o, na, nb):
+    """No class has an X_beta = 0 group but the simple ones: the diagonal and
+    the single hops of alpha alone are left out, so there is no F row at all."""
+    from oracle import pauli as opauli
+    from paper_2606_28952_amd import api
+
+    seed = 700 + 10 * n_o + nb
+    h1, h2 = synth.molecular_spin_integrals(n_o, seed)
+    op = ojw.jw_sum(h1, h2)
+    flips = (op.letters == opauli.X) | (op.letters == opauli.Y)
+    keep = flips[:, n_o:].any(axis=1) | (flips[:, :n_o].sum(axis=1) == 4)
+    op = opauli.PauliSum(2 * n_o, op.letters[keep], op.coeff[keep])
+    x, z = op.xz()
+    G = api.PauliSum.create(2 * n_o, x, z, op.coeff).canonicalize().group()
+    sp = api.Space.sector(n_o, na, nb)
+    psi_np = synth.random_state(sp.dim, seed + 1)
+    ref = oapply.apply_scatter(op, ospace.SectorSpace(n_o, na, nb), psi_np)
+    G.factor(sp)
+    psi = torch.from_numpy(psi_np).to(dev)
+    out = torch.empty_like(psi)
+    e = api.expval(G, sp, psi, out=out).cpu().numpy()
+    assert rel_err(out.cpu().numpy(), ref) < 1e-12
+    e_ref = np.vdot(psi_np, ref)
+    assert abs(e[0] - e_ref.real) < 1e-12 * max(1.0, abs(e_ref))
