@@ -51,7 +51,9 @@ constexpr uint32_t kPanelVBytes = (kPanelZero + 1u) * 16u;
 // LDS: the V tile, the image matrix and the classes' records; before them the
 // staged rows, then the list coefficients and sources, in the same place
 constexpr uint32_t kPanelMixBytes = kPanelVBytes + kPanelPairs * kPanelClasses * 8u + kPanelClasses * 32u;
-constexpr uint32_t kPanelPullBytes = kPanelPullSlots * 128u;  // after the classes' records
+// after the classes' records; slots are read kPanelPullRead at a time, past the last one too
+constexpr uint32_t kPanelPullRead = 4;
+constexpr uint32_t kPanelPullBytes = (kPanelPullSlots + kPanelPullRead - 1u) * 128u;
 
 // The panel kernel's variants: beta columns (512 per target column of a
 // lane), orbital pairs (32 per 16-pair tile of a wave), classes per row (four

@@ -384,20 +384,20 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
     uint32_t at = 0;  // byte offset of this lane's next entry
     auto pull = [&](int j) {
       const uint32_t n = ((j < 4 ? cw.x : cw.y) >> (8 * (j & 3))) & 255u;
-      for (uint32_t i = 0; i < n; i += 4) {
-        uint32_t e[4];
-        double2 v[4];
+      for (uint32_t i = 0; i < n; i += kPanelPullRead) {
+        uint32_t e[kPanelPullRead];
+        double2 v[kPanelPullRead];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (uint32_t q = 0; q < kPanelPullRead; ++q)
           e[q] = *reinterpret_cast<const uint16_t*>(smem + kPanelMixBytes + at + 128u * q);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = s_v[i + q < n ? e[q] & 0x1fffu : kPanelZero];
+        for (uint32_t q = 0; q < kPanelPullRead; ++q) v[q] = s_v[i + q < n ? e[q] & 0x1fffu : kPanelZero];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (uint32_t q = 0; q < kPanelPullRead; ++q) {
           ar[0][j] += signed_by_bit31(v[q].x, e[q] << 16);
           ai[0][j] += signed_by_bit31(v[q].y, e[q] << 16);
         }
-        at += 128u * min(n - i, 4u);
+        at += 128u * min(n - i, kPanelPullRead);
       }
     };
     auto counts = [&](uint32_t tile) {
