@@ -91,6 +91,17 @@ __device__ __forceinline__ double widen(double v) {
   return v;
 }
 
+// The same for operands of a matrix instruction, which must not read a register
+// in the two wait states after a vector instruction wrote it: the compiler keeps
+// that distance for instructions it knows, not for one inside an asm, so the asm
+// waits itself.
+__device__ __forceinline__ double widen_operand(float v) {
+  double d;
+  asm volatile("v_cvt_f64_f32 %0, %1\n\ts_nop 1" : "=v"(d) : "v"(v));
+  return d;
+}
+__device__ __forceinline__ double widen_operand(double v) { return widen(v); }
+
 // Software pipeline over entries 0 .. n - 1: the loads of D - 1 entries are in
 // flight while one is evaluated (past the end the last entry is loaded again).
 template <int D, class B, class L, class E>
@@ -422,7 +433,7 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
       for (int k = 0; k < KS; ++k) {
         // classes past the end hold the target row, which the X_alpha = 0
         // class reads too, against zeros
-        const double xr = widen(b[k].x), xi = widen(b[k].y);
+        const double xr = widen_operand(b[k].x), xi = widen_operand(b[k].y);
         load(tile + 1, k);
         double cur[MT];
 #pragma unroll
