@@ -951,10 +951,11 @@ pbs_status pbs_vqe_create(const pbs_grouped* h, uint32_t n_orb, uint32_t n_rot, 
       v->n_jobs = static_cast<uint32_t>(sps.size());
       // factor tables for the panel kernel: the alpha side depends on a
       // block's alpha string count alone and the beta side on its beta string
-      // count, so one plan per count serves all blocks
+      // count, so one plan per count serves all blocks (an operator without
+      // sector terms has no tables to make them from)
       v->plans.resize(n_orb + 1);
       std::vector<const FactorPlan*> pa(v->n_jobs, nullptr), pb(v->n_jobs, nullptr);
-      if (h->real_coef) {
+      if (h->real_coef && h->n_pterm != 0) {
         Scratch scratch(s);
         auto build = [&](uint32_t k) {  // false: the operator is not one for the panel kernel
           auto plan = make_factor_plan(*h, *v->spaces[k * (n_orb + 1) + k], false, s);

@@ -280,3 +280,16 @@ def test_vqe_tile_groups_match_single_rotations(dev, n_rot, dtype):
     tol_e, tol_g = (1e-12 * scale, 1e-11 * scale) if dtype == torch.complex128 else (2e-6 * scale, 4e-6 * scale)
     assert abs(e - e1) < tol_e and np.abs(g - g1).max() < tol_g
     assert (psi - v.state()).abs().max().item() < (1e-12 if dtype == torch.complex128 else 2e-6)
+
+
+@pytest.mark.parametrize("n_orb", [3, 4, 6])
+def test_vqe_of_the_zero_operator(dev, n_orb):
+    """An operator without terms: energy and gradient are exactly zero."""
+    api = _api()
+    h1 = torch.zeros(2 * n_orb, 2 * n_orb, dtype=torch.float64, device=dev)
+    h2 = torch.zeros((2 * n_orb,) * 4, dtype=torch.float64, device=dev)
+    G = api.jw_transform(h1, h2).group()
+    x, z = synth.excitation_masks(n_orb, 2, 1, 2)
+    v = api.VQE(G, n_orb, x, z, 0b011 | (0b001 << n_orb))
+    e, g = v.energy_grad(np.linspace(0.1, 0.4, len(x)))
+    assert e == 0.0 and np.all(np.asarray(g) == 0.0)
