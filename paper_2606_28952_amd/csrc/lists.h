@@ -126,8 +126,9 @@ __global__ __launch_bounds__(kLB) void k_apply_lists(SectorArgs P, ListsArgs L, 
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t n_list = a1 - a0;
   double e_re = 0.0, e_im = 0.0, nrm = 0.0;
-  // The row's columns with N gathers of the simple classes in flight (past the
-  // end of the list the first one is loaded again; a longer list ends in a loop).
+  // The row's columns with N gathers of the simple classes in flight, N even and
+  // the list no shorter than N - 1: where it has N - 1 entries the first is loaded
+  // again and left out of the sums, a longer list ends in a loop.
   // A column's entries are loaded first, then the gathers, which arrive while
   // the entries are evaluated: loads return in order.
   auto sweep = [&](auto ahead) {
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(kLB) void k_apply_lists(SectorArgs P, ListsArgs L, 
       asm volatile("" : "+s"(src), "+s"(coef));
 #pragma unroll
       for (uint32_t i = 0; i < N; ++i)
-        a[i] = psi_col[static_cast<uint64_t>(i < n_list ? ldc(src + i) : ldc(src)) * db];
+        a[i] = psi_col[static_cast<uint64_t>(i + 1 < N || i < n_list ? ldc(src + i) : ldc(src)) * db];
       __builtin_amdgcn_sched_barrier(0);
       auto column = [&](const Entries& e) {
 #pragma unroll
@@ -178,8 +179,8 @@ __global__ __launch_bounds__(kLB) void k_apply_lists(SectorArgs P, ListsArgs L, 
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (uint32_t i = 0; i < N; ++i) {
-        const double c = i < n_list ? ldc(coef + i) : 0.0;
-        Coef<true>::mac(c, widen(a[i].x), widen(a[i].y), ar[i & 3], ai[i & 3]);
+        if (i + 1 == N && i >= n_list) break;
+        Coef<true>::mac(ldc(coef + i), widen(a[i].x), widen(a[i].y), ar[i & 3], ai[i & 3]);
       }
       for (uint32_t e = a0 + N; e < a1; ++e) {
         const T v = psi_col[static_cast<uint64_t>(ldc(P.alist_src + e)) * db];
@@ -197,20 +198,20 @@ __global__ __launch_bounds__(kLB) void k_apply_lists(SectorArgs P, ListsArgs L, 
       }
     }
   };
-  if (n_list == 0)
-    sweep(std::integral_constant<uint32_t, 0>{});
-  else if (n_list <= 8)
-    sweep(std::integral_constant<uint32_t, 8>{});
-  else if (n_list <= 12 || sizeof(T) > 8)  // (registers: 20 gathers of 16 bytes spill)
-    sweep(std::integral_constant<uint32_t, 12>{});
-  else if (n_list <= 14)
-    sweep(std::integral_constant<uint32_t, 14>{});
-  else if (n_list <= 16)
-    sweep(std::integral_constant<uint32_t, 16>{});
-  else if (n_list <= 18)
-    sweep(std::integral_constant<uint32_t, 18>{});
-  else
-    sweep(std::integral_constant<uint32_t, 20>{});
+  constexpr uint32_t kAhead = sizeof(T) > 8 ? 12 : kListRowsAhead;  // (registers: 20 gathers of 16 bytes spill)
+  switch ((min(n_list, kAhead) + 1u) / 2u) {
+    case 0: sweep(std::integral_constant<uint32_t, 0>{}); break;
+    case 1: sweep(std::integral_constant<uint32_t, 2>{}); break;
+    case 2: sweep(std::integral_constant<uint32_t, 4>{}); break;
+    case 3: sweep(std::integral_constant<uint32_t, 6>{}); break;
+    case 4: sweep(std::integral_constant<uint32_t, 8>{}); break;
+    case 5: sweep(std::integral_constant<uint32_t, 10>{}); break;
+    case 6: sweep(std::integral_constant<uint32_t, 12>{}); break;
+    case 7: sweep(std::integral_constant<uint32_t, kAhead < 14 ? 0 : 14>{}); break;
+    case 8: sweep(std::integral_constant<uint32_t, kAhead < 16 ? 0 : 16>{}); break;
+    case 9: sweep(std::integral_constant<uint32_t, kAhead < 18 ? 0 : 18>{}); break;
+    default: sweep(std::integral_constant<uint32_t, kAhead < 20 ? 0 : 20>{}); break;
+  }
   if (EXPVAL) block_reduce3_store<kLB>(e_re, e_im, nrm, partial + 3ull * row);
 }
 

@@ -210,3 +210,30 @@ def test_lists_kernel_long_rows(dev, n, na, nb, dtype, kind):
     assert torch.equal(torch.view_as_real(torch.cat(parts)), torch.view_as_real(out))
     G.set_factored(5)  # without the move tables
     assert rel_err(api.apply_pauli_sum(G, sp, psi).cpu().numpy().astype(np.complex128), ref) < tol
+
+
+@pytest.mark.parametrize("n,na,nb,dtype", [(16, 1, 7, "c64"), (16, 2, 7, "c64"), (16, 2, 5, "c128")])
+def test_lists_kernel_infinite_amplitude(dev, n, na, nb, dtype):
+    """Rows of the lists kernel are summed from their own sources alone: where a
+    large amplitude gives a large sum, an infinite one gives that infinity, and
+    the other sums stay as they are."""
+    api = _api()
+    h1, h2 = _chain_integrals(n, "equal", np.random.default_rng(1))
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(n, na, nb)
+    G.factor(sp)
+    da, db = sp.shape()[3:5]
+    psi = torch.from_numpy(synth.random_state(sp.dim, 5)).to(dev)
+    psi = psi.to(torch.complex128 if dtype == "c128" else torch.complex64)
+    for row in range(min(da, 16)):
+        col = (37 * row) % db
+        outs = []
+        for value in (1e30, float("inf")):
+            torch.view_as_real(psi)[row * db + col, 0] = value
+            outs.append(torch.view_as_real(api.apply_pauli_sum(G, sp, psi)).reshape(da, db, 2))
+        torch.view_as_real(psi)[row * db + col, 0] = 0.25
+        others = torch.arange(da, device=dev) != row
+        big, inf = outs[0][others], outs[1][others]
+        large = big.abs() > 1e20
+        assert bool(large.any())
+        assert torch.equal(torch.where(large, big.sign() * float("inf"), big), inf), row
