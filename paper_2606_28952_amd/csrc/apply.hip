@@ -911,16 +911,15 @@ void fill_batch(pbs_batch& B, uint32_t config) {
                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
   }
   const uint32_t cus = device_cus();
-  // panel launches, the costliest variant first; a launch of several jobs
-  // takes full row blocks once they fill the device for some rounds
+  // panel launches, the costliest variant first
   std::vector<PanelJob> psorted;
   std::vector<pbs_batch::PanelLaunch> panels;
   for (int v = static_cast<int>(std::size(kPanelVariants)) - 1; v >= 0; --v) {
     const std::vector<uint32_t>& list = by_variant[v];
     if (list.empty()) continue;
-    const uint32_t r = kPanelVariants[v].rows;
-    uint64_t least = 0;
-    for (uint32_t i : list) least += (B.sp[i]->dim_alpha + r - 1) / r;
+    std::vector<std::pair<uint32_t, uint32_t>> sizes;
+    for (uint32_t i : list) sizes.emplace_back(pj[i].args.dim_alpha, pj[i].args.dim_beta);
+    const uint32_t r = panel_batch_rows(sizes, kPanelVariants[v].rows, cus);
     std::vector<double> pcost;
     std::vector<uint64_t> pitems;
     pbs_batch::PanelLaunch P;
@@ -928,7 +927,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
     P.first = static_cast<uint32_t>(psorted.size());
     P.n = static_cast<uint32_t>(list.size());
     for (uint32_t i : list) {
-      if (least >= 4ull * cus) pj[i].args.n_blk = (pj[i].args.dim_alpha + r - 1) / r;
+      pj[i].args.n_blk = (pj[i].args.dim_alpha + r - 1) / r;
       pj[i].args.row_end = pj[i].args.dim_alpha;
       pj[i].psi = B.psi[i];
       pj[i].out = B.out[i];

@@ -36,8 +36,29 @@ static void check_pull_region() {
         kPanelMixBytes + kPanelPullBytes);
 }
 
+// Rows per workgroup of a batch: between one and the variant's most; one where
+// every row finds a free compute unit, the most where many rounds follow, more
+// than one where single rows would take many rounds, and no more than leaves
+// whole rounds.
+static void check_batch_rows() {
+  using Jobs = std::vector<std::pair<uint32_t, uint32_t>>;
+  CHECK(panel_batch_rows(Jobs(3, {70, 70}), 4, 256) == 1, "210 rows on 256 units");
+  CHECK(panel_batch_rows(Jobs(16, {252, 252}), 4, 256) == 4, "4,032 rows in one round of four");
+  CHECK(panel_batch_rows(Jobs(64, {924, 924}), 4, 256) == 4, "59,136 rows");
+  CHECK(panel_batch_rows(Jobs(1, {3432, 3432}), 2, 256) == 2, "3,432 long rows, two at most");
+  CHECK(panel_batch_rows(Jobs(3, {252, 252}), 4, 256) == 3, "756 rows in one round of three");
+  for (uint32_t n = 1; n <= 40; n += 3)
+    for (uint32_t most : {2u, 4u}) {
+      Jobs jobs;
+      for (uint32_t i = 0; i < n; ++i) jobs.push_back({10 + 37 * i % 200, 20 + 53 * i % 400});
+      const uint32_t r = panel_batch_rows(jobs, most, 256);
+      CHECK(r >= 1 && r <= most, "%u jobs: %u rows of %u", n, r, most);
+    }
+}
+
 int main() {
   check_pull_region();
+  check_batch_rows();
   if (g_fail) return 1;
   std::printf("all panel plan checks passed\n");
   return 0;
