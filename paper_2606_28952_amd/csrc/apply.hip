@@ -504,10 +504,12 @@ bool plan_lists(const pbs_grouped& h, const pbs_space& sp, const SectorArgs& a, 
 struct PanelShape {
   int variant = 0;  // of kPanelVariants
   size_t lds = 0;
+  double fill = 0.0;  // see panel_fill
 };
 
 // Arguments and shape of the panel kernel when the operator's factor tables
-// allow it for this sector and every factored part is switched on.  The
+// allow it for this sector and every factored part is switched on (whether it is
+// the faster one there says panel_pays).  The
 // alpha side (lists, images) and the beta side (move coefficients, F rows,
 // gather entries) may come from two plans of the same operator.
 bool plan_panel(const pbs_grouped& h, const pbs_space& sp, const FactorPlan* A, const FactorPlan* F, PanelArgs* out,
@@ -523,6 +525,7 @@ bool plan_panel(const pbs_grouped& h, const pbs_space& sp, const FactorPlan* A, 
   a.dim_alpha = static_cast<uint32_t>(sp.dim_alpha);
   a.dim_beta = static_cast<uint32_t>(sp.dim_beta);
   const PanelVariant& v = kPanelVariants[shape->variant];
+  shape->fill = panel_fill(shape->variant, sp.n_alpha * (sp.n_orb - sp.n_alpha), sp.n_beta * (sp.n_orb - sp.n_beta));
   a.n_blk = panel_blocks(a.dim_alpha, v.rows, device_cus());
   a.n_tiles = F->n_tiles;
   a.n_img = F->n_img;
@@ -592,7 +595,9 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     if (o) o = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(o) - row_begin * sp.dim_beta * sizeof(T));
     PanelArgs pa;
     PanelShape ps;
-    if (plan_panel(h, sp, h.fplan.get(), h.fplan.get(), &pa, &ps)) {
+    // (the whole sector decides, so that a share of its rows runs the same kernel)
+    if (plan_panel(h, sp, h.fplan.get(), h.fplan.get(), &pa, &ps) &&
+        panel_pays(ps.variant, sp.dim_alpha, sp.dim_beta, ps.fill, sizeof(T), device_cus())) {
       pa.row_begin = static_cast<uint32_t>(row_begin);
       pa.row_end = static_cast<uint32_t>(row_end);
       pa.skip = skip;
@@ -839,15 +844,25 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   const bool given = config & PBS_BATCH_GIVEN_ORDER, allow_row = !(config & PBS_BATCH_NO_ROW_STAGING);
   const bool qenum = !(config & PBS_BATCH_NO_DOUBLE_MOVES), penum = !(config & PBS_BATCH_NO_SINGLE_MOVES);
   const bool factd = !(config & PBS_BATCH_NO_FACTORED);
-  // jobs that a single launch gives to the panel kernel run on it here too,
-  // unless a flag asks for another evaluation
+  // jobs run on the panel kernel where that pays for all jobs of a variant
+  // together, unless a flag asks for another evaluation; tables that the batch's
+  // owner brought serve no other kernel
+  const uint32_t cus = device_cus();
   std::vector<PanelJob> pj(n);
   std::vector<PanelShape> shape(n);
+  std::vector<char> can(n, 0);
   std::vector<uint32_t> sector;
   std::vector<std::vector<uint32_t>> by_variant(std::size(kPanelVariants));
+  std::vector<uint64_t> variant_rows(std::size(kPanelVariants), 0);
+  for (uint32_t i = 0; i < n && allow_row && qenum && penum && factd; ++i) {
+    can[i] = plan_panel(*B.h[i], *B.sp[i], B.alpha_plan(i), B.beta_plan(i), &pj[i].args, &shape[i]);
+    if (can[i]) variant_rows[shape[i].variant] += B.sp[i]->dim_alpha;
+  }
   for (uint32_t i = 0; i < n; ++i) {
-    if (allow_row && qenum && penum && factd && plan_panel(*B.h[i], *B.sp[i], B.alpha_plan(i), B.beta_plan(i), &pj[i].args, &shape[i]))
-      by_variant[shape[i].variant].push_back(i);
+    const PanelShape& ps = shape[i];
+    if (can[i] && (!B.plan_a.empty() || panel_pays(ps.variant, variant_rows[ps.variant], B.sp[i]->dim_beta, ps.fill,
+                                                   static_cast<uint32_t>(esz), cus)))
+      by_variant[ps.variant].push_back(i);
     else
       sector.push_back(i);
   }
@@ -910,7 +925,6 @@ void fill_batch(pbs_batch& B, uint32_t config) {
       PBS_HIP(hipFuncSetAttribute(sector_kernel(B.dt, ev, true, r16, rowlds, realc),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
   }
-  const uint32_t cus = device_cus();
   // panel launches, the costliest variant first
   std::vector<PanelJob> psorted;
   std::vector<pbs_batch::PanelLaunch> panels;

@@ -86,6 +86,42 @@ inline int panel_variant_for(uint64_t rows, uint64_t cols, uint32_t pairs, uint3
   return -1;
 }
 
+// Share of a variant's padded products (classes x pairs) that a target row's
+// image classes and a target's single beta moves use.
+inline double panel_fill(int variant, uint32_t alpha_hops, uint32_t beta_hops) {
+  const PanelVariant& p = kPanelVariants[variant];
+  return static_cast<double>(alpha_hops) * beta_hops / (static_cast<double>(p.classes) * p.pairs);
+}
+
+// Whether the panel kernel is the faster one for a sector of `cols` beta strings
+// in a launch of `rows` rows, all jobs of the variant together; elem: bytes of an
+// amplitude.  It takes one workgroup per row, or a few rows, and pays for the
+// padding of its products; the sector kernel takes 512 columns per workgroup, so
+// it fills the device with fewer rows, and its work follows the moves that exist.
+// Sector kernel against panel kernel, one launch, us:
+//  * narrow rows, one per workgroup, are short either way: (12; 3, 3) complex64
+//    87 against 77, (11; 2, 5) 75 against 66.  A second row for some workgroups
+//    doubles the panel kernel's time: (14; 3, 3), 364 rows, complex64 175 / 180,
+//    complex128 211 / 189.  495 columns of 12 orbitals: (12; 3, 4) complex64
+//    101 / 111, complex128 118 / 116; eight jobs of (12; 4, 4) complex64 1,329 / 1,475
+//  * long rows, fewer than compute units: (14; 1, 7) complex64 117 / 600, (14; 2, 7)
+//    complex64 355 / 642, complex128 472 / 648; (12; 3, 6), 220 rows, complex64
+//    166 / 181, complex128 214 / 171
+//  * and more of them: (13; 3, 5), fill 0.28, complex64 390 / 424, (13; 3, 6), 0.30,
+//    518 / 506, (14; 3, 4), 1,001 columns, 330 / 349; with 495 and more rows at 0.29
+//    to 0.38 1.03 to 1.8 times as fast ((13; 5, 4) alone 0.99); 24 jobs of (14; 1, 7),
+//    0.13, 1,027 / 1,190, six of (14; 2, 7), 0.24, 1,749 / 2,048, six of (12; 3, 6),
+//    0.25, 894 / 849; complex128 faster throughout (gathers of 16 bytes)
+inline bool panel_pays(int variant, uint64_t rows, uint64_t cols, double fill, uint32_t elem, uint32_t cus) {
+  if (variant == 0) return true;
+  const bool narrow = cols <= 400;
+  if (elem > 8) return narrow || 4 * rows >= 3ull * cus;
+  const bool many = 2 * rows >= 3ull * cus;
+  if (cols <= kPanelLanes) return narrow && (many || rows <= cus);
+  if (many) return fill >= 0.25;
+  return rows > cus && cols > 2 * kPanelLanes && fill >= 0.29;
+}
+
 // Row blocks that split dim_alpha rows evenly into at most `rows` each:
 // as few as that allows, rounded up to whole rounds of one workgroup per
 // compute unit (one row each when there are fewer rows than units).

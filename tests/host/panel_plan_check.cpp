@@ -19,6 +19,12 @@ static int g_fail = 0;
     }                                                           \
   } while (0)
 
+static uint64_t binomial(uint32_t n, uint32_t k) {
+  uint64_t c = 1;
+  for (uint32_t i = 1; i <= k; ++i) c = c * (n - k + i) / i;
+  return c;
+}
+
 // A group of n >= 1 slots that ends with slot `end` of a full tile is read
 // kPanelPullRead slots at a time from its first one: every read lies in the
 // region, which lies in the LDS of a compute unit.
@@ -56,8 +62,41 @@ static void check_batch_rows() {
     }
 }
 
+// Sectors of n orbitals, a alpha and b beta, that one launch gives to the panel
+// kernel (1) or leaves to the sector kernel (0), complex64 and complex128: the
+// sizes on both sides of every line of panel_pays, 256 compute units.
+static void check_panel_pays() {
+  struct Case {
+    uint32_t n, a, b, jobs;
+    int c64, c128;
+  };
+  const Case cases[] = {
+      {4, 2, 2, 1, 1, 1},   {11, 2, 5, 1, 1, 1},  {11, 5, 6, 1, 1, 1},  {12, 2, 3, 1, 1, 1},  {12, 3, 3, 1, 1, 1},
+      {13, 3, 3, 1, 0, 1},  {14, 3, 3, 1, 0, 1},  {14, 1, 3, 1, 1, 1},  {12, 1, 4, 1, 0, 0},  {12, 3, 4, 1, 0, 1},
+      {12, 4, 4, 1, 0, 1},  {12, 1, 6, 1, 0, 0},  {12, 2, 6, 1, 0, 0},  {12, 3, 6, 1, 0, 1},  {12, 4, 6, 1, 1, 1},
+      {12, 6, 6, 1, 1, 1},  {13, 1, 6, 1, 0, 0},  {13, 2, 6, 1, 0, 0},  {13, 3, 5, 1, 0, 1},  {13, 3, 6, 1, 1, 1},
+      {13, 4, 4, 1, 1, 1},  {14, 1, 7, 1, 0, 0},  {14, 2, 7, 1, 0, 0},  {14, 3, 4, 1, 0, 1},  {14, 3, 7, 1, 1, 1},
+      {14, 7, 7, 1, 1, 1},  {14, 1, 7, 6, 0, 0},  {14, 1, 7, 24, 0, 1}, {14, 2, 7, 6, 0, 1},  {12, 3, 6, 6, 1, 1},
+      {12, 4, 4, 8, 0, 1},  {14, 3, 3, 6, 1, 1},  {12, 2, 3, 12, 1, 1}, {13, 3, 5, 6, 1, 1},
+  };
+  for (const Case& c : cases) {
+    const uint64_t rows = binomial(c.n, c.a), cols = binomial(c.n, c.b);
+    const int v = panel_variant_for(rows, cols, c.n * (c.n - 1) / 2, c.a * (c.n - c.a) + 1);
+    CHECK(v >= 0, "(%u; %u, %u) has no variant", c.n, c.a, c.b);
+    if (v < 0) continue;
+    const double fill = panel_fill(v, c.a * (c.n - c.a), c.b * (c.n - c.b));
+    CHECK(fill > 0.0 && fill < 1.0, "(%u; %u, %u) fill %g", c.n, c.a, c.b, fill);
+    for (uint32_t elem : {8u, 16u}) {
+      const int want = elem == 8 ? c.c64 : c.c128;
+      CHECK(panel_pays(v, rows * c.jobs, cols, fill, elem, 256) == (want != 0), "%u x (%u; %u, %u), %u bytes: want %d",
+            c.jobs, c.n, c.a, c.b, elem, want);
+    }
+  }
+}
+
 int main() {
   check_pull_region();
+  check_panel_pays();
   check_batch_rows();
   if (g_fail) return 1;
   std::printf("all panel plan checks passed\n");
