@@ -2,6 +2,7 @@
 // sectors Eq. sreverse_sum) and the fused energy of Eq. vqe_energy: the
 // full-space kernel, launch planning of the sector kernels (whose device code
 // lives in sector.h), and the C ABI entry points, single and batched.
+#include <atomic>
 #include <iterator>
 #include <memory>
 #include <mutex>
@@ -47,7 +48,7 @@ __device__ inline void walsh(double (&f)[R]) {
       }
 }
 
-template <class T, bool EXPVAL, int R>
+template <class T, bool EXPVAL, int R, bool QUEUED>
 __global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_t n_groups,
                                                            const uint64_t* __restrict__ xg,
                                                            const uint32_t* __restrict__ off,
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_
                                                            const double* __restrict__ ck, const T* __restrict__ psi,
                                                            T* __restrict__ out, double* __restrict__ partial,
                                                            const uint32_t* skip) {
-  if (skip && *skip) return;
+  if (QUEUED && *skip) return;  // see Form
   constexpr uint32_t kTile = kFullLanes * R;
   __shared__ T s_psi[kTile];
   const uint32_t tid = threadIdx.x;
@@ -244,13 +245,22 @@ int device_lds_limit() {
   return v;
 }
 
+// Compute units of the current device (asked once per device: the query takes as
+// long as the difference between two kernels of a small launch).
 uint32_t device_cus() {
+  static std::atomic<int> known[64];
   int dev = 0, v = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) {
+  if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();
     return 256;
   }
+  const bool listed = dev >= 0 && dev < 64;
+  if (listed && (v = known[dev].load(std::memory_order_relaxed)) > 0) return static_cast<uint32_t>(v);
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  if (listed) known[dev].store(v, std::memory_order_relaxed);
   return static_cast<uint32_t>(v);
 }
 
@@ -558,10 +568,12 @@ bool plan_panel(const pbs_grouped& h, const pbs_space& sp, const FactorPlan* A, 
 // Launches the apply (EXPVAL: with the energy partials) for target alpha
 // rows [row_begin, row_end) of a sector space (the whole space by default);
 // out holds those rows only, from row_begin's first column.  Returns the
-// number of energy partials written.  skip: see SectorArgs::skip.
-template <class T, bool EXPVAL>
+// number of energy partials written.  QUEUED: see Form; nothing is done when
+// *skip is not zero.
+template <class T, bool EXPVAL, bool QUEUED = false>
 uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void* out, double* partial,
                 hipStream_t s, uint64_t row_begin = 0, uint64_t row_end = ~0ull, const uint32_t* skip = nullptr) {
+  constexpr Form form = QUEUED ? Form::kQueued : Form::kSingle;
   const T* p = static_cast<const T*>(psi);
   T* o = static_cast<T*>(out);
   if (!sp.sector) {
@@ -576,10 +588,10 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
       return static_cast<uint64_t>(grid);
     };
     if constexpr (sizeof(T) == 8)
-      if (lanes >= 8 * want) return go(k_apply_full<T, EXPVAL, 8>, 8);
-    if (lanes >= 4 * want) return go(k_apply_full<T, EXPVAL, 4>, 4);
-    if (lanes >= 2 * want) return go(k_apply_full<T, EXPVAL, 2>, 2);
-    return go(k_apply_full<T, EXPVAL, 1>, 1);
+      if (lanes >= 8 * want) return go(k_apply_full<T, EXPVAL, 8, QUEUED>, 8);
+    if (lanes >= 4 * want) return go(k_apply_full<T, EXPVAL, 4, QUEUED>, 4);
+    if (lanes >= 2 * want) return go(k_apply_full<T, EXPVAL, 2, QUEUED>, 2);
+    return go(k_apply_full<T, EXPVAL, 1, QUEUED>, 1);
   } else {
     SectorArgs a;
     bool r16 = false;
@@ -589,7 +601,6 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     const uint64_t rows = row_end - row_begin;
     if (rows == 0) return 0;
     a.row_begin = static_cast<uint32_t>(row_begin);
-    a.skip = skip;
     // the kernels store target t = row * dim_beta + column at out[t]: shift
     // the base so that row_begin's first column lands at out[0]
     if (o) o = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(o) - row_begin * sp.dim_beta * sizeof(T));
@@ -600,13 +611,12 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
         panel_pays(ps.variant, sp.dim_alpha, sp.dim_beta, ps.fill, sizeof(T), device_cus())) {
       pa.row_begin = static_cast<uint32_t>(row_begin);
       pa.row_end = static_cast<uint32_t>(row_end);
-      pa.skip = skip;
       // the blocks that hold rows row_begin and row_end - 1
       auto block_of = [&](uint64_t row) { return static_cast<uint32_t>(((row + 1) * pa.n_blk - 1) / pa.dim_alpha); };
       pa.blk0 = block_of(row_begin);
       const uint32_t blocks = block_of(row_end - 1) - pa.blk0 + 1u;
-      void* kern = panel_kernel(dt, EXPVAL, false, ps.variant);
-      void* args[] = {&pa, &p, &o, &partial};
+      void* kern = panel_kernel(dt, EXPVAL, form, ps.variant);
+      void* args[] = {&pa, &p, &o, &partial, &skip};
       PBS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(ps.lds)));
       PBS_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(kPanelLanes), args, ps.lds, s));
       return rows;
@@ -614,9 +624,9 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     ListsArgs la;
     size_t lds_rows = 0;
     if (h.real_coef && plan_lists(h, sp, a, r16, sizeof(T), &la, &lds_rows)) {
-      void* kern = h.fplan->bl_narrow ? reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, true>)
-                                 : reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, false>);
-      void* args[] = {&a, &la, &p, &o, &partial};
+      void* kern = h.fplan->bl_narrow ? reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, true, QUEUED>)
+                                 : reinterpret_cast<void*>(k_apply_lists<T, EXPVAL, false, QUEUED>);
+      void* args[] = {&a, &la, &p, &o, &partial, &skip};
       PBS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_rows)));
       PBS_HIP(hipLaunchKernel(kern, dim3(static_cast<unsigned>(rows)), dim3(kLB), args, lds_rows, s));
       return rows;
@@ -624,15 +634,15 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     RowsLayout Lr;
     if (h.real_coef && plan_rows(h, a, r16, EXPVAL, &Lr, &lds_rows)) {
       // one workgroup per alpha row, sweeping all of its columns
-      hipLaunchKernelGGL((k_apply_rows<T, EXPVAL>), dim3(static_cast<unsigned>(rows)), dim3(kSB), lds_rows, s, a, Lr,
-                         p, o, partial);
+      hipLaunchKernelGGL((k_apply_rows<T, EXPVAL, QUEUED>), dim3(static_cast<unsigned>(rows)), dim3(kSB), lds_rows, s,
+                         a, Lr, p, o, partial, skip);
       PBS_HIP(hipGetLastError());
       return rows;
     }
-    void* kern = sector_kernel(dt, EXPVAL, false, r16, a.row_lds != 0, h.real_coef);
+    void* kern = sector_kernel(dt, EXPVAL, form, r16, a.row_lds != 0, h.real_coef);
     if (L.lds > 64 * 1024)
       PBS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(L.lds)));
-    void* args[] = {&a, &p, &o, &partial};
+    void* args[] = {&a, &p, &o, QUEUED ? static_cast<void*>(&skip) : static_cast<void*>(&partial)};
     const uint64_t parts = rows * L.chunks;
     PBS_HIP(hipLaunchKernel(kern, dim3(static_cast<unsigned>(parts)), L.block, args, L.lds, s));
     PBS_HIP(hipGetLastError());
@@ -648,9 +658,9 @@ void apply_launch(const pbs_grouped& h, const pbs_space& sp, pbs_dtype dt, const
                   const uint32_t* skip) {
   validate(&h, &sp, dt);
   if (dt == PBS_C128)
-    launch<double2, false>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
+    launch<double2, false, true>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
   else
-    launch<float2, false>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
+    launch<float2, false, true>(h, sp, psi, out, nullptr, s, 0, ~0ull, skip);
 }
 
 }  // namespace pbs
@@ -922,7 +932,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   }
   if (lds > 64 * 1024) {
     for (bool ev : {false, true})
-      PBS_HIP(hipFuncSetAttribute(sector_kernel(B.dt, ev, true, r16, rowlds, realc),
+      PBS_HIP(hipFuncSetAttribute(sector_kernel(B.dt, ev, Form::kBatch, r16, rowlds, realc),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
   }
   // panel launches, the costliest variant first
@@ -961,7 +971,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
     P.items = static_cast<uint32_t>(pp.total);
     P.grid = config & PBS_BATCH_PERSISTENT ? std::min(P.items, cus) : P.items;  // one workgroup per compute unit
     for (bool ev : {false, true})
-      PBS_HIP(hipFuncSetAttribute(panel_kernel(B.dt, ev, true, v), hipFuncAttributeMaxDynamicSharedMemorySize,
+      PBS_HIP(hipFuncSetAttribute(panel_kernel(B.dt, ev, Form::kBatch, v), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(P.lds)));
     panels.push_back(P);
   }
@@ -987,7 +997,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
     // as many workgroups as are resident at once (both kernel forms share
     // their resources); each walks the item list with a fixed stride
     int per_cu = 0;
-    PBS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sector_kernel(B.dt, false, true, r16, rowlds, realc),
+    PBS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sector_kernel(B.dt, false, Form::kBatch, r16, rowlds, realc),
                                                          kSB, lds));
     const uint64_t resident = static_cast<uint64_t>(cus) * static_cast<uint64_t>(std::max(per_cu, 1));
     B.grid = static_cast<uint32_t>(std::min<uint64_t>(B.sector_items, resident));
@@ -1002,7 +1012,7 @@ void launch_batch(const pbs_batch& b, double* energies, hipStream_t s) {
   const bool ev = energies != nullptr;
   double* partial = b.partial.get();
   if (b.n_sector) {
-    void* kern = sector_kernel(b.dt, ev, true, b.r16, b.row_lds, b.realc);
+    void* kern = sector_kernel(b.dt, ev, Form::kBatch, b.r16, b.row_lds, b.realc);
     const BatchJob* jobs = b.jobs.get();
     uint32_t n = b.n_sector, items = b.sector_items;
     void* args[] = {&jobs, &n, &items, &partial};
@@ -1012,7 +1022,7 @@ void launch_batch(const pbs_batch& b, double* energies, hipStream_t s) {
     const PanelJob* jobs = b.pjobs.get() + P.first;
     uint32_t n = P.n, items = P.items;
     void* args[] = {&jobs, &n, &items, &partial};
-    PBS_HIP(hipLaunchKernel(panel_kernel(b.dt, ev, true, P.variant), dim3(P.grid), dim3(kPanelLanes), args, P.lds, s));
+    PBS_HIP(hipLaunchKernel(panel_kernel(b.dt, ev, Form::kBatch, P.variant), dim3(P.grid), dim3(kPanelLanes), args, P.lds, s));
   }
   if (ev) {
     hipLaunchKernelGGL(k_batch_finish, dim3(b.n_jobs), dim3(kBlock), 0, s, b.finish.get(), partial, energies);

@@ -76,12 +76,13 @@ struct ColumnEntries<false> {
   __device__ uint32_t mag(int i) const { return (word(i) >> 16) & 0x7fffu; }
 };
 
-template <class T, bool EXPVAL, bool ONE>
+template <class T, bool EXPVAL, bool ONE, bool QUEUED>
 __global__ __launch_bounds__(kLB) void k_apply_lists(SectorArgs P, ListsArgs L, const T* __restrict__ psi,
-                                                     T* __restrict__ out, double* __restrict__ partial) {
+                                                     T* __restrict__ out, double* __restrict__ partial,
+                                                     const uint32_t* skip) {
   extern __shared__ __align__(16) unsigned char smem[];
   using Entries = ColumnEntries<ONE>;
-  if (P.skip && *P.skip) return;
+  if (QUEUED && *skip) return;  // see Form
   const uint32_t row = lists_row_of(blockIdx.x, gridDim.x);
   const uint32_t ia = row + P.row_begin, db = P.dim_beta;
   T* s_row = reinterpret_cast<T*>(smem);  // [db + 1]: an absent entry reads the zero behind the row

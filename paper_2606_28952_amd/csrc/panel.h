@@ -73,7 +73,6 @@ struct PanelArgs {
   const uint4* pull;         // per tile, wave and target group: slots of 64 two-byte entries
   const uint4* pull_cnt;     // [n_tiles][waves]: slots per target group (a byte each, x and y), first slot of the
                              // wave in its tile (z), first slot of the tile (w)
-  const uint32_t* skip;      // nothing is done when this is set and not zero
 };
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -125,9 +124,11 @@ __device__ __forceinline__ void pipelined(uint32_t n, B (&buf)[D], const L& load
 // NT kPB); MT: 16-pair tiles per wave (n_pairs <= 32 MT); KS: K steps of four
 // classes (at most 4 KS - 1 image classes per row).
 // Args: PanelArgs, as kernel argument or in the constant address space.
-template <class T, bool EXPVAL, int NT, int MT, int KS, int R, class Args>
+// QUEUED: nothing is done when *stop is not zero.
+template <class T, bool EXPVAL, int NT, int MT, int KS, int R, bool QUEUED, class Args>
 __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ psi, T* __restrict__ out,
-                                           double* __restrict__ slot, uint32_t ia, uint32_t nr) {
+                                           double* __restrict__ slot, uint32_t ia, uint32_t nr,
+                                           const uint32_t* stop = nullptr) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -156,7 +157,7 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
         const T* rowg = psi + static_cast<uint64_t>(ia + g + r) * db;
         for (uint32_t c = tid; c < db; c += kPB) s_st[c * kS + r] = rowg[c];
       }
-    const bool skip = g == 0 && P.skip && *P.skip;
+    const bool skip = QUEUED && g == 0 && *stop != 0;
     __syncthreads();
     if (skip) return;
     // beta-only part, two moves per step, the next two loading
@@ -503,14 +504,14 @@ __device__ inline uint32_t panel_block_of(uint32_t w, uint32_t n) {
 // Workgroup w: the target rows of one of the n_blk row blocks that split the
 // sector's rows evenly, the blocks from blk0 on, that lie in [row_begin,
 // row_end).
-template <class T, bool EXPVAL, int NT, int MT, int KS, int R>
+template <class T, bool EXPVAL, int NT, int MT, int KS, int R, bool QUEUED>
 __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_panel(
-    PanelArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial) {
+    PanelArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial, const uint32_t* skip) {
   const uint64_t b = P.blk0 + panel_block_of(blockIdx.x, gridDim.x);
   const uint32_t r0 = max(static_cast<uint32_t>(b * P.dim_alpha / P.n_blk), P.row_begin);
   const uint32_t r1 = min(static_cast<uint32_t>((b + 1) * P.dim_alpha / P.n_blk), P.row_end);
   if (r1 > r0)
-    panel_body<T, EXPVAL, NT, MT, KS, R>(P, psi, out, partial + 3ull * (r0 - P.row_begin), r0, r1 - r0);
+    panel_body<T, EXPVAL, NT, MT, KS, R, QUEUED>(P, psi, out, partial + 3ull * (r0 - P.row_begin), r0, r1 - r0, skip);
 }
 
 // A job of a batched launch of one panel variant.
@@ -542,35 +543,36 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint64_t b = panel_block_of(w - J.block_base, J.args.n_blk);
     const uint32_t r0 = static_cast<uint32_t>(b * J.args.dim_alpha / J.args.n_blk);
     const uint32_t r1 = static_cast<uint32_t>((b + 1) * J.args.dim_alpha / J.args.n_blk);
-    panel_body<T, EXPVAL, NT, MT, KS, R>(J.args, static_cast<const T*>(J.psi), static_cast<T*>(J.out),
+    panel_body<T, EXPVAL, NT, MT, KS, R, false>(J.args, static_cast<const T*>(J.psi), static_cast<T*>(J.out),
                                          partial + 3ull * (J.first + r0), r0, r1 - r0);
   }
 }
 
 template <class T, int NT, int MT, int KS, int R>
-void* panel_variant(bool expval, bool batch) {
-  if (batch)
+void* panel_variant(bool expval, Form form) {
+  if (form == Form::kBatch)
     return expval ? reinterpret_cast<void*>(k_apply_panel_batch<T, true, NT, MT, KS, R>)
                   : reinterpret_cast<void*>(k_apply_panel_batch<T, false, NT, MT, KS, R>);
-  return expval ? reinterpret_cast<void*>(k_apply_panel<T, true, NT, MT, KS, R>)
-                : reinterpret_cast<void*>(k_apply_panel<T, false, NT, MT, KS, R>);
+  if (form == Form::kQueued) return reinterpret_cast<void*>(k_apply_panel<T, false, NT, MT, KS, R, true>);
+  return expval ? reinterpret_cast<void*>(k_apply_panel<T, true, NT, MT, KS, R, false>)
+                : reinterpret_cast<void*>(k_apply_panel<T, false, NT, MT, KS, R, false>);
 }
 
 }  // namespace
 
 // Kernel of a shape (PanelShape::variant); each storage type and half of the
 // variants is defined in its own translation unit (panel_<storage>_<width>.hip).
-void* panel_kernel_c64_narrow(bool expval, bool batch, int variant);
-void* panel_kernel_c64_wide(bool expval, bool batch, int variant);
-void* panel_kernel_c128_narrow(bool expval, bool batch, int variant);
-void* panel_kernel_c128_wide(bool expval, bool batch, int variant);
+void* panel_kernel_c64_narrow(bool expval, Form form, int variant);
+void* panel_kernel_c64_wide(bool expval, Form form, int variant);
+void* panel_kernel_c128_narrow(bool expval, Form form, int variant);
+void* panel_kernel_c128_wide(bool expval, Form form, int variant);
 
-inline void* panel_kernel(pbs_dtype dt, bool expval, bool batch, int variant) {
+inline void* panel_kernel(pbs_dtype dt, bool expval, Form form, int variant) {
   if (variant >= kPanelWide)
-    return dt == PBS_C128 ? panel_kernel_c128_wide(expval, batch, variant)
-                          : panel_kernel_c64_wide(expval, batch, variant);
-  return dt == PBS_C128 ? panel_kernel_c128_narrow(expval, batch, variant)
-                        : panel_kernel_c64_narrow(expval, batch, variant);
+    return dt == PBS_C128 ? panel_kernel_c128_wide(expval, form, variant)
+                          : panel_kernel_c64_wide(expval, form, variant);
+  return dt == PBS_C128 ? panel_kernel_c128_narrow(expval, form, variant)
+                        : panel_kernel_c64_narrow(expval, form, variant);
 }
 
 }  // namespace pbs

@@ -4,12 +4,12 @@
 
 namespace pbs {
 
-void* panel_kernel_c128_narrow(bool expval, bool batch, int variant) {
+void* panel_kernel_c128_narrow(bool expval, Form form, int variant) {
   switch (variant) {
-    case 0: return panel_variant<double2, 1, 2, 8, 4>(expval, batch);
-    case 1: return panel_variant<double2, 1, 3, 13, 4>(expval, batch);
-    case 2: return panel_variant<double2, 2, 3, 10, 4>(expval, batch);
-    default: return panel_variant<double2, 2, 3, 13, 4>(expval, batch);
+    case 0: return panel_variant<double2, 1, 2, 8, 4>(expval, form);
+    case 1: return panel_variant<double2, 1, 3, 13, 4>(expval, form);
+    case 2: return panel_variant<double2, 2, 3, 10, 4>(expval, form);
+    default: return panel_variant<double2, 2, 3, 13, 4>(expval, form);
   }
 }
 

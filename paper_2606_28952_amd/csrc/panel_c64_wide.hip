@@ -4,11 +4,11 @@
 
 namespace pbs {
 
-void* panel_kernel_c64_wide(bool expval, bool batch, int variant) {
+void* panel_kernel_c64_wide(bool expval, Form form, int variant) {
   switch (variant) {
-    case 4: return panel_variant<float2, 4, 3, 11, 4>(expval, batch);
-    case 5: return panel_variant<float2, 4, 3, 13, 4>(expval, batch);
-    default: return panel_variant<float2, 7, 3, 13, 2>(expval, batch);
+    case 4: return panel_variant<float2, 4, 3, 11, 4>(expval, form);
+    case 5: return panel_variant<float2, 4, 3, 13, 4>(expval, form);
+    default: return panel_variant<float2, 7, 3, 13, 2>(expval, form);
   }
 }
 

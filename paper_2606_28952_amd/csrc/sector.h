@@ -40,6 +40,11 @@
 #include "handles.h"
 
 namespace pbs {
+
+// How an apply kernel is launched: on its own, over a batch's jobs, or (plain
+// product only) in a queue with a skip flag.
+enum class Form { kSingle, kBatch, kQueued };
+
 namespace {
 
 constexpr int kBlock = 256;
@@ -261,7 +266,6 @@ struct SectorArgs {
   const double* fp;
   const uint32_t* eq;
   const double* fq;
-  const uint32_t* skip;  // nothing is done when this is set and not zero
 };
 
 // Combinatorial rank of a spin string: uint16 tables in LDS (n_orb <= 16,
@@ -589,10 +593,13 @@ __device__ __forceinline__ void stage_row(T* s_row, const T* rowg, uint32_t db, 
 
 // One workgroup: target alpha string ia (one row of the state), beta columns
 // chunk*kSB .. chunk*kSB + kSB - 1, one target per lane.  See the file header
-// for the scheme.  `slot` receives the workgroup's energy partials.
-template <class T, bool EXPVAL, bool R16, bool ROWLDS, bool REALC>
+// for the scheme.  `slot` receives the workgroup's energy partials.  QUEUED:
+// nothing is done when *skip is not zero (a template argument, since the test
+// costs every other launch 1 to 4% of a short kernel).
+template <class T, bool EXPVAL, bool R16, bool ROWLDS, bool REALC, bool QUEUED = false>
 __device__ __forceinline__ void sector_body(const SectorArgs& P, const T* __restrict__ psi, T* __restrict__ out,
-                                            double* __restrict__ slot, uint64_t ia, uint32_t chunk) {
+                                            double* __restrict__ slot, uint64_t ia, uint32_t chunk,
+                                            const uint32_t* skip = nullptr) {
   using C = Coef<REALC>;
   using V = typename C::V;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -636,9 +643,9 @@ __device__ __forceinline__ void sector_body(const SectorArgs& P, const T* __rest
     s_Fz[f_cap + threadIdx.x] = 0u;
   }
   // (read among the prologue's loads: in front of them it costs 0.2 us a launch)
-  const bool skip = P.skip && *P.skip;
+  const bool skipped = QUEUED && *skip != 0;
   __syncthreads();
-  if (skip) return;
+  if (skipped) return;
 
   const uint32_t db = P.dim_beta;
   const uint32_t col = chunk * kSB + threadIdx.x;
@@ -1171,11 +1178,12 @@ struct RowsLayout {
   uint32_t off_rank, off_lsrc, off_lc, off_cls, off_grp, off_f, off_fz, off_e;
 };
 
-template <class T, bool EXPVAL>
+template <class T, bool EXPVAL, bool QUEUED>
 __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 8 : 1, 8))) void k_apply_rows(SectorArgs P, RowsLayout Lr, const T* __restrict__ psi,
-                                                    T* __restrict__ out, double* __restrict__ partial) {
+                                                    T* __restrict__ out, double* __restrict__ partial,
+                                                    const uint32_t* skip) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (P.skip && *P.skip) return;
+  if (QUEUED && *skip) return;
   const uint32_t ia = blockIdx.x + P.row_begin;
   const uint64_t db = P.dim_beta;
   uint16_t* s_rank = reinterpret_cast<uint16_t*>(smem + Lr.off_rank);
@@ -1325,6 +1333,17 @@ __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   sector_body<T, EXPVAL, R16, ROWLDS, REALC>(P, psi, out, partial + 3ull * blockIdx.x, row + P.row_begin, chunk);
 }
 
+// The same in a queue whose owner may empty it: nothing is done when *skip is
+// not zero.
+template <class T, bool R16, bool ROWLDS, bool REALC>
+__global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_apply_sector_queued(
+    SectorArgs P, const T* __restrict__ psi, T* __restrict__ out, const uint32_t* skip) {
+  const uint32_t chunks = (P.dim_beta + kSB - 1) / kSB;
+  uint32_t row, chunk;
+  row_chunk_of(blockIdx.x, gridDim.x / chunks, chunks, P.row_lds != 0, row, chunk);
+  sector_body<T, false, R16, ROWLDS, REALC, true>(P, psi, out, nullptr, row + P.row_begin, chunk, skip);
+}
+
 // A job of a batched launch: one operator on one sector state.
 struct BatchJob {
   SectorArgs args;
@@ -1372,42 +1391,44 @@ __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   }
 }
 
-// Address of one sector kernel variant (single launch or batch).
+// Address of one sector kernel variant.
 template <class T, bool EXPVAL, bool R16, bool ROWLDS, bool REALC>
-void* sector_variant(bool batch) {
-  return batch ? reinterpret_cast<void*>(k_apply_sector_batch<T, EXPVAL, R16, ROWLDS, REALC>)
-               : reinterpret_cast<void*>(k_apply_sector<T, EXPVAL, R16, ROWLDS, REALC>);
+void* sector_variant(Form form) {
+  if constexpr (!EXPVAL)
+    if (form == Form::kQueued) return reinterpret_cast<void*>(k_apply_sector_queued<T, R16, ROWLDS, REALC>);
+  return form == Form::kBatch ? reinterpret_cast<void*>(k_apply_sector_batch<T, EXPVAL, R16, ROWLDS, REALC>)
+                              : reinterpret_cast<void*>(k_apply_sector<T, EXPVAL, R16, ROWLDS, REALC>);
 }
 
 template <class T, bool EXPVAL>
-void* sector_variants(bool batch, bool r16, bool rowlds, bool realc) {
+void* sector_variants(Form form, bool r16, bool rowlds, bool realc) {
   if (r16) {
-    if (rowlds) return realc ? sector_variant<T, EXPVAL, true, true, true>(batch)
-                             : sector_variant<T, EXPVAL, true, true, false>(batch);
-    return realc ? sector_variant<T, EXPVAL, true, false, true>(batch)
-                 : sector_variant<T, EXPVAL, true, false, false>(batch);
+    if (rowlds) return realc ? sector_variant<T, EXPVAL, true, true, true>(form)
+                             : sector_variant<T, EXPVAL, true, true, false>(form);
+    return realc ? sector_variant<T, EXPVAL, true, false, true>(form)
+                 : sector_variant<T, EXPVAL, true, false, false>(form);
   }
-  if (rowlds) return realc ? sector_variant<T, EXPVAL, false, true, true>(batch)
-                           : sector_variant<T, EXPVAL, false, true, false>(batch);
-  return realc ? sector_variant<T, EXPVAL, false, false, true>(batch)
-               : sector_variant<T, EXPVAL, false, false, false>(batch);
+  if (rowlds) return realc ? sector_variant<T, EXPVAL, false, true, true>(form)
+                           : sector_variant<T, EXPVAL, false, true, false>(form);
+  return realc ? sector_variant<T, EXPVAL, false, false, true>(form)
+               : sector_variant<T, EXPVAL, false, false, false>(form);
 }
 
 }  // namespace
 
 // Each is defined in its own translation unit (sector_<storage>_<mode>.hip)
 // so the variants compile in parallel.
-void* sector_kernel_c64_apply(bool batch, bool r16, bool rowlds, bool realc);
-void* sector_kernel_c64_expval(bool batch, bool r16, bool rowlds, bool realc);
-void* sector_kernel_c128_apply(bool batch, bool r16, bool rowlds, bool realc);
-void* sector_kernel_c128_expval(bool batch, bool r16, bool rowlds, bool realc);
+void* sector_kernel_c64_apply(Form form, bool r16, bool rowlds, bool realc);
+void* sector_kernel_c64_expval(Form form, bool r16, bool rowlds, bool realc);
+void* sector_kernel_c128_apply(Form form, bool r16, bool rowlds, bool realc);
+void* sector_kernel_c128_expval(Form form, bool r16, bool rowlds, bool realc);
 
-inline void* sector_kernel(pbs_dtype dt, bool expval, bool batch, bool r16, bool rowlds, bool realc) {
+inline void* sector_kernel(pbs_dtype dt, bool expval, Form form, bool r16, bool rowlds, bool realc) {
   if (dt == PBS_C128)
-    return expval ? sector_kernel_c128_expval(batch, r16, rowlds, realc)
-                  : sector_kernel_c128_apply(batch, r16, rowlds, realc);
-  return expval ? sector_kernel_c64_expval(batch, r16, rowlds, realc)
-                : sector_kernel_c64_apply(batch, r16, rowlds, realc);
+    return expval ? sector_kernel_c128_expval(form, r16, rowlds, realc)
+                  : sector_kernel_c128_apply(form, r16, rowlds, realc);
+  return expval ? sector_kernel_c64_expval(form, r16, rowlds, realc)
+                : sector_kernel_c64_apply(form, r16, rowlds, realc);
 }
 
 }  // namespace pbs

@@ -3,8 +3,8 @@
 
 namespace pbs {
 
-void* sector_kernel_c128_expval(bool batch, bool r16, bool rowlds, bool realc) {
-  return sector_variants<double2, true>(batch, r16, rowlds, realc);
+void* sector_kernel_c128_expval(Form form, bool r16, bool rowlds, bool realc) {
+  return sector_variants<double2, true>(form, r16, rowlds, realc);
 }
 
 }  // namespace pbs
