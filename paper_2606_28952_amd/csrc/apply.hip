@@ -876,6 +876,20 @@ void fill_batch(pbs_batch& B, uint32_t config) {
     else
       sector.push_back(i);
   }
+  // a second launch for a handful of targets costs more than it saves: of the
+  // variational blocks of 4 and 5 orbitals (36 and 400 panel targets) an evaluation
+  // takes 142 and 150 us with it, 134 and 144 without; of 6 (2,500) 161 and 160, of
+  // 7 (12,544) 207 and 242
+  uint64_t targets = 0;
+  for (const auto& list : by_variant)
+    for (uint32_t i : list) targets += B.sp[i]->dim;
+  if (!sector.empty() && targets < 1000) {
+    for (auto& list : by_variant) {
+      sector.insert(sector.end(), list.begin(), list.end());
+      list.clear();
+    }
+    std::sort(sector.begin(), sector.end());
+  }
   const uint32_t ns = static_cast<uint32_t>(sector.size());
   std::vector<BatchJob> jobs(ns);
   std::vector<double> cost(ns);

@@ -239,3 +239,29 @@ def test_config3_batch_of_64_uneven_sectors(dev):
     batch = api.Batch(jobs)
     batch.set_config(128)  # PBS_BATCH_PERSISTENT
     check(batch, "factored persistent")
+
+
+@pytest.mark.parametrize("sizes", [[(5, 2, 3)], [(5, 2, 3), (6, 1, 5)], [(8, 4, 4), (6, 1, 5)]])
+def test_batch_of_tabled_and_other_jobs(dev, sizes):
+    """Factored jobs alone, a few of their targets beside a job without tables
+    (one launch serves both), and many of them (a launch each): outputs and
+    energies of all jobs against the oracle, in the caller's order."""
+    api = _api()
+    jobs, want = [], []
+    for k, (n, na, nb) in enumerate(sizes):
+        h1, h2 = synth.molecular_spin_integrals(n, 300 + k)
+        G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+        sp = api.Space.sector(n, na, nb)
+        if k == 0:
+            G.factor(sp)
+        psi = synth.random_state(sp.dim, 310 + k)
+        want.append((psi, oapply.apply_scatter(ojw.jw_sum(h1, h2), ospace.SectorSpace(n, na, nb), psi)))
+        t = torch.from_numpy(psi).to(dev)
+        jobs.append((G, sp, t, torch.empty_like(t)))
+    energies = torch.zeros(3 * len(jobs), dtype=torch.float64, device=dev)
+    api.Batch(jobs).run(energies)
+    e = energies.cpu().numpy().reshape(-1, 3)
+    for (psi, ref), job, got in zip(want, jobs, e):
+        assert rel_err(job[3].cpu().numpy(), ref) < 1e-12
+        assert abs(got[0] - np.vdot(psi, ref).real) < 1e-12 * max(1.0, abs(got[0]))
+        assert abs(got[2] - 1.0) < 1e-13
