@@ -131,6 +131,16 @@ inline uint32_t panel_blocks(uint32_t dim_alpha, uint32_t rows, uint32_t cus) {
   return std::min(dim_alpha, (least + cus - 1u) / cus * cus);
 }
 
+// Workgroups per row of a launch of few rows of `groups` times 512 columns: one
+// per group, or per two groups, while all of them fit on the device at once.
+inline uint32_t panel_parts(uint64_t rows, uint32_t groups, uint32_t cus) {
+  for (uint32_t per : {1u, 2u}) {
+    const uint32_t parts = (groups + per - 1u) / per;
+    if (rows * parts <= cus) return parts;
+  }
+  return 1;
+}
+
 // Target rows per workgroup (at most `most`) of a launch that takes whole jobs
 // of rows x cols configurations: the number whose workgroups, dealt to the
 // compute units one at a time as these get free (longest first), end first.

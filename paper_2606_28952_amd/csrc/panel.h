@@ -52,9 +52,9 @@ constexpr int kPB = static_cast<int>(kPanelLanes);
 constexpr int kPW = kPB / 64;                                    // waves
 
 struct PanelArgs {
-  uint32_t dim_alpha, dim_beta, n_tiles, pad;
-  uint32_t row_begin, row_end;  // target rows of the launch
-  uint32_t blk0, n_blk;         // first row block of the launch; blocks of the whole sector
+  uint32_t dim_alpha, dim_beta, n_tiles;
+  uint32_t row_begin, rows;  // target rows of the launch
+  uint32_t n_blk;            // blocks that split them evenly
   uint32_t n_img, n_pairs, n_bb, diag_rank;
   uint64_t diag_off;  // of the diagonal group's F rows in fz (doubles)
   const uint32_t* alist_off;
@@ -124,11 +124,12 @@ __device__ __forceinline__ void pipelined(uint32_t n, B (&buf)[D], const L& load
 // NT kPB); MT: 16-pair tiles per wave (n_pairs <= 32 MT); KS: K steps of four
 // classes (at most 4 KS - 1 image classes per row).
 // Args: PanelArgs, as kernel argument or in the constant address space.
-// QUEUED: nothing is done when *stop is not zero.
-template <class T, bool EXPVAL, int NT, int MT, int KS, int R, bool QUEUED, class Args>
+// QUEUED: nothing is done when *stop is not zero.  PART: of the row's groups of
+// kPB columns, those from j0 on (else all, j0 = 0).
+template <class T, bool EXPVAL, int NT, int MT, int KS, int R, bool QUEUED, bool PART, class Args>
 __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ psi, T* __restrict__ out,
                                            double* __restrict__ slot, uint32_t ia, uint32_t nr,
-                                           const uint32_t* stop = nullptr) {
+                                           const uint32_t* stop, uint32_t j0) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -139,12 +140,12 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
   for (int j = 0; j < NT; ++j) {
 #pragma unroll
     for (int r = 0; r < R; ++r) ar[r][j] = ai[r][j] = 0.0;
-    cb[j] = min(tid + j * kPB, db - 1u);
+    cb[j] = min(tid + (j0 + j) * kPB, db - 1u);
   }
 
   // X_alpha = 0: kS rows staged side by side, so that one table entry and
   // one gather serve them all
-  constexpr int kS = sizeof(T) == 8 ? R : 2;
+  constexpr int kS = sizeof(T) == 8 || R == 1 ? R : 2;
   constexpr int kH = NT > 4 ? (NT + 1) / 2 : NT;  // the lane's columns in two parts: fewer registers in flight
   T* s_st = reinterpret_cast<T*>(smem);
 #pragma unroll
@@ -165,11 +166,12 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
 #pragma unroll
       for (int r = 0; r < kS; r += 2)
         if (static_cast<uint32_t>(g + r) < nr) {
+          constexpr int kPair = kS > 1 ? 1 : 0;
           double x0, y0, x1, y1;
           Amp<T>::load(s_st, col * kS + r, x0, y0);
-          Amp<T>::load(s_st, col * kS + r + 1, x1, y1);
+          if (kPair) Amp<T>::load(s_st, col * kS + r + kPair, x1, y1);
           Coef<true>::mac(c, x0, y0, ar[g + r][j], ai[g + r][j]);
-          Coef<true>::mac(c, x1, y1, ar[g + r + 1][j], ai[g + r + 1][j]);
+          if (kPair) Coef<true>::mac(c, x1, y1, ar[g + r + kPair][j], ai[g + r + kPair][j]);
         }
     };
     struct Moves {
@@ -395,7 +397,8 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
     uint4 cw = make_uint4(0u, 0u, 0u, 0u);
     uint32_t at = 0;  // byte offset of this lane's next entry
     auto pull = [&](int j) {
-      const uint32_t n = ((j < 4 ? cw.x : cw.y) >> (8 * (j & 3))) & 255u;
+      const uint32_t jg = PART ? j0 + j : static_cast<uint32_t>(j);
+      const uint32_t n = ((jg < 4 ? cw.x : cw.y) >> (8 * (jg & 3))) & 255u;
       for (uint32_t i = 0; i < n; i += kPanelPullRead) {
         uint32_t e[kPanelPullRead];
         double2 v[kPanelPullRead];
@@ -411,6 +414,13 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
         }
         at += 128u * min(n - i, kPanelPullRead);
       }
+    };
+    // the slots of the groups before j0 in a wave's list of a tile
+    auto before = [&](const uint4& c) {
+      uint32_t n = 0;
+      if (PART)
+        for (uint32_t j = 0; j < j0; ++j) n += ((j < 4 ? c.x : c.y) >> (8 * (j & 3))) & 255u;
+      return n;
     };
     auto counts = [&](uint32_t tile) {
       const uint32_t* c = reinterpret_cast<const uint32_t*>(P.pull_cnt + tile * kPW + wave);
@@ -451,7 +461,7 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
       }
       __syncthreads();  // the previous tile is gathered
       cw = cn;
-      at = cn.z * 128u + lane * 2u;
+      at = (cn.z + before(cn)) * 128u + lane * 2u;
       s_pull[tid] = pe0;
       s_pull[kPB + tid] = pe1;
 #pragma unroll
@@ -469,7 +479,7 @@ __device__ __forceinline__ void panel_body(const Args& P, const T* __restrict__ 
     double e_re = 0.0, e_im = 0.0, nrm = 0.0;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const uint32_t col = tid + j * kPB;
+      const uint32_t col = tid + (j0 + j) * kPB;
       if (col < db) {
         const uint64_t t = static_cast<uint64_t>(row) * db + col;
         if (EXPVAL) {
@@ -501,22 +511,35 @@ __device__ inline uint32_t panel_block_of(uint32_t w, uint32_t n) {
   return w < per * kXcds ? w % kXcds * per + w / kXcds : w;
 }
 
-// Workgroup w: the target rows of one of the n_blk row blocks that split the
-// sector's rows evenly, the blocks from blk0 on, that lie in [row_begin,
-// row_end).
+// Workgroup w: one of the n_blk row blocks that split the launch's rows evenly.
 template <class T, bool EXPVAL, int NT, int MT, int KS, int R, bool QUEUED>
 __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_panel(
     PanelArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial, const uint32_t* skip) {
-  const uint64_t b = P.blk0 + panel_block_of(blockIdx.x, gridDim.x);
-  const uint32_t r0 = max(static_cast<uint32_t>(b * P.dim_alpha / P.n_blk), P.row_begin);
-  const uint32_t r1 = min(static_cast<uint32_t>((b + 1) * P.dim_alpha / P.n_blk), P.row_end);
-  if (r1 > r0)
-    panel_body<T, EXPVAL, NT, MT, KS, R, QUEUED>(P, psi, out, partial + 3ull * (r0 - P.row_begin), r0, r1 - r0, skip);
+  const uint64_t b = panel_block_of(blockIdx.x, gridDim.x);
+  const uint32_t r0 = static_cast<uint32_t>(b * P.rows / P.n_blk);
+  const uint32_t r1 = static_cast<uint32_t>((b + 1) * P.rows / P.n_blk);
+  panel_body<T, EXPVAL, NT, MT, KS, R, QUEUED, false>(P, psi, out, partial + 3ull * r0, P.row_begin + r0, r1 - r0,
+                                                      skip, 0);
+}
+
+// Launches of few rows (a share of a sector): `parts` workgroups per row, NT
+// groups of kPB columns each, so that a short launch fills more of the device.
+// Every part computes the row's V for itself; the rest of its work is its own
+// columns'.  Outputs have the same bits (nothing is summed across columns).  16 of
+// the 3,432 rows of 28 qubits, complex64: 1.35 ms with two rows per workgroup,
+// 0.82 with one, 0.45 in seven parts; 128 of the 924 rows of (12; 6, 6): 0.63 with
+// four, 0.23 with one, 0.15 in two parts (the sector kernel: 0.29 and 0.15).
+template <class T, bool EXPVAL, int NT, int MT, int KS>
+__global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_apply_panel_part(
+    PanelArgs P, const T* __restrict__ psi, T* __restrict__ out, double* __restrict__ partial, uint32_t parts) {
+  const uint32_t b = panel_block_of(blockIdx.x, gridDim.x), row = b / parts;
+  panel_body<T, EXPVAL, NT, MT, KS, 1, false, true>(P, psi, out, partial + 3ull * b, P.row_begin + row, 1, nullptr,
+                                                    (b - row * parts) * NT);
 }
 
 // A job of a batched launch of one panel variant.
 struct PanelJob {
-  PanelArgs args;  // blk0 = 0, every row
+  PanelArgs args;  // every row
   const void* psi;
   void* out;
   uint32_t block_base;  // first work item of the job
@@ -541,10 +564,10 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     ConstJob& J = *(ConstJob*)(jobs + lo);
     const uint64_t b = panel_block_of(w - J.block_base, J.args.n_blk);
-    const uint32_t r0 = static_cast<uint32_t>(b * J.args.dim_alpha / J.args.n_blk);
-    const uint32_t r1 = static_cast<uint32_t>((b + 1) * J.args.dim_alpha / J.args.n_blk);
-    panel_body<T, EXPVAL, NT, MT, KS, R, false>(J.args, static_cast<const T*>(J.psi), static_cast<T*>(J.out),
-                                         partial + 3ull * (J.first + r0), r0, r1 - r0);
+    const uint32_t r0 = static_cast<uint32_t>(b * J.args.rows / J.args.n_blk);
+    const uint32_t r1 = static_cast<uint32_t>((b + 1) * J.args.rows / J.args.n_blk);
+    panel_body<T, EXPVAL, NT, MT, KS, R, false, false>(J.args, static_cast<const T*>(J.psi), static_cast<T*>(J.out),
+                                                       partial + 3ull * (J.first + r0), r0, r1 - r0, nullptr, 0);
   }
 }
 
@@ -558,6 +581,16 @@ void* panel_variant(bool expval, Form form) {
                 : reinterpret_cast<void*>(k_apply_panel<T, false, NT, MT, KS, R, false>);
 }
 
+// NT of a part: one group of columns, or two.
+template <class T, int MT, int KS>
+void* panel_part_variant(bool expval, bool two) {
+  if (two)
+    return expval ? reinterpret_cast<void*>(k_apply_panel_part<T, true, 2, MT, KS>)
+                  : reinterpret_cast<void*>(k_apply_panel_part<T, false, 2, MT, KS>);
+  return expval ? reinterpret_cast<void*>(k_apply_panel_part<T, true, 1, MT, KS>)
+                : reinterpret_cast<void*>(k_apply_panel_part<T, false, 1, MT, KS>);
+}
+
 }  // namespace
 
 // Kernel of a shape (PanelShape::variant); each storage type and half of the
@@ -566,6 +599,15 @@ void* panel_kernel_c64_narrow(bool expval, Form form, int variant);
 void* panel_kernel_c64_wide(bool expval, Form form, int variant);
 void* panel_kernel_c128_narrow(bool expval, Form form, int variant);
 void* panel_kernel_c128_wide(bool expval, Form form, int variant);
+
+// Kernel of a part of a row, for the variants of several groups of columns
+// (panel_<storage>_part.hip).
+void* panel_part_c64(bool expval, bool two, int variant);
+void* panel_part_c128(bool expval, bool two, int variant);
+
+inline void* panel_part(pbs_dtype dt, bool expval, bool two, int variant) {
+  return dt == PBS_C128 ? panel_part_c128(expval, two, variant) : panel_part_c64(expval, two, variant);
+}
 
 inline void* panel_kernel(pbs_dtype dt, bool expval, Form form, int variant) {
   if (variant >= kPanelWide)

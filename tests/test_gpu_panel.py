@@ -134,3 +134,34 @@ def test_panel_without_diagonal_factors(dev, n_o, na, nb):
     assert rel_err(out.cpu().numpy(), ref) < 1e-12
     e_ref = np.vdot(psi_np, ref)
     assert abs(e[0] - e_ref.real) < 1e-12 * max(1.0, abs(e_ref))
+
+
+@pytest.mark.parametrize("n_o,na,nb", [(12, 6, 6), (13, 5, 4), (13, 4, 6), (14, 5, 5), (14, 4, 7)])
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+def test_panel_shares_of_few_rows(dev, n_o, na, nb, dtype):
+    """Shares of few rows give several workgroups to a row: every count of parts
+    (one or two groups of 512 columns each, the last one not full) and the sizes
+    at which it changes give the whole sector's bits, and energies that add up."""
+    from paper_2606_28952_amd import api
+
+    h1, h2 = synth.molecular_spin_integrals(n_o, 501)
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(n_o, na, nb)
+    G.factor(sp)
+    psi = torch.from_numpy(synth.random_state(sp.dim, 502)).to(dev).to(dtype)
+    da, db = sp.shape()[3:5]
+    whole = torch.view_as_real(api.apply_pauli_sum(G, sp, psi)).reshape(da, db, 2)
+    groups = (db + 511) // 512
+    for rows in sorted({1, 256 // groups, 256 // groups + 1, 512 // (groups + 1), 512 // groups + 1, 257}):
+        a = (da - rows) // 2
+        out = torch.empty(rows * db, dtype=dtype, device=dev)
+        e = api.expval_rows(G, sp, psi, a, a + rows, out=out).cpu().numpy()
+        assert torch.equal(torch.view_as_real(out).reshape(rows, db, 2), whole[a:a + rows]), rows
+        part = api.apply_pauli_sum_rows(G, sp, psi, a, a + rows)
+        assert torch.equal(torch.view_as_real(part), torch.view_as_real(out)), rows
+        p = psi.reshape(da, db)[a:a + rows].to(torch.complex128)
+        ref = torch.sum(p.conj() * torch.view_as_complex(whole[a:a + rows].to(torch.float64))).cpu().numpy()
+        # the energy sums float64 products, the reference those rounded to storage
+        tol = 1e-12 if dtype == torch.complex128 else 1e-6
+        assert abs(e[0] - ref.real) < tol * max(1.0, abs(ref)) and abs(e[1] - ref.imag) < tol * max(1.0, abs(ref))
+        assert abs(e[2] - float(p.abs().square().sum())) < 1e-12
