@@ -365,8 +365,8 @@ pbs_status pbs_batch_run(const pbs_batch* b, double* energies, void* stream);
 pbs_status pbs_batch_set_config(pbs_batch* b, uint32_t config);
 
 /* Autotuner: times schedules (a warm-up run, then `reps` runs, 1..100, with
- * HIP events on the stream; schedules that build the same job table are
- * timed once), greedily: the four workgroup orders with the default flags,
+ * HIP events on the stream; schedules that build the same job table and
+ * launch as many workgroups are timed once), greedily: the four workgroup orders with the default flags,
  * then the 64 flag combinations with the best order.  Keeps the fastest and
  * returns it in *config and its time per run in *ms (either may be NULL).
  * Runs the batch, so the output buffers are overwritten.  Call it before

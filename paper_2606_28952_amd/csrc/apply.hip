@@ -835,10 +835,16 @@ struct pbs_batch {
   const pbs::FactorPlan* beta_plan(uint32_t i) const {
     return plan_b.empty() || !plan_b[i] ? h[i]->fplan.get() : plan_b[i];
   }
+  bool brought(uint32_t i) const { return (!plan_a.empty() && plan_a[i]) || (!plan_b.empty() && plan_b[i]); }
+  bool brought_any() const {
+    for (uint32_t i = 0; i < n_jobs; ++i)
+      if (brought(i)) return true;
+    return false;
+  }
   pbs::DevBuf<pbs::BatchJob> jobs;
   pbs::DevBuf<pbs::PanelJob> pjobs;
   pbs::DevBuf<pbs::FinishJob> finish;
-  std::string table;  // the job tables of the schedule in use, byte for byte (the tuner compares them)
+  std::string table;  // the job tables and grids of the schedule in use, byte for byte (the tuner compares them)
   pbs::DevBuf<double> partial;
 };
 
@@ -879,7 +885,7 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   }
   for (uint32_t i = 0; i < n; ++i) {
     const PanelShape& ps = shape[i];
-    if (can[i] && (!B.plan_a.empty() || panel_pays(ps.variant, variant_rows[ps.variant], B.sp[i]->dim_beta, ps.fill,
+    if (can[i] && (B.brought(i) || panel_pays(ps.variant, variant_rows[ps.variant], B.sp[i]->dim_beta, ps.fill,
                                                    static_cast<uint32_t>(esz), cus)))
       by_variant[ps.variant].push_back(i);
     else
@@ -1027,6 +1033,9 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   B.table.assign(1, static_cast<char>(rowlds));
   B.table.append(reinterpret_cast<const char*>(sorted.data()), ns * sizeof(BatchJob));
   B.table.append(reinterpret_cast<const char*>(psorted.data()), psorted.size() * sizeof(PanelJob));
+  // (a persistent launch has the same jobs and fewer workgroups)
+  B.table.append(reinterpret_cast<const char*>(&B.grid), sizeof(B.grid));
+  for (const auto& P : B.panels) B.table.append(reinterpret_cast<const char*>(&P.grid), sizeof(P.grid));
   B.config = config;
 }
 
@@ -1118,8 +1127,8 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
     hipEvent_t e0, e1;
     PBS_HIP(hipEventCreate(&e0));
     PBS_HIP(hipEventCreate(&e1));
-    std::vector<std::pair<std::string, double>> seen;  // job table + variant -> time
-    // time of schedule c (schedules with the same table and variant share one measurement)
+    std::vector<std::pair<std::string, double>> seen;  // job table, variant and grid -> time
+    // time of schedule c (schedules with the same table, variant and grid share one measurement)
     auto time_config = [&](uint32_t c) {
       fill_batch(*b, c);
       const std::string& key = b->table;
@@ -1154,7 +1163,7 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
       for (uint32_t f = 1; f < kBatchConfigs; ++f) {
         if (f & PBS_BATCH_ORDER_MASK) continue;
         // (tables that the batch's owner brought are not an operator's own to ignore)
-        if ((f & PBS_BATCH_NO_FACTORED) && !b->plan_a.empty()) continue;
+        if ((f & PBS_BATCH_NO_FACTORED) && b->brought_any()) continue;
         const double t = time_config(ord | f);
         if (t < best_ms) {
           best = ord | f;
