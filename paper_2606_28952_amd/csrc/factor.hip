@@ -692,8 +692,9 @@ std::unique_ptr<FactorPlan> make_factor_plan(const pbs_grouped& h, const pbs_spa
   }
   for (int k = 0; k < 3; ++k) F.ns_sizes[k] = static_cast<uint32_t>(rest[k].size());
   PanelLists L;
-  F.panel_variant = panel_variant_for(sp.dim_alpha, sp.dim_beta, h.n_pairs, sp.n_alpha * (sp.n_orb - sp.n_alpha) + 1u);
-  bool panel = F.plist && F.panel_variant >= 0 && panel_lists(F, h, sp, T, meta, cls_f, zpair, icls, &L);
+  const int variant =
+      panel_variant_for(sp.dim_alpha, sp.dim_beta, h.n_pairs, sp.n_alpha * (sp.n_orb - sp.n_alpha) + 1u);
+  bool panel = F.plist && variant >= 0 && panel_lists(F, h, sp, T, meta, cls_f, zpair, icls, &L);
 
   ColumnGroups cols;
   const bool blist = F.alist && F.c0 == 0xffffffffu && ns.size() == 1 && sp.n_orb <= 16 && db < 65536 &&

@@ -139,7 +139,6 @@ struct FactorPlan {
   // groups split into a beta-only part and a part with the pair's parity
   // zpair, and whose quad groups are beta-only.
   bool panel = false;
-  int panel_variant = -1;    // of kPanelVariants
   uint32_t n_bb = 0, n_tiles = 0, diag_rank = 0;
   uint64_t diag_off = 0;
   DevBuf<uint32_t> bb_src;   // [ceil(n_bb / 2)][dim_beta]: source columns of moves 2i | 2i + 1 << 16

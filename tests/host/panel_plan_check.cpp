@@ -3,6 +3,9 @@
 // UndefinedBehaviorSanitizer.  Returns non-zero when a check failed.
 #include <algorithm>
 #include <cstdio>
+#include <cstdlib>
+#include <utility>
+#include <vector>
 
 #include "../../paper_2606_28952_amd/csrc/host_plan.h"
 
@@ -94,7 +97,30 @@ static void check_panel_pays() {
   }
 }
 
-int main() {
+// n a b jobs -> variant and rows of a workgroup: of a single launch (jobs 0) or
+// of a batch of `jobs` equal jobs, 256 compute units.
+static int print_split(char** v) {
+  const uint32_t n = std::atoi(v[1]), a = std::atoi(v[2]), b = std::atoi(v[3]), jobs = std::atoi(v[4]);
+  const uint32_t rows = static_cast<uint32_t>(binomial(n, a)), cols = static_cast<uint32_t>(binomial(n, b));
+  const int variant = panel_variant_for(rows, cols, n * (n - 1) / 2, a * (n - a) + 1);
+  if (variant < 0) return 1;
+  const uint32_t most = kPanelVariants[variant].rows;
+  uint32_t per;
+  if (jobs) {
+    per = panel_batch_rows(std::vector<std::pair<uint32_t, uint32_t>>(jobs, {rows, cols}), most, 256);
+  } else {
+    const uint32_t blocks = panel_blocks(rows, most, 256);
+    per = (rows + blocks - 1) / blocks;
+  }
+  const double fill = panel_fill(variant, a * (n - a), b * (n - b));
+  const uint64_t all = static_cast<uint64_t>(rows) * (jobs ? jobs : 1);
+  std::printf("%d %u %d %d\n", variant, per, panel_pays(variant, all, cols, fill, 8, 256),
+              panel_pays(variant, all, cols, fill, 16, 256));
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc == 5) return print_split(argv);
   check_pull_region();
   check_panel_pays();
   check_batch_rows();

@@ -163,3 +163,43 @@ def test_hubbard_4x4_free_fermions(dev, dtype, tol):
         occ = [i for i in range(n) if (bits >> i) & 1]
         want = (np.abs(prop_h[:, occ]) ** 2).sum(axis=1)
         np.testing.assert_allclose(got[sigma], want, atol=tol)
+
+
+@pytest.mark.parametrize("kind", ["lists", "rows"])
+def test_krylov_ends_early_on_long_rows(dev, kind):
+    """The same on the kernels of rows too long to stage (6,435 complex128 columns
+    of 15 orbitals, one alpha): without beta hops a product of basis states on the
+    beta side and an eigenvector of the ring of alpha is an eigenvector."""
+    api = _api()
+    n, nb = 15, 7
+    h1, h2 = np.zeros((2 * n, 2 * n)), np.zeros((2 * n,) * 4)
+    for p in range(n):
+        q = (p + 1) % n
+        for s in (0, n):
+            h1[s + p, s + q] = h1[s + q, s + p] = -1.0 if s == 0 else 1e-3
+    G = api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+    sp = api.Space.sector(n, 1, nb)
+    G.factor(sp)
+    if kind == "rows":
+        G.set_factored(5)  # without the move tables the lists are left aside
+    # alpha: the ring's constant orbital, energy -2; beta: the antisymmetric state of
+    # the seven lowest orbitals of its ring, whose one-body energies add up
+    k = 2.0 * np.pi * np.arange(n) / n
+    order = np.argsort(2e-3 * np.cos(k), kind="stable")
+    occ = order[:nb]
+    orb = np.exp(1j * np.outer(np.arange(n), k[occ])) / np.sqrt(n)
+    strings = [t for t in range(1 << n) if bin(t).count("1") == nb]
+    amp = np.array([np.linalg.det(orb[[i for i in range(n) if t >> i & 1]]) for t in strings])
+    v = np.kron(np.ones(n) / np.sqrt(n), amp).astype(np.complex128)
+    energy = -2.0 + float(np.sum(2e-3 * np.cos(k[occ])))
+    t = torch.from_numpy(v).to(dev)
+    h = api.apply_pauli_sum(G, sp, t).cpu().numpy()
+    assert rel_err(h, energy * v) < 1e-12
+    prop = api.KrylovPropagator(G, sp, dtype=torch.complex128, m=12)
+    info = prop.step(t, 0.05)
+    # the residual is rounding, some 1e-16 of |H|, or just above the end's 1e-14
+    assert info[2] <= 2.0
+    assert rel_err(t.cpu().numpy(), np.exp(-1j * energy * 0.05) * v) < 1e-12
+    t.zero_()
+    assert list(prop.step(t, 0.05)) == [0.0, 0.0, 0.0, 0.0]
+    assert torch.count_nonzero(torch.view_as_real(t)) == 0

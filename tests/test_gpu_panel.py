@@ -17,6 +17,7 @@ from oracle import apply as oapply
 from oracle import jw as ojw
 from oracle import space as ospace
 from tests.conftest import rel_err
+from tests.panel_sizes import BATCHES, SINGLE
 
 pytestmark = pytest.mark.gpu
 
@@ -165,3 +166,65 @@ def test_panel_shares_of_few_rows(dev, n_o, na, nb, dtype):
         tol = 1e-12 if dtype == torch.complex128 else 1e-6
         assert abs(e[0] - ref.real) < tol * max(1.0, abs(ref)) and abs(e[1] - ref.imag) < tol * max(1.0, abs(ref))
         assert abs(e[2] - float(p.abs().square().sum())) < 1e-12
+
+
+def _operator(dev, n_o, seed):
+    from paper_2606_28952_amd import api
+
+    h1, h2 = synth.molecular_spin_integrals(n_o, seed)
+    return api.jw_transform(torch.from_numpy(h1).to(dev), torch.from_numpy(h2).to(dev)).group()
+
+
+@pytest.mark.parametrize("n_o,na,nb", list(SINGLE))
+def test_panel_variants_match_plain(dev, n_o, na, nb):
+    """Every variant with its full number of rows per workgroup (the host test of
+    the same sizes says that they do), both storage types, against the unfactored
+    evaluation."""
+    from paper_2606_28952_amd import api
+
+    G = _operator(dev, n_o, 800 + n_o + na)
+    sp = api.Space.sector(n_o, na, nb)
+    psi = torch.from_numpy(synth.random_state(sp.dim, 801)).to(dev)
+    psi32 = psi.to(torch.complex64)
+    plain = api.apply_pauli_sum(G, sp, psi)
+    plain32 = api.apply_pauli_sum(G, sp, psi32.to(torch.complex128))
+    G.factor(sp)
+    out, out32 = torch.empty_like(psi), torch.empty_like(psi32)
+    e = api.expval(G, sp, psi, out=out).cpu().numpy()
+    e32 = api.expval(G, sp, psi32, out=out32).cpu().numpy()
+
+    def off(a, b):
+        return float((a - b).abs().square().sum().sqrt() / b.abs().square().sum().sqrt())
+
+    assert off(out, plain) < 1e-12
+    assert off(out32.to(torch.complex128), plain32) < 1e-6
+    for got, p, h in ((e, psi, plain), (e32, psi32.to(torch.complex128), plain32)):
+        ref = float(torch.sum(p.conj() * h).real)
+        assert abs(got[0] - ref) < 1e-12 * max(1.0, abs(ref))
+    assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi)), torch.view_as_real(out))
+    assert torch.equal(torch.view_as_real(api.apply_pauli_sum(G, sp, psi32)), torch.view_as_real(out32))
+
+
+@pytest.mark.parametrize("sector,n_jobs", list(BATCHES))
+def test_panel_batches_equal_single_launches(dev, sector, n_jobs):
+    """A batch's workgroups take three or four rows of a job, a single launch of it
+    one or two: same outputs, bit for bit, and energies to rounding."""
+    from paper_2606_28952_amd import api
+
+    sp = api.Space.sector(*sector)
+    jobs, energies = [], torch.zeros(3 * n_jobs, dtype=torch.float64, device=dev)
+    operators = []
+    for k in range(n_jobs):
+        if k < 3:
+            G = _operator(dev, sector[0], 850 + k)
+            G.factor(sp)
+            operators.append(G)
+        psi = torch.from_numpy(synth.random_state(sp.dim, 860 + k)).to(dev)
+        jobs.append((operators[k % 3], sp, psi, torch.empty_like(psi)))
+    api.Batch(jobs).run(energies)
+    e = energies.cpu().numpy().reshape(-1, 3)
+    for (G, _, psi, out), got in zip(jobs, e):
+        single = torch.empty_like(psi)
+        want = api.expval(G, sp, psi, out=single).cpu().numpy()
+        assert torch.equal(torch.view_as_real(out), torch.view_as_real(single))
+        assert np.abs(got - want).max() < 1e-12 * max(1.0, abs(want[0]))
