@@ -410,7 +410,7 @@ pbs_status pbs_krylov_step(const pbs_grouped* h, const pbs_space* sp, pbs_dtype 
  * cos(theta_k) + i sin(theta_k) P_k, over the full 2^(2 n_orb) space, with
  * its energy <psi|H|psi> (Section 2.1, Eq. vqe_energy).  H must conserve
  * N_alpha and N_beta (a JW Hamiltonian of spin-orbital integrals): the
- * product H|psi> runs through the batched sector kernel over all
+ * product H|psi> runs through the batched kernels over all
  * (N_alpha, N_beta) blocks of the full space.  This is checked on the
  * grouped terms when the handle is created: an operator with a sector-changing
  * part (a pairing term, a lone X_p X_q) is refused with PBS_ERR_UNSUPPORTED
@@ -422,8 +422,11 @@ pbs_status pbs_krylov_step(const pbs_grouped* h, const pbs_space* sp, pbs_dtype 
  *  ref    basis index of the reference state (bit k = qubit k).
  *  dt     storage of the state vectors; energies, overlaps and gradients are
  *         float64.
- * Allocates four full-space vectors and the sector tables; synchronizes the
- * stream. */
+ * Allocates four full-space vectors, the sector tables and, for a real
+ * two-body operator, factor tables for every number of spin-up or spin-down
+ * electrons (as pbs_grouped_factor's, one set per number for all blocks; at 24
+ * qubits the handle takes 21 ms to create, 13 without them); synchronizes
+ * the stream. */
 pbs_status pbs_vqe_create(const pbs_grouped* h, uint32_t n_orb, uint32_t n_rot, const uint64_t* x, const uint64_t* z,
                           uint64_t ref, pbs_dtype dt, void* stream, pbs_vqe** out);
 

@@ -13,7 +13,8 @@
 // each move once per target instead of once per target and class.
 //
 // One workgroup of eight waves owns up to four alpha rows (two with 2,048 and
-// more columns) and all their beta columns, one workgroup per compute unit:
+// more columns) and all their beta columns (a part of them in a launch of few
+// rows, k_apply_panel_part), one workgroup per compute unit:
 //  * X_alpha = 0 class: its beta-only part (pair and quad groups without
 //    alpha Z-masks, a float64 coefficient per move and column) gathers from
 //    the staged target rows, one table read for all of them; its diagonal

@@ -236,7 +236,7 @@ size_t scan_scratch_bytes(uint64_t n);
 // Stable LSD radix sort of m items keyed by nw 64-bit words (SoA: word w of
 // item i at keys[w*m + i], word 0 least significant), carrying a uint32
 // payload, nw <= 2 kMaxWords.  Sorts by the bits that differ between items
-// (found by a device reduction, read back once above 4096 items).  Result
+// (found by a device reduction, read back once above 8192 items).  Result
 // ends in keys/vals.
 void radix_sort_keys(uint64_t* keys, uint32_t* vals, uint64_t m, int nw, hipStream_t s);
 
