@@ -62,7 +62,7 @@ WORKLOADS = {
 # sources that decide what the sector apply kernel does per launch: its
 # device code, its launch planner and the tables grouping builds for it
 APPLY_SOURCES = ("apply.hip", "factor.hip", "group.hip", "handles.h", "host_plan.h", "lists.h", "panel.h", "panel_c128_narrow.hip",
-                 "panel_c128_wide.hip", "panel_c64_narrow.hip", "panel_c64_wide.hip", "sector.h",
+                 "panel_c128_part.hip", "panel_c128_wide.hip", "panel_c64_narrow.hip", "panel_c64_part.hip", "panel_c64_wide.hip", "sector.h",
                  "sector_c128_apply.hip", "sector_c128_expval.hip", "sector_c64_apply.hip", "sector_c64_expval.hip")
 
 

@@ -366,9 +366,10 @@ pbs_status pbs_batch_set_config(pbs_batch* b, uint32_t config);
 
 /* Autotuner: times schedules (a warm-up run, then `reps` runs, 1..100, with
  * HIP events on the stream; schedules that build the same job table and
- * launch as many workgroups are timed once), greedily: the four workgroup orders with the default flags,
- * then the 64 flag combinations with the best order.  Keeps the fastest and
- * returns it in *config and its time per run in *ms (either may be NULL).
+ * launch as many workgroups are timed once), greedily: the four workgroup
+ * orders with the default flags, then the other flags' 32 combinations with the
+ * best order, then the best of these as a persistent launch.  Keeps the fastest
+ * and returns it in *config and its time per run in *ms (either may be NULL).
  * Runs the batch, so the output buffers are overwritten.  Call it before
  * capturing pbs_batch_run in a graph: it rebuilds the job table.
  * Synchronizes. */

@@ -1148,8 +1148,8 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
     uint32_t best = 0;
     double best_ms = 0.0;
     try {
-      // greedy: the workgroup order first (default flags), then the four
-      // flags with that order
+      // greedy: the workgroup order first (default flags), then the evaluation's
+      // flags with that order, then the best of these as a persistent launch
       best_ms = time_config(0);
       for (uint32_t o = 1; o < 4; ++o) {
         const uint32_t c = o << 4;
@@ -1161,7 +1161,7 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
       }
       const uint32_t ord = best & PBS_BATCH_ORDER_MASK;
       for (uint32_t f = 1; f < kBatchConfigs; ++f) {
-        if (f & PBS_BATCH_ORDER_MASK) continue;
+        if (f & (PBS_BATCH_ORDER_MASK | PBS_BATCH_PERSISTENT)) continue;
         // (tables that the batch's owner brought are not an operator's own to ignore)
         if ((f & PBS_BATCH_NO_FACTORED) && b->brought_any()) continue;
         const double t = time_config(ord | f);
@@ -1169,6 +1169,10 @@ pbs_status pbs_batch_tune(pbs_batch* b, uint32_t reps, void* stream, uint32_t* c
           best = ord | f;
           best_ms = t;
         }
+      }
+      if (const double t = time_config(best | PBS_BATCH_PERSISTENT); t < best_ms) {
+        best |= PBS_BATCH_PERSISTENT;
+        best_ms = t;
       }
       fill_batch(*b, best);
       b->tuned_ms = best_ms;
