@@ -16,6 +16,51 @@ namespace pbs {
 namespace {
 
 // ---------------------------------------------------------------- full space
+// One target per lane, every group gathered from memory: for the spaces and
+// operators that full_tile leaves.
+template <class T, bool EXPVAL, bool QUEUED>
+__global__ __launch_bounds__(kBlock) void k_apply_lanes(uint64_t dim, uint32_t n_groups,
+                                                        const uint64_t* __restrict__ xg,
+                                                        const uint32_t* __restrict__ off,
+                                                        const uint64_t* __restrict__ zk,
+                                                        const double* __restrict__ ck, const T* __restrict__ psi,
+                                                        T* __restrict__ out, double* __restrict__ partial,
+                                                        const uint32_t* skip) {
+  if (QUEUED && *skip) return;  // see Form
+  const double2* ck2 = reinterpret_cast<const double2*>(ck);
+  double e_re = 0.0, e_im = 0.0, nrm = 0.0;
+  for (uint64_t t = blockIdx.x * static_cast<uint64_t>(kBlock) + threadIdx.x; t < dim;
+       t += static_cast<uint64_t>(gridDim.x) * kBlock) {
+    double acc_r = 0.0, acc_i = 0.0;
+    for (uint32_t g = 0; g < n_groups; ++g) {
+      const uint64_t s = t ^ xg[g];
+      double fr = 0.0, fi = 0.0;
+      const uint32_t k1 = off[g + 1];
+      for (uint32_t k = off[g]; k < k1; ++k) {
+        const uint32_t par = static_cast<uint32_t>(__popcll(zk[k] & s));
+        const double2 c = ck2[k];
+        fr += signed_by(c.x, par);
+        fi += signed_by(c.y, par);
+      }
+      double ar, ai;
+      Amp<T>::load(psi, s, ar, ai);
+      acc_r = fma(ar, fr, fma(-ai, fi, acc_r));
+      acc_i = fma(ar, fi, fma(ai, fr, acc_i));
+    }
+    if (EXPVAL) {
+      double pr, pi;
+      Amp<T>::load(psi, t, pr, pi);
+      e_re = fma(pr, acc_r, fma(pi, acc_i, e_re));
+      e_im = fma(pr, acc_i, fma(-pi, acc_r, e_im));
+      nrm = fma(pr, pr, fma(pi, pi, nrm));
+      if (out) Amp<T>::store(out, t, acc_r, acc_i);
+    } else {
+      Amp<T>::store(out, t, acc_r, acc_i);
+    }
+  }
+  if (EXPVAL) block_reduce3_store<kBlock>(e_re, e_im, nrm, partial + 3ull * blockIdx.x);
+}
+
 // A workgroup owns a tile of R * 256 consecutive targets, R per lane (256
 // apart), and holds the tile's amplitudes in LDS: groups whose X-mask stays
 // within the tile gather from there, the others gather the same places of one
@@ -32,7 +77,7 @@ namespace {
 // from memory took 117 and 120.  At 18 sites, where most of the time is latency,
 // 10.5 against 10.7.  Tiles of 512 or 1024 lanes, 16 targets per lane, or four
 // gathers in flight per lane are all slower (53 to 61 us).
-constexpr uint32_t kFullLanes = 256;
+static_assert(kFullLanes == kBlock, "both full-space kernels have the same workgroups");
 
 // f[j] <- sum over p of (-1)^popcount(p & j) f[p]
 template <int R>
@@ -60,22 +105,19 @@ __global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_
   constexpr uint32_t kTile = kFullLanes * R;
   __shared__ T s_psi[kTile];
   const uint32_t tid = threadIdx.x;
-  const uint64_t n_tiles = (dim + kTile - 1) / kTile;
+  const uint64_t n_tiles = dim / kTile;  // (full_tile: whole tiles)
   double e_re = 0.0, e_im = 0.0, nrm = 0.0;
   for (uint64_t w = blockIdx.x; w < n_tiles; w += gridDim.x) {
     const uint64_t per = n_tiles / kXcds;
     const uint64_t tile = (w < per * kXcds ? w % kXcds * per + w / kXcds : w) * kTile;
-    // a space smaller than one tile: the lanes behind it repeat its targets
-    const uint32_t lane = dim < kTile ? tid & static_cast<uint32_t>(dim - 1) : tid;
-    const uint32_t step = dim < kTile ? 0u : kFullLanes;
     if (w != blockIdx.x) __syncthreads();
 #pragma unroll
-    for (int j = 0; j < R; ++j) s_psi[tid + kFullLanes * j] = psi[tile + lane + step * j];
+    for (int j = 0; j < R; ++j) s_psi[tid + kFullLanes * j] = psi[tile + tid + kFullLanes * j];
     __syncthreads();
     double ar[R], ai[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) ar[j] = ai[j] = 0.0;
-    const uint64_t t0 = tile + lane;
+    const uint64_t t0 = tile + tid;
     // a group's mask, end and first term are read while the group before it is
     // evaluated
     uint32_t g = 0, k = 0, k1 = n_groups ? off[1] : 0u, k1_next = 0;
@@ -89,7 +131,7 @@ __global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_
       k1_next = off[next + 1u];
       c_next = ck[2 * kn];
       d_next = ck[2 * kn + 1];
-      const uint32_t xl = static_cast<uint32_t>(x) & (kTile - 1), place = lane ^ (xl & (kFullLanes - 1));
+      const uint32_t xl = static_cast<uint32_t>(x) & (kTile - 1), place = tid ^ (xl & (kFullLanes - 1));
       if (x < kTile) {
 #pragma unroll
         for (int j = 0; j < R; ++j) a[j] = s_psi[place + (kFullLanes * j ^ (xl & ~(kFullLanes - 1)))];
@@ -183,7 +225,6 @@ __global__ __launch_bounds__(kFullLanes) void k_apply_full(uint64_t dim, uint32_
 #pragma unroll
     for (int j = 0; j < R; ++j) {
       const uint64_t t = tile + tid + kFullLanes * j;
-      if (t >= dim) continue;
       if (EXPVAL) {
         const T own = s_psi[tid + kFullLanes * j];
         const double pr = static_cast<double>(own.x), pi = static_cast<double>(own.y);
@@ -578,9 +619,6 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
   const T* p = static_cast<const T*>(psi);
   T* o = static_cast<T*>(out);
   if (!sp.sector) {
-    // as many targets per lane as leave a workgroup per compute unit; eight of
-    // 16 bytes cost too many registers (102 us at 22 sites, 83 with four)
-    const uint64_t lanes = sp.dim / kFullLanes, want = device_cus();
     auto go = [&](auto kern, uint32_t r) {
       const unsigned grid = grid_for(sp.dim, kFullLanes * r, kFullGridCap);
       hipLaunchKernelGGL(kern, dim3(grid), dim3(kFullLanes), 0, s, sp.dim, static_cast<uint32_t>(h.n_groups),
@@ -588,11 +626,12 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
       PBS_HIP(hipGetLastError());
       return static_cast<uint64_t>(grid);
     };
+    const uint32_t r = full_tile(sp.dim, h.n_groups, h.n_signed, sizeof(T), device_cus());
     if constexpr (sizeof(T) == 8)
-      if (lanes >= 8 * want) return go(k_apply_full<T, EXPVAL, 8, QUEUED>, 8);
-    if (lanes >= 4 * want) return go(k_apply_full<T, EXPVAL, 4, QUEUED>, 4);
-    if (lanes >= 2 * want) return go(k_apply_full<T, EXPVAL, 2, QUEUED>, 2);
-    return go(k_apply_full<T, EXPVAL, 1, QUEUED>, 1);
+      if (r == 8) return go(k_apply_full<T, EXPVAL, 8, QUEUED>, 8);
+    if (r == 4) return go(k_apply_full<T, EXPVAL, 4, QUEUED>, 4);
+    if (r == 2) return go(k_apply_full<T, EXPVAL, 2, QUEUED>, 2);
+    return go(k_apply_lanes<T, EXPVAL, QUEUED>, 1);
   } else {
     SectorArgs a;
     bool r16 = false;

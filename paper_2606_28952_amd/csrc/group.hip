@@ -6,16 +6,26 @@
 namespace pbs {
 namespace {
 
-__global__ void k_x_heads(const uint64_t* x, uint64_t m, uint32_t* heads) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    heads[i] = (i == 0 || x[i] != x[i - 1]) ? 1u : 0u;
+// Heads of the groups, and how many groups are more than one real term without Z
+// bits (added to *n_signed, one addition per wave).
+__global__ void k_x_heads(const uint64_t* x, const uint64_t* zk, const double* ck, uint64_t m, uint32_t* heads,
+                          uint32_t* n_signed) {
+  for (uint64_t i0 = blockIdx.x * static_cast<uint64_t>(blockDim.x); i0 < m;
+       i0 += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
+    const uint64_t i = i0 + threadIdx.x;
+    const bool head = i < m && (i == 0 || x[i] != x[i - 1]);
+    if (i < m) heads[i] = head ? 1u : 0u;
+    const bool plain = head && (i + 1 == m || x[i + 1] != x[i]) && zk[i] == 0 && ck[2 * i + 1] == 0.0;
+    const uint32_t n = static_cast<uint32_t>(__popcll(__ballot(head && !plain)));
+    if ((threadIdx.x & 63u) == 0 && n) atomicAdd(n_signed, n);
+  }
 }
 
 // CSR terms: Z-masks and XZ-form coefficients C_k = c_k * i^popcount(x_k & z_k)
-// (Section 2.3).
+// (Section 2.3).  Clears *n_signed for k_x_heads.
 __global__ void k_csr_terms(const uint64_t* x, const uint64_t* z, const double* c, uint64_t m, uint64_t* zk,
-                            double* ck) {
+                            double* ck, uint32_t* n_signed) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *n_signed = 0u;
   for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < m;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
     zk[i] = z[i];
@@ -269,7 +279,7 @@ __global__ void k_pair_map(uint32_t n_class, const int32_t* p0, const int32_t* p
 // pinned staging: at 16 qubits the eleven waits and twelve pageable copies it
 // took before were half of the grouping's time.
 static void build_sector_tables(pbs_grouped& g, const uint64_t* x, const uint32_t* n_groups, hipStream_t s,
-                                const std::function<void(uint64_t)>& groups_known) {
+                                const std::function<void(uint64_t, uint32_t)>& groups_known) {
   const uint64_t m = g.n_terms;
   const uint32_t h = g.n_qubits / 2;
   g.half = h;
@@ -286,11 +296,11 @@ static void build_sector_tables(pbs_grouped& g, const uint64_t* x, const uint32_
     PBS_HIP(hipGetLastError());
     exclusive_scan_u32(alive.get(), apos.get(), m, n_alive, s);
   }
-  uint32_t groups = 0, first[2] = {0u, 0u};
-  if (m) st.fetch(&groups, n_groups, 1);
+  uint32_t groups[2] = {0u, 0u}, first[2] = {0u, 0u};
+  if (m) st.fetch(groups, n_groups, 2);
   st.fetch(first, n_alive, 2);
   st.wait();
-  groups_known(groups);
+  groups_known(groups[0], groups[1]);
   const uint64_t ma = first[0];
   g.n_pterm = static_cast<uint32_t>(ma);
   g.has_sector = true;
@@ -469,17 +479,19 @@ pbs_status pbs_group_by_xmask(const pbs_sum* hs, void* stream, pbs_grouped** out
       const uint64_t m = hs->n_terms;
       g->n_qubits = hs->n_qubits;
       g->n_terms = m;
-      DevBuf<uint32_t> heads(m, s), gid(m, s), cnt(1, s);
+      DevBuf<uint32_t> heads(m, s), gid(m, s), cnt(2, s);  // cnt: groups, those with signs
       g->zk.alloc(m);
       g->ck.alloc(2 * m);
       if (m) {
         hipLaunchKernelGGL(k_csr_terms, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), hs->z.get(),
-                           hs->coeff.get(), m, g->zk.get(), g->ck.get());
-        hipLaunchKernelGGL(k_x_heads, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), m, heads.get());
+                           hs->coeff.get(), m, g->zk.get(), g->ck.get(), cnt.get() + 1);
+        hipLaunchKernelGGL(k_x_heads, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), g->zk.get(),
+                           g->ck.get(), m, heads.get(), cnt.get() + 1);
         exclusive_scan_u32(heads.get(), gid.get(), m, cnt.get(), s);
       }
-      auto groups_known = [&](uint64_t G) {
+      auto groups_known = [&](uint64_t G, uint32_t n_signed) {
         g->n_groups = G;
+        g->n_signed = n_signed;
         g->xg.alloc(G);
         g->off.alloc(G + 1);
         hipLaunchKernelGGL(k_csr_groups, dim3(grid_for(m, 256, 65536)), dim3(256), 0, s, hs->x.get(), m, heads.get(),
@@ -488,8 +500,12 @@ pbs_status pbs_group_by_xmask(const pbs_sum* hs, void* stream, pbs_grouped** out
       };
       if ((g->n_qubits % 2) == 0)
         build_sector_tables(*g, hs->x.get(), cnt.get(), s, groups_known);
-      else
-        groups_known(m ? read_scalar(cnt.get(), s) : 0u);
+      else if (m) {
+        const uint2 n = read_scalar(reinterpret_cast<const uint2*>(cnt.get()), s);
+        groups_known(n.x, n.y);
+      } else {
+        groups_known(0, 0);
+      }
       PBS_HIP(hipStreamSynchronize(s));
     } catch (...) {
       delete g;

@@ -169,6 +169,7 @@ struct FactorPlan {
 struct pbs_grouped {
   uint32_t n_qubits = 0;
   uint64_t n_groups = 0;
+  uint32_t n_signed = 0;  // groups of more than one real term without Z bits
   uint64_t n_terms = 0;
   pbs::DevBuf<uint64_t> xg;
   pbs::DevBuf<uint32_t> off;

@@ -177,6 +177,25 @@ inline uint32_t panel_batch_rows(std::vector<std::pair<uint32_t, uint32_t>> jobs
   return best;
 }
 
+// Targets per lane of the full-space kernel: as many as leave a workgroup of 256
+// lanes per compute unit; eight of 16 bytes cost too many registers (102 us at 22
+// sites, 83 with four).  1: the kernel without tiles.  Tiles share a group's loads
+// among targets, but one workgroup per unit waits for each of them in turn, and a
+// group with signs takes twice as long there as a run of groups without: so few
+// lanes take tiles only for operators that are mostly such runs.  Without and
+// with tiles, us: 18 sites complex64, Ising chain (1 of 19 groups signed) 10.6 / 9.6,
+// 40 random strings 17.9 / 25.3, 2,000 659 / 1,094; 17 sites, chain, complex128 9.2 /
+// 8.3; 20 sites, 500 random strings 500 / 500 and 562 / 465, 10 orbitals 6,360 /
+// 4,470; one target per lane in tiles: 14 sites, 300 random strings 71 / 104, 6
+// orbitals 197 / 209, chains of up to 16 sites equal.
+constexpr uint32_t kFullLanes = 256;
+inline uint32_t full_tile(uint64_t dim, uint64_t groups, uint64_t with_signs, uint32_t elem, uint32_t cus) {
+  const uint64_t lanes = dim / kFullLanes;
+  if (lanes < 2ull * cus || (lanes < 16ull * cus && 4 * with_signs > groups)) return 1;
+  if (elem == 8 && lanes >= 8ull * cus) return 8;
+  return lanes >= 4ull * cus ? 4 : 2;
+}
+
 inline uint32_t align16(uint32_t v) { return (v + 15u) & ~15u; }
 
 // What the layout depends on: the device's LDS per workgroup (less the

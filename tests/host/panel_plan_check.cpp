@@ -119,9 +119,33 @@ static int print_split(char** v) {
   return 0;
 }
 
+// Targets per lane of the full-space kernels on both sides of every line of
+// full_tile (256 compute units); tiles are whole wherever they are used.
+static void check_full_tile() {
+  struct Case {
+    uint32_t sites, groups, with_signs, c64, c128;
+  };
+  const Case cases[] = {{0, 1, 1, 1, 1},     {6, 7, 1, 1, 1},     {16, 17, 1, 1, 1},   {17, 18, 1, 2, 2},
+                        {17, 40, 40, 1, 1},  {18, 19, 1, 4, 4},   {18, 16, 4, 4, 4},   {18, 16, 5, 1, 1},
+                        {19, 20, 1, 8, 4},   {19, 20, 20, 1, 1},  {20, 500, 500, 8, 4}, {22, 23, 1, 8, 4}};
+  for (const Case& c : cases)
+    for (uint32_t elem : {8u, 16u}) {
+      const uint32_t r = full_tile(1ull << c.sites, c.groups, c.with_signs, elem, 256);
+      CHECK(r == (elem == 8 ? c.c64 : c.c128), "%u sites, %u of %u groups with signs, %u bytes: %u", c.sites,
+            c.with_signs, c.groups, elem, r);
+    }
+  for (uint32_t cus : {32u, 64u, 128u, 256u, 304u})
+    for (uint32_t sites = 0; sites < 30; ++sites)
+      for (uint32_t elem : {8u, 16u}) {
+        const uint32_t r = full_tile(1ull << sites, 4, 1, elem, cus);
+        CHECK(r == 1 || (1ull << sites) % (kFullLanes * r) == 0, "%u sites, %u units: %u", sites, cus, r);
+      }
+}
+
 int main(int argc, char** argv) {
   if (argc == 5) return print_split(argv);
   check_pull_region();
+  check_full_tile();
   check_panel_pays();
   check_batch_rows();
   if (g_fail) return 1;
