@@ -530,7 +530,7 @@ bool plan_lists(const pbs_grouped& h, const pbs_space& sp, const SectorArgs& a, 
                 ListsArgs* out, size_t* lds) {
   const FactorPlan* F = h.fplan.get();
   if (!r16 || a.row_lds || a.alist_off == nullptr || F == nullptr || !F->blist || !(h.fact_on & kFactMoves) ||
-      F->n_beta != sp.n_beta || F->dim_beta != sp.dim_beta)
+      F->n_beta != sp.n_beta || F->dim_beta != sp.dim_beta || !lists_pays(F->bl_narrow, F->alist_max))
     return false;
   ListsArgs L{};
   const uint32_t nu = F->bl_ub - F->bl_ua;

@@ -177,6 +177,15 @@ inline uint32_t panel_batch_rows(std::vector<std::pair<uint32_t, uint32_t>> jobs
   return best;
 }
 
+// Whether the lists kernel is the faster one for rows too long for the sector
+// kernel's staging (shorter rows were not compared): its gathers of other rows
+// beyond the first kListRowsAhead wait one by one, which shows when the rows have
+// many and the columns' entries look up their magnitudes.  Rows kernel against
+// lists kernel, 16 orbitals, complex64, hops between all pairs: 60 gathers a row,
+// 120 magnitudes 13.5 / 13.0 ms, 64 gathers 21.5 / 22.1; one magnitude, 64
+// gathers, 19.1 / 15.5.
+inline bool lists_pays(bool one_magnitude, uint32_t longest_list) { return one_magnitude || longest_list <= 60; }
+
 // Targets per lane of the full-space kernel: as many as leave a workgroup of 256
 // lanes per compute unit; eight of 16 bytes cost too many registers (102 us at 22
 // sites, 83 with four).  1: the kernel without tiles.  Tiles share a group's loads

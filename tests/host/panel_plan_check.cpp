@@ -142,10 +142,18 @@ static void check_full_tile() {
       }
 }
 
+// Lists or rows kernel, on both sides of the line.
+static void check_lists_pays() {
+  CHECK(lists_pays(true, 64) && lists_pays(true, 16) && lists_pays(false, 60) && !lists_pays(false, 61) &&
+            !lists_pays(false, 64),
+        "lists kernel's line");
+}
+
 int main(int argc, char** argv) {
   if (argc == 5) return print_split(argv);
   check_pull_region();
   check_full_tile();
+  check_lists_pays();
   check_panel_pays();
   check_batch_rows();
   if (g_fail) return 1;
