@@ -103,7 +103,8 @@ inline double panel_fill(int variant, uint32_t alpha_hops, uint32_t beta_hops) {
 //    87 against 77, (11; 2, 5) 75 against 66.  A second row for some workgroups
 //    doubles the panel kernel's time: (14; 3, 3), 364 rows, complex64 175 / 180,
 //    complex128 211 / 189.  495 columns of 12 orbitals: (12; 3, 4) complex64
-//    101 / 111, complex128 118 / 116; eight jobs of (12; 4, 4) complex64 1,329 / 1,475
+//    101 / 111, complex128 118 / 116; (12; 4, 4), two rows, 167 / 210 and 216 / 220, and
+//    eight jobs of it 1,329 / 1,475 and 1,846 / 1,544
 //  * long rows, fewer than compute units: (14; 1, 7) complex64 117 / 600, (14; 2, 7)
 //    complex64 355 / 642, complex128 472 / 648; (12; 3, 6), 220 rows, complex64
 //    166 / 181, complex128 214 / 171
@@ -115,7 +116,8 @@ inline double panel_fill(int variant, uint32_t alpha_hops, uint32_t beta_hops) {
 inline bool panel_pays(int variant, uint64_t rows, uint64_t cols, double fill, uint32_t elem, uint32_t cus) {
   if (variant == 0) return true;
   const bool narrow = cols <= 400;
-  if (elem > 8) return narrow || 4 * rows >= 3ull * cus;
+  if (elem > 8)
+    return narrow || (4 * rows >= 3ull * cus && (cols > kPanelLanes || rows <= cus || rows >= 4ull * cus));
   const bool many = 2 * rows >= 3ull * cus;
   if (cols <= kPanelLanes) return narrow && (many || rows <= cus);
   if (many) return fill >= 0.25;

@@ -76,11 +76,11 @@ static void check_panel_pays() {
   const Case cases[] = {
       {4, 2, 2, 1, 1, 1},   {11, 2, 5, 1, 1, 1},  {11, 5, 6, 1, 1, 1},  {12, 2, 3, 1, 1, 1},  {12, 3, 3, 1, 1, 1},
       {13, 3, 3, 1, 0, 1},  {14, 3, 3, 1, 0, 1},  {14, 1, 3, 1, 1, 1},  {12, 1, 4, 1, 0, 0},  {12, 3, 4, 1, 0, 1},
-      {12, 4, 4, 1, 0, 1},  {12, 1, 6, 1, 0, 0},  {12, 2, 6, 1, 0, 0},  {12, 3, 6, 1, 0, 1},  {12, 4, 6, 1, 1, 1},
+      {12, 4, 4, 1, 0, 0},  {12, 1, 6, 1, 0, 0},  {12, 2, 6, 1, 0, 0},  {12, 3, 6, 1, 0, 1},  {12, 4, 6, 1, 1, 1},
       {12, 6, 6, 1, 1, 1},  {13, 1, 6, 1, 0, 0},  {13, 2, 6, 1, 0, 0},  {13, 3, 5, 1, 0, 1},  {13, 3, 6, 1, 1, 1},
       {13, 4, 4, 1, 1, 1},  {14, 1, 7, 1, 0, 0},  {14, 2, 7, 1, 0, 0},  {14, 3, 4, 1, 0, 1},  {14, 3, 7, 1, 1, 1},
       {14, 7, 7, 1, 1, 1},  {14, 1, 7, 6, 0, 0},  {14, 1, 7, 24, 0, 1}, {14, 2, 7, 6, 0, 1},  {12, 3, 6, 6, 1, 1},
-      {12, 4, 4, 8, 0, 1},  {14, 3, 3, 6, 1, 1},  {12, 2, 3, 12, 1, 1}, {13, 3, 5, 6, 1, 1},
+      {12, 4, 4, 8, 0, 1},  {12, 3, 4, 8, 0, 1},  {14, 3, 3, 6, 1, 1},  {12, 2, 3, 12, 1, 1}, {13, 3, 5, 6, 1, 1},
   };
   for (const Case& c : cases) {
     const uint64_t rows = binomial(c.n, c.a), cols = binomial(c.n, c.b);
