@@ -648,7 +648,7 @@ uint64_t launch(const pbs_grouped& h, const pbs_space& sp, const void* psi, void
     PanelShape ps;
     // (the whole sector decides, so that a share of its rows runs the same kernel)
     if (plan_panel(h, sp, h.fplan.get(), h.fplan.get(), &pa, &ps) &&
-        panel_pays(ps.variant, sp.dim_alpha, sp.dim_beta, ps.fill, sizeof(T), device_cus())) {
+        panel_pays(ps.variant, sp.dim_alpha, sp.dim_alpha, sp.dim_beta, ps.fill, sizeof(T), device_cus())) {
       const uint32_t cus = device_cus(), groups = static_cast<uint32_t>((sp.dim_beta + kPanelLanes - 1) / kPanelLanes);
       pa.row_begin = static_cast<uint32_t>(row_begin);
       pa.rows = static_cast<uint32_t>(rows);
@@ -924,8 +924,9 @@ void fill_batch(pbs_batch& B, uint32_t config) {
   }
   for (uint32_t i = 0; i < n; ++i) {
     const PanelShape& ps = shape[i];
-    if (can[i] && (B.brought(i) || panel_pays(ps.variant, variant_rows[ps.variant], B.sp[i]->dim_beta, ps.fill,
-                                                   static_cast<uint32_t>(esz), cus)))
+    if (can[i] && (B.brought(i) ||
+                   panel_pays(ps.variant, variant_rows[ps.variant], B.sp[i]->dim_alpha, B.sp[i]->dim_beta, ps.fill,
+                              static_cast<uint32_t>(esz), cus)))
       by_variant[ps.variant].push_back(i);
     else
       sector.push_back(i);

@@ -113,7 +113,17 @@ inline double panel_fill(int variant, uint32_t alpha_hops, uint32_t beta_hops) {
 //    to 0.38 1.03 to 1.8 times as fast ((13; 5, 4) alone 0.99); 24 jobs of (14; 1, 7),
 //    0.13, 1,027 / 1,190, six of (14; 2, 7), 0.24, 1,749 / 2,048, six of (12; 3, 6),
 //    0.25, 894 / 849; complex128 faster throughout (gathers of 16 bytes)
-inline bool panel_pays(int variant, uint64_t rows, uint64_t cols, double fill, uint32_t elem, uint32_t cus) {
+//  * one sector of up to 512 columns whose rows need a second row in most
+//    workgroups: (12; 4, 3) complex64 140 / 156, complex128 158 / 164, (12; 4, 2) 112 / 123
+//    and 112 / 131; (11; 6, 7) 137 / 143 and 165 / 152, (11; 6, 8) 120 / 121 and 129 / 129,
+//    (11; 6, 9) 103 / 101 and 104 / 110, (11; 5, 5) 153 / 153 and 198 / 160
+// job_rows: the sector's own rows.
+inline bool panel_pays(int variant, uint64_t rows, uint64_t job_rows, uint64_t cols, double fill, uint32_t elem,
+                       uint32_t cus) {
+  if (rows == job_rows && cols <= kPanelLanes && 2 * rows >= 3ull * cus) {
+    if (variant != 0) return false;
+    return elem > 8 ? cols >= 128 : cols >= rows || cols <= 64;
+  }
   if (variant == 0) return true;
   const bool narrow = cols <= 400;
   if (elem > 8)

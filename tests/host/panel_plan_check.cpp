@@ -81,6 +81,8 @@ static void check_panel_pays() {
       {13, 4, 4, 1, 1, 1},  {14, 1, 7, 1, 0, 0},  {14, 2, 7, 1, 0, 0},  {14, 3, 4, 1, 0, 1},  {14, 3, 7, 1, 1, 1},
       {14, 7, 7, 1, 1, 1},  {14, 1, 7, 6, 0, 0},  {14, 1, 7, 24, 0, 1}, {14, 2, 7, 6, 0, 1},  {12, 3, 6, 6, 1, 1},
       {12, 4, 4, 8, 0, 1},  {12, 3, 4, 8, 0, 1},  {14, 3, 3, 6, 1, 1},  {12, 2, 3, 12, 1, 1}, {13, 3, 5, 6, 1, 1},
+      {12, 4, 3, 1, 0, 0},  {12, 4, 2, 1, 0, 0},  {12, 4, 3, 4, 1, 1},  {11, 6, 7, 1, 0, 1},  {11, 6, 8, 1, 0, 1},
+      {11, 6, 9, 1, 1, 0},  {11, 5, 5, 1, 1, 1},  {11, 4, 3, 1, 1, 1},  {11, 6, 7, 2, 1, 1},  {13, 3, 2, 1, 0, 1},
   };
   for (const Case& c : cases) {
     const uint64_t rows = binomial(c.n, c.a), cols = binomial(c.n, c.b);
@@ -91,7 +93,7 @@ static void check_panel_pays() {
     CHECK(fill > 0.0 && fill < 1.0, "(%u; %u, %u) fill %g", c.n, c.a, c.b, fill);
     for (uint32_t elem : {8u, 16u}) {
       const int want = elem == 8 ? c.c64 : c.c128;
-      CHECK(panel_pays(v, rows * c.jobs, cols, fill, elem, 256) == (want != 0), "%u x (%u; %u, %u), %u bytes: want %d",
+      CHECK(panel_pays(v, rows * c.jobs, rows, cols, fill, elem, 256) == (want != 0), "%u x (%u; %u, %u), %u bytes: want %d",
             c.jobs, c.n, c.a, c.b, elem, want);
     }
   }
@@ -114,8 +116,8 @@ static int print_split(char** v) {
   }
   const double fill = panel_fill(variant, a * (n - a), b * (n - b));
   const uint64_t all = static_cast<uint64_t>(rows) * (jobs ? jobs : 1);
-  std::printf("%d %u %d %d\n", variant, per, panel_pays(variant, all, cols, fill, 8, 256),
-              panel_pays(variant, all, cols, fill, 16, 256));
+  std::printf("%d %u %d %d\n", variant, per, panel_pays(variant, all, rows, cols, fill, 8, 256),
+              panel_pays(variant, all, rows, cols, fill, 16, 256));
   return 0;
 }
 
