@@ -519,8 +519,11 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const uint64_t b = panel_block_of(blockIdx.x, gridDim.x);
   const uint32_t r0 = static_cast<uint32_t>(b * P.rows / P.n_blk);
   const uint32_t r1 = static_cast<uint32_t>((b + 1) * P.rows / P.n_blk);
-  panel_body<T, EXPVAL, NT, MT, KS, R, QUEUED, false>(P, psi, out, partial + 3ull * r0, P.row_begin + r0, r1 - r0,
-                                                      skip, 0);
+  // (no block is empty, but without the test the compiler places 30 more register
+  // moves in the body: 28 qubits, complex64, 10.31 ms without, 10.29 with it)
+  if (r1 > r0)
+    panel_body<T, EXPVAL, NT, MT, KS, R, QUEUED, false>(P, psi, out, partial + 3ull * r0, P.row_begin + r0, r1 - r0,
+                                                        skip, 0);
 }
 
 // Launches of few rows (a share of a sector): `parts` workgroups per row, NT
